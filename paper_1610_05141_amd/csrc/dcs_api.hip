@@ -340,6 +340,7 @@ int32_t device_ctx(DeviceCtx** out) {
     if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return DCS_EHIP;
     c.cus = prop.multiProcessorCount;
     c.leaf_occupancy = dcs::leaf_occupancy();
+    c.sort_occupancy = dcs::sort_occupancy();
     c.bern_wave_occupancy = dcs::bern_wave_occupancy();
     c.wb_occupancy = dcs::wb_occupancy();
     c.small_occupancy = dcs::small_occupancy();
@@ -451,7 +452,7 @@ void timing_end(hipStream_t s, Timing* t) {
 
 // Leaf kinds that no leaf of a single instance's tree can have except by a
 // deviation of its counts from their expectations by tens of standard
-// deviations; their kernels are then not launched and k_leaf_mixed runs any
+// deviations; their kernels are then not launched and k_leaf_sort runs any
 // such leaf itself (the sample never depends on this).  A leaf's parent held
 // n0 or more values or a range above 2^32.  Dense leaves (dense_ratio n_v >=
 // N_v) then need some range of at most 2 dense_ratio n0 elements at density
@@ -474,12 +475,16 @@ uint32_t mixed_takes(const Instance& I) {
   return takes;
 }
 
+bool has_wide_dense(uint32_t variant, uint32_t n0, uint32_t dense_ratio) {
+  return variant == 0 && static_cast<uint64_t>(dense_ratio) * (n0 - 1) > (1u << 16);
+}
+
 // Enqueue reset + tree + leaf for the instances already in the workspace.
 int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Instance* single,
                           uint32_t n_inst, uint64_t threads, uint64_t top_threads,
                           uint64_t leaf_cap, uint32_t stack_depth, uint64_t* out, hipStream_t s,
-                          unsigned int* err, uint32_t leaf_wgs_per_cu, uint64_t* part_out,
-                          const Instance* whole) {
+                          unsigned int* err, uint32_t leaf_wgs_per_cu, bool wide_dense,
+                          uint64_t* part_out, const Instance* whole) {
   if (leaf_cap >= dcs::kMaxLeafJobs) return DCS_ENOMEM;
   char* base = static_cast<char*>(ws);
   Control* ctl = reinterpret_cast<Control*>(base + L.ctl);
@@ -501,9 +506,12 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
                          ctl, redo, 0, s);
   timing_end(s, &t1);
   if (e != hipSuccess) return DCS_EHIP;
+  // work-groups of the 512-thread kernels, and of the sort kernel
   uint64_t want = static_cast<uint64_t>(c->cus) * std::max<uint32_t>(1, leaf_wgs_per_cu);
-  if (c->leaf_grid > 0) want = static_cast<uint64_t>(c->leaf_grid);
+  uint64_t sort_want = static_cast<uint64_t>(c->cus) * std::max(1, c->sort_occupancy);
+  if (c->leaf_grid > 0) want = sort_want = static_cast<uint64_t>(c->leaf_grid);
   want = std::max<uint64_t>(1, std::min<uint64_t>(want, leaf_cap));
+  sort_want = std::max<uint64_t>(1, std::min<uint64_t>(sort_want, leaf_cap));
   // batches launch every leaf kernel; a single instance, or the parts of
   // one sample, skip those whose kinds the sample's tree cannot plausibly hold
   if (whole == nullptr && single != nullptr && n_inst == 1) whole = single;
@@ -513,20 +521,19 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   Timing t4{}, t5{};
   timing_begin(2, s, &t2);
   timing_begin(4, s, &t4);
-  e = dcs::launch_leaf(dcs::kLeafFront, leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want),
-                       s);
+  e = dcs::launch_leaf_sort(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(sort_want), s, 0,
+                            takes);
   timing_end(s, &t4);
   if (e == hipSuccess) {
     timing_begin(5, s, &t5);
-    e = dcs::launch_leaf(dcs::kLeafBack, leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want),
-                         s, takes);
+    if (wide_dense)
+      e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 0);
     timing_end(s, &t5);
   }
   Timing t13{};
   if (e == hipSuccess && !(takes & dcs::kTakesOnce)) {
     timing_begin(13, s, &t13);
-    e = dcs::launch_leaf(dcs::kLeafOnce, leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want),
-                         s);
+    e = dcs::launch_leaf_once(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s);
     timing_end(s, &t13);
   }
   Timing t6{};
@@ -548,14 +555,16 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
     timing_end(s, &t12);
   }
   // Second round: the tree threads marked in `redo` run again into the
-  // emptied job array, and one work-group pass samples their leaves (both
+  // emptied job array, and the work-group kernels sample their leaves (they
   // return at once when nothing was marked).
   if (e == hipSuccess && redo != nullptr)
     e = dcs::launch_tree(inst, n_inst, threads, frontier, leaves, leaf_cap, stacks, stack_depth,
                          ctl, redo, 1, s);
   if (e == hipSuccess && redo != nullptr)
-    e = dcs::launch_leaf_round2(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s,
-                                takes);
+    e = dcs::launch_leaf_sort(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(sort_want), s, 1,
+                              takes);
+  if (e == hipSuccess && redo != nullptr && wide_dense)
+    e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 1);
   timing_end(s, &t2);
   if (e != hipSuccess) return DCS_EHIP;
   return DCS_OK;
@@ -606,7 +615,8 @@ int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, con
   I.top_cut = pl.top_cut;
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out, static_cast<hipStream_t>(stream),
-                           error_word(c, stream), leaf_wgs_for(c, variant, n));
+                           error_word(c, stream), leaf_wgs_for(c, variant, n),
+                           has_wide_dense(variant, P.n0, P.dense_ratio));
 }
 
 struct BernLayout {
@@ -744,7 +754,8 @@ int32_t dcs_sample_part(int32_t variant, uint64_t n, uint64_t N, uint64_t seed,
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out_dev, static_cast<hipStream_t>(stream),
                            error_word(c, stream),
-                           leaf_wgs_for(c, static_cast<uint32_t>(variant), np), count_rank_dev);
+                           leaf_wgs_for(c, static_cast<uint32_t>(variant), np),
+                           has_wide_dense(I.variant, P.n0, P.dense_ratio), count_rank_dev);
 }
 
 int32_t dcs_sample_segments(uint64_t n, const uint64_t* lengths, uint64_t K, uint64_t seed,
@@ -824,7 +835,7 @@ int32_t dcs_sample_segments(uint64_t n, const uint64_t* lengths, uint64_t K, uin
   if (n == 0) return DCS_OK;
   return run_tree_pipeline(c, ws, L, nullptr, static_cast<uint32_t>(K), tb, tt, leaf_cap,
                            stack_depth, out_dev, s, error_word(c, stream),
-                           leaf_wgs_for(c, 0, n));
+                           leaf_wgs_for(c, 0, n), has_wide_dense(0, P.n0, P.dense_ratio));
 }
 
 int32_t dcs_sample_wholerange(uint64_t n, uint64_t N, uint64_t seed, const dcs_params* params,
@@ -1012,6 +1023,7 @@ struct dcs_batch {
   uint64_t threads = 0, top_threads = 0, leaf_cap = 0, total_out = 0;
   uint32_t stack_depth = 1;
   bool second_round = false;
+  bool wide_dense = false;
   TreeLayout layout;
   void* ws = nullptr;
   int device = 0;
@@ -1059,6 +1071,7 @@ int32_t dcs_batch_create(const dcs_instance* instances, uint32_t count, dcs_batc
     tt += pl.threads ? pl.top_threads : 0;
     b->leaf_cap += pl.leaf_cap;
     b->second_round = b->second_round || pl.second_round;
+    b->wide_dense = b->wide_dense || has_wide_dense(d.variant, P.n0, P.dense_ratio);
     b->stack_depth = std::max(b->stack_depth, pl.stack_depth);
     b->total_out += d.n;
     b->host.push_back(I);
@@ -1097,7 +1110,7 @@ int32_t dcs_batch_run(dcs_batch* b, uint64_t* out_dev, int32_t use_graph, void* 
   if (!use_graph || g_profile) {
     return run_tree_pipeline(c, b->ws, b->layout, nullptr, n_inst, b->threads, b->top_threads,
                              b->leaf_cap, b->stack_depth, out_dev, s, err,
-                             leaf_wgs_for(c, 0, b->total_out));
+                             leaf_wgs_for(c, 0, b->total_out), b->wide_dense);
   }
   if (s == nullptr) return DCS_EINVAL;  // capture needs a real stream
   // the captured reset names the output and the stream's error word:
@@ -1114,7 +1127,7 @@ int32_t dcs_batch_run(dcs_batch* b, uint64_t* out_dev, int32_t use_graph, void* 
     if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) return DCS_EHIP;
     rc = run_tree_pipeline(c, b->ws, b->layout, nullptr, n_inst, b->threads, b->top_threads,
                            b->leaf_cap, b->stack_depth, out_dev, s, err,
-                           leaf_wgs_for(c, 0, b->total_out));
+                           leaf_wgs_for(c, 0, b->total_out), b->wide_dense);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(s, &g);
     if (rc != DCS_OK) return rc;
@@ -1278,7 +1291,8 @@ int32_t dcs_online_next(dcs_online* o, uint64_t first, uint64_t count, uint64_t*
   whole.dense_ratio = o->P.dense_ratio;
   whole.variant = v;
   return run_tree_pipeline(c, ws, L, nullptr, n_inst, tb, tt, leaf_cap, stack_depth, out_dev, s,
-                           error_word(c, stream), leaf_wgs_for(c, v, total), nullptr, &whole);
+                           error_word(c, stream), leaf_wgs_for(c, v, total),
+                           has_wide_dense(v, o->P.n0, o->P.dense_ratio), nullptr, &whole);
 }
 
 int32_t dcs_online_destroy(dcs_online* o) {

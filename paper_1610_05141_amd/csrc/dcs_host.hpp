@@ -56,6 +56,7 @@ struct DeviceCtx {
   bool init = false;
   int cus = 256;
   int leaf_occupancy = 2;
+  int sort_occupancy = 4;
   int bern_wave_occupancy = 8;
   int dense_occupancy = 8;
   int wb_occupancy = 8;
@@ -112,6 +113,7 @@ int32_t device_ctx(DeviceCtx** out);
 // holds lock().
 // Leaf work-groups: DCS_LEAF_GRID if set, else cus * leaf_wgs_per_cu (both
 // leaf kernels use it).
+// wide_dense: some instance's tree satisfies has_wide_dense.
 // whole: an instance whose canonical tree holds every leaf of the launch
 // (the sample whose parts the instances are); with `single` it decides which
 // specialised leaf kernels can be left out.
@@ -119,7 +121,11 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
                           uint32_t n_inst, uint64_t threads, uint64_t top_threads,
                           uint64_t leaf_cap, uint32_t stack_depth, uint64_t* out, hipStream_t s,
                           unsigned int* err, uint32_t leaf_wgs_per_cu,
-                          uint64_t* part_out = nullptr, const Instance* whole = nullptr);
+                          bool wide_dense, uint64_t* part_out = nullptr,
+                          const Instance* whole = nullptr);
+// Whether an instance's tree can hold dense leaves over ranges above 2^16
+// (dense_ratio n_v >= N_v > 2^16 with n_v < n0), which k_leaf_mixed runs.
+bool has_wide_dense(uint32_t variant, uint32_t n0, uint32_t dense_ratio);
 
 // Kernel timing with pooled HIP events on the launch stream (dcs_profile_*):
 // kinds as listed at dcs_profile_read; caller holds lock().

@@ -6,13 +6,13 @@
 //                exactly as a processing element of Algorithm P does
 //                (paper Sec. 3.2, Fig. 2), then expands the subtree below by
 //                a depth-first walk; every leaf becomes a self-contained job.
-//   k_leaf       persistent work-groups, each taking every G-th leaf job (the
+//   k_leaf_*     persistent work-groups, each taking every G-th leaf job (the
 //                atomic jobs of Sec. 4.2, assigned statically so that job
 //                records stream into LDS ahead of use), run the base case:
 //                  sparse  Algorithm H semantics (Sec. 2): the first n_v
-//                          distinct values of the node's stream, found in
-//                          rounds with an LDS counting sort by most
-//                          significant bits (the sorted-H idea of Sec. 4.1);
+//                          distinct values of the node's stream, in order by
+//                          an LDS counting sort by most significant bits
+//                          (the sorted-H idea of Sec. 4.1);
 //                  dense   Algorithm B (Sec. 2): geometric skips + prefix sum
 //                          (Sec. 4.7), restart on a short sample, removal of
 //                          the excess by Algorithm H semantics;
@@ -339,11 +339,6 @@ __device__ __forceinline__ uint64_t window_pass(uint32_t* keys, uint32_t n, uint
 // counter whose scanned start is a spare slot, so the passes carry no
 // per-key branches.  Each key keeps its counter index | slot << 16 in one
 // register between the passes.
-// kLazyZero: the counters are zero on entry and are zeroed again once read
-// (during the first window pass), and the sentinels and the duplicate flag
-// are written after the counting barrier, so that a caller may start the next
-// sort without a barrier after this sort's result has been read; otherwise
-// everything is cleared on entry.
 // ---------------------------------------------------------------------------
 template <int B>
 __device__ __forceinline__ void zero_counters(uint32_t* cnt, uint32_t tid) {
@@ -352,13 +347,10 @@ __device__ __forceinline__ void zero_counters(uint32_t* cnt, uint32_t tid) {
   if (tid == 0) cnt[kSpareCount] = 0;
 }
 
-constexpr uint32_t kDeadKey = 0xFFFFFFFFu;  // counter/slot word of a key left out
-
-// kMasked: key[q] takes part iff bit q of `live` is set (n of them), wherever
-// it sits; otherwise key[q] takes part iff its position 4(tid + kB) + j < n.
-template <int B, bool kLazyZero = false, bool kMasked = false>
+// key[q] takes part iff its position 4(tid + kB) + j < n.
+template <int B>
 __device__ uint32_t sort_registers(const uint32_t (&key)[kKeys / B], uint32_t n, uint32_t shift,
-                                   uint32_t nb, LeafSmem& sm, uint32_t live_mask = 0) {
+                                   uint32_t nb, LeafSmem& sm) {
   constexpr int kBlk = kKeys / (4 * B);
   constexpr int kPer = kBuckets / B;  // buckets per thread in the scan
   constexpr int kPairs = kKeys / (2 * B);
@@ -369,29 +361,15 @@ __device__ uint32_t sort_registers(const uint32_t (&key)[kKeys / B], uint32_t n,
   uint32_t* cnt = sm.buck;
   uint32_t* keys = sm.keys;
   // 1. zero the counters, sentinels after the keys, count
-  if (!kLazyZero) {
-    zero_counters<B>(cnt, tid);
-    if (tid < 24) keys[n + tid] = 0xFFFFFFFFu;
-    if (tid == 0) sm.scr[kScrDups] = 0;
-    __syncthreads();
-  }
+  zero_counters<B>(cnt, tid);
+  if (tid < 24) keys[n + tid] = 0xFFFFFFFFu;
+  if (tid == 0) sm.scr[kScrDups] = 0;
+  __syncthreads();
   uint32_t as[4 * kBlk];
 #pragma unroll
   for (int k = 0; k < kBlk; ++k) {
     const uint32_t first = 4 * (wave_first + k * B);  // first key position of the wave
-    if (kMasked) {
-      // dead keys skip the counters and the scatter (all of them on one
-      // spare word would serialize the LDS accesses of the whole wave)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int q = 4 * k + j;
-        as[q] = kDeadKey;
-        if ((live_mask >> q) & 1u) {
-          const uint32_t a = bpad(key[q] >> shift);
-          as[q] = a | (atomicAdd(&cnt[a], 1u) << 16);
-        }
-      }
-    } else if (first + 256 <= n) {                    // every lane holds 4 keys
+    if (first + 256 <= n) {                    // every lane holds 4 keys
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int q = 4 * k + j;
@@ -411,10 +389,6 @@ __device__ uint32_t sort_registers(const uint32_t (&key)[kKeys / B], uint32_t n,
   __syncthreads();
   // 2. scan: thread tid owns buckets [kPer tid, kPer tid + kPer), contiguous
   // words from bpad(kPer tid)
-  if (kLazyZero) {
-    if (tid < 24) keys[n + tid] = 0xFFFFFFFFu;
-    if (tid == 0) sm.scr[kScrDups] = 0;
-  }
   {
     uint32_t* run8 = cnt + bpad(kPer * tid);
     uint32_t c[kPer];
@@ -443,13 +417,7 @@ __device__ uint32_t sort_registers(const uint32_t (&key)[kKeys / B], uint32_t n,
   // 3. scatter in bucket order (unused positions land on the spare slot)
 #pragma unroll
   for (int k = 0; k < kBlk; ++k) {
-    if (kMasked) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int q = 4 * k + j;
-        if (as[q] != kDeadKey) keys[cnt[as[q] & 0xFFFFu] + (as[q] >> 16)] = key[q];
-      }
-    } else if (4 * (wave_first + k * B) < n) {
+    if (4 * (wave_first + k * B) < n) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int q = 4 * k + j;
@@ -459,14 +427,7 @@ __device__ uint32_t sort_registers(const uint32_t (&key)[kKeys / B], uint32_t n,
   }
   __syncthreads();
   // 4. order inside buckets
-  if (shift == 0 || cmax <= 1) {
-    if (kLazyZero) {
-      zero_counters<B>(cnt, tid);
-      __syncthreads();
-    }
-    return (shift == 0 && cmax >= 2) ? 1u : 0u;
-  }
-  if (kLazyZero) zero_counters<B>(cnt, tid);  // read for the last time in the scatter
+  if (shift == 0 || cmax <= 1) return (shift == 0 && cmax >= 2) ? 1u : 0u;
   if (cmax <= 9) {
     uint64_t dup;
     // the second pass's windows are two sorted halves of first-pass windows
@@ -609,7 +570,7 @@ __device__ __forceinline__ void write_sorted_pairs(uint64_t* out, uint64_t base,
 // ---------------------------------------------------------------------------
 // Rounds after the first: keys[0..have) hold distinct values; draw the next
 // (nv - have) non-void values from word t on, sort, repeat while values repeat.
-template <int B, bool kLazyZero = false>
+template <int B>
 __device__ void sparse_rounds(const Stream& st, uint64_t t, uint32_t have, uint32_t nv,
                               const RangeInfo& ri, uint32_t shift, uint32_t nb, LeafSmem& sm) {
   uint32_t* keys = sm.keys;
@@ -620,67 +581,9 @@ __device__ void sparse_rounds(const Stream& st, uint64_t t, uint32_t have, uint3
                        [&](uint32_t p, uint32_t v) { keys[base + p] = v; });
     load_registers<B>(key, keys, nv);
     __syncthreads();
-    if (sort_registers<B, kLazyZero>(key, nv, shift, nb, sm) == 0) return;
+    if (sort_registers<B>(key, nv, shift, nb, sm) == 0) return;
     have = compact_distinct<B>(keys, sm.tmp, sm.scr, nv);
   }
-}
-
-// First round of a sparse or with-replacement leaf over a range that is not a
-// power of two, in registers: the words t < W of the stream mapped into
-// [0, N_v), W = n_v plus twice the expected number of void words among n_v,
-// plus 32 (at most 4096); the first
-// n_v non-void values in stream order are the live keys (bit q of *live for
-// key[q]), ranked by one block scan.  Returns how many of the W words are
-// non-void (below n_v the caller takes the LDS rounds instead); when it is at
-// least n_v, sm.scr[kScrNext] holds the word index just after the n_v-th
-// value once a barrier has passed.
-template <int B>
-__device__ uint32_t first_round_regs(const Stream& st, uint32_t nv, const RangeInfo& ri,
-                                     uint32_t (&key)[kKeys / B], uint32_t* live, LeafSmem& sm) {
-  constexpr int kBlk = kKeys / (4 * B);
-  static_assert(kBlk == 2, "two 16-bit counts share one scanned word");
-  const uint32_t tid = lane_tid();
-  const uint64_t extra = ((2ull * nv * ri.thr) >> 32) + 32u;
-  const uint32_t W = nv + extra < kKeys ? nv + static_cast<uint32_t>(extra) : kKeys;
-  const uint32_t nblk = (W + 3) >> 2;
-  uint32_t ok = 0;
-#pragma unroll
-  for (int k = 0; k < kBlk; ++k) {
-    const uint32_t blk = tid + k * B;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) key[4 * k + j] = 0;
-    if (blk < nblk) {
-      const uint4 w = philox_block(st, blk);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t v;
-        const bool good = range_map(pick(w, j), ri.s, ri.thr, &v);
-        key[4 * k + j] = v;
-        if (good && 4 * blk + j < W) ok |= 1u << (4 * k + j);
-      }
-    }
-  }
-  uint32_t total;
-  const uint32_t packed = static_cast<uint32_t>(__popc(ok & 0xFu)) |
-                          (static_cast<uint32_t>(__popc(ok >> 4)) << 16);
-  const uint32_t excl = block_scan_excl<B, uint32_t>(packed, sm.scr, &total);
-  const uint32_t total0 = total & 0xFFFFu;
-  uint32_t m = 0;
-#pragma unroll
-  for (int k = 0; k < kBlk; ++k) {
-    const uint32_t base = k == 0 ? (excl & 0xFFFFu) : total0 + (excl >> 16);
-    const uint32_t okk = (ok >> (4 * k)) & 0xFu;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t rank = base + static_cast<uint32_t>(__popc(okk & ((1u << j) - 1u)));
-      if (((okk >> j) & 1u) && rank < nv) {
-        m |= 1u << (4 * k + j);
-        if (rank == nv - 1) sm.scr[kScrNext] = 4 * (tid + k * B) + j + 1;
-      }
-    }
-  }
-  *live = m;
-  return total0 + (total >> 16);
 }
 
 // A sparse leaf whose first n_v values are expected to repeat (n_v^2 / (2 N_v)
@@ -873,32 +776,6 @@ __device__ const uint32_t* leaf_sparse_once(const Stream& st, uint32_t nv, const
   return keys;
 }
 
-template <int B>
-__device__ void leaf_sparse(const Leaf& L, uint64_t* out, LeafSmem& sm) {
-  const uint32_t nv = L.nv;
-  if (nv == 0) return;
-  const RangeInfo ri = range_info(L.Nv);
-  uint32_t shift, nb;
-  bucket_params(L.Nv, nv, &shift, &nb);
-  const Stream st = make_stream(L.seed, L.id, kLeaf, 0);
-  uint32_t key[kKeys / B];
-  uint32_t live;
-  const uint32_t got = first_round_regs<B>(st, nv, ri, key, &live, sm);
-  __builtin_amdgcn_s_setprio(2);  // the sort and its rounds ahead of other work-groups
-  if (got >= nv) {
-    if (sort_registers<B, false, true>(key, nv, shift, nb, sm, live) != 0) {
-      const uint64_t t = sm.scr[kScrNext];
-      const uint32_t have = compact_distinct<B>(sm.keys, sm.tmp, sm.scr, nv);
-      sparse_rounds<B>(st, t, have, nv, ri, shift, nb, sm);
-    }
-  } else {
-    // too many void words among the first W: the general rounds from word 0
-    sparse_rounds<B>(st, 0, 0, nv, ri, shift, nb, sm);
-  }
-  __builtin_amdgcn_s_setprio(0);
-  write_sorted_pairs<B>(out + L.off, L.lo, sm.keys, nv);
-}
-
 // Sparse leaves of more than kSmallMax values whose first n_v values are
 // expected to repeat (n_v^2 >= 2 N_v, any range) run in k_leaf_once, in one
 // pass; k_leaf_mixed skips them, so that its own leaf bodies keep their
@@ -916,72 +793,501 @@ __device__ void leaf_once(const Leaf& L, uint64_t* out, LeafSmem& sm) {
   write_sorted_pairs<B>(out + L.off, L.lo, sorted, nv);
 }
 
-// Sparse or with-replacement leaf on a power-of-two range (no word is void):
-// the first round's n_v words go from Philox straight into registers; for a
-// sparse leaf the general rounds take over only if a value repeats (a
-// with-replacement leaf keeps repeats).
-template <int B>
-__device__ void leaf_sparse_pow2(const Leaf& L, uint64_t* out, LeafSmem& sm) {
-  constexpr int kBlk = kKeys / (4 * B);
-  const uint32_t tid = lane_tid();
-  const uint32_t nv = L.nv;
-  const uint32_t kb = bit_length(L.Nv) - 1;        // range = 2^kb, 1 <= kb <= 32
-  const uint32_t pshift = 32u - kb;                 // value = word >> pshift
-  uint32_t shift, nb;
-  bucket_params(L.Nv, nv, &shift, &nb);
-  const bool wr = (L.flags & 3u) == kKindWr;
-  const Stream st = make_stream(L.seed, L.id, wr ? kWrLeaf : kLeaf, 0);
-  const uint32_t nblk = (nv + 3) >> 2;
-  uint32_t key[kKeys / B];
-#pragma unroll
-  for (int k = 0; k < kBlk; ++k) {
-    const uint32_t blk = tid + k * B;  // tid is opaque: no Philox round is hoisted
-    if (blk < nblk) {
-      const uint4 w = philox_block(st, blk);
-      key[4 * k + 0] = w.x >> pshift;
-      key[4 * k + 1] = w.y >> pshift;
-      key[4 * k + 2] = w.z >> pshift;
-      key[4 * k + 3] = w.w >> pshift;
-    }
-  }
-  // The sort is a chain of barrier-separated LDS phases; at raised issue
-  // priority its waves go ahead of other work-groups' Philox and store
-  // instructions, so a work-group spends less time waiting at its barriers
-  // (the stores and the next leaf's draws fill the gaps).
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t dups = sort_registers<B, true>(key, nv, shift, nb, sm);
-  __builtin_amdgcn_s_setprio(0);
-  if (dups != 0 && !wr) {
-    const uint32_t have = compact_distinct<B>(sm.keys, sm.tmp, sm.scr, nv);
-    sparse_rounds<B, true>(st, nv, have, nv, range_info(L.Nv), shift, nb, sm);
-  }
-  write_sorted_pairs<B>(out + L.off, L.lo, sm.keys, nv);
+// ---------------------------------------------------------------------------
+// Sparse and with-replacement leaves: one work-group per leaf, sorted by the
+// leading bits of the raw stream words.
+//
+// The map from a 32-bit word to its value in [0, N_v) is monotone, so a leaf
+// sorts its words and maps them as they are written out; words are uniform
+// over 2^32 whatever the range, which keeps the buckets even for every N_v.
+//   1. count: bucket = word >> 19 (2^13 buckets, four-bit counters, eight to
+//      an LDS word); the atomic's old value gives the key its slot.  With
+//      4095 keys the largest bucket holds 5 or 6 most often, more than 8 in
+//      one leaf in 40,000.
+//   2. scan: 1024 counter words; the keys of a word are one dot product of
+//      its nibbles with ones.
+//   3. scatter: the word's prefix + the nibbles below the key's + its slot.
+//   4. rows: a wave takes 128 consecutive positions, two to a lane, runs as
+//      many odd-even transposition rounds as the largest bucket has keys
+//      (in-lane and neighbouring-lane exchanges, no LDS), and writes the
+//      inner positions; the outer 2 H lanes of a row are the neighbours' keys
+//      that a bucket at the row's edge may hold.
+// Equal neighbours are repeats (sparse leaves).  The row pass has then
+// written the leaf as if they were values of their own; the repair draws the
+// missing values (Algorithm H takes the stream's next ones that are new),
+// and a second row pass writes every position that moves.
+//
+// What bounds it: see k_leaf_sort.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kSortBucketBits = 13;
+constexpr uint32_t kSortCnt = (1u << kSortBucketBits) / 8;  // counter words
+constexpr uint32_t kSortPre = 8;                            // words before position 0
+constexpr uint32_t kSortKeys = kSortPre + kMaxN0 + 152;     // then keys, sentinels
+constexpr uint32_t kSortSpare = kMaxN0 + 15 + 128;          // key slot that nothing reads
+constexpr uint32_t kSortCacheLeaves = 16;
+constexpr uint32_t kSortCache = kSortCacheLeaves * kLeafWords;
+constexpr uint32_t kMaxFix = 32;                            // repeats repaired in place
+constexpr uint32_t kCand = 8;                               // candidates per repair step
+// scratch words: [0, 16) scan; 16 class bits; 17 repeats; 18 next word;
+// 19 candidates that are no new values; 20 jobs to run; 21 some value
+// repeats; [32, 64) repeats' positions;
+// [64, 96) new values; [96, 104) candidates
+constexpr uint32_t kSsClass = 16, kSsDups = 17, kSsNext = 18, kSsDead = 19, kSsKeep = 20, kSsAny = 21,
+                   kSsDupPos = 32, kSsNew = 64, kSsCand = 96, kSsWords = 112;
+constexpr uint32_t kOnes4 = 0x11111111u, kFours4 = 0x44444444u;
+constexpr uint32_t kSmemSort = kSortKeys + 2 * kSortCnt + kSortCache + kSsWords;
+
+struct SortSmem {
+  uint32_t* keys;  // position 0 (kSortPre words before it)
+  uint32_t* cnt;   // kSortCnt counter words, zero between leaves, then as many prefixes
+  uint32_t* scr;   // kSsWords
+};
+
+__device__ __forceinline__ SortSmem sort_smem(uint32_t* smem) {
+  SortSmem sm;
+  sm.cnt = smem;  // first: counter and prefix are one two-offset LDS read
+  sm.keys = smem + 2 * kSortCnt + kSortPre;
+  sm.scr = smem + 2 * kSortCnt + kSortKeys + kSortCache;
+  return sm;
+}
+__device__ __forceinline__ uint32_t* sort_cache(uint32_t* smem) {
+  return smem + 2 * kSortCnt + kSortKeys;
 }
 
-// With-replacement leaf: the first n_v non-void draws, sorted, repeats kept.
-template <int B>
-__device__ void leaf_wr(const Leaf& L, uint64_t* out, LeafSmem& sm) {
-  const uint32_t nv = L.nv;
-  if (nv == 0) return;
-  const RangeInfo ri = range_info(L.Nv);
-  uint32_t shift, nb;
-  bucket_params(L.Nv, nv, &shift, &nb);
-  const Stream st = make_stream(L.seed, L.id, kWrLeaf, 0);
-  uint32_t key[kKeys / B];
-  uint32_t live;
-  const uint32_t got = first_round_regs<B>(st, nv, ri, key, &live, sm);
-  __builtin_amdgcn_s_setprio(2);  // the sort ahead of other work-groups
-  if (got >= nv) {
-    sort_registers<B, false, true>(key, nv, shift, nb, sm, live);
-  } else {
-    uint32_t* keys = sm.keys;
-    take_values<B>(st, 0, nv, ri, sm.scr, [&](uint32_t p, uint32_t v) { keys[p] = v; });
-    load_registers<B>(key, keys, nv);
-    __syncthreads();
-    sort_registers<B>(key, nv, shift, nb, sm);
+// The map from words to values and the void test of a range in [1, 2^32].
+struct WordMap {
+  uint32_t s;       // range (2^32 as 0)
+  uint32_t thr;     // 2^32 mod range: words with low half of w s below it are void
+  uint32_t pshift;  // power-of-two range above 1: value = w >> pshift
+  bool pow2;
+};
+
+__device__ __forceinline__ WordMap word_map(uint64_t range) {
+  WordMap m;
+  m.s = static_cast<uint32_t>(range);
+  m.pow2 = (range & (range - 1)) == 0 && range > 1;
+  m.pshift = 33u - bit_length(range);
+  m.thr = m.pow2 ? 0u : (0u - m.s) % m.s;  // 2^32 mod range
+  return m;
+}
+
+template <bool kPow2>
+__device__ __forceinline__ uint32_t word_value(const WordMap& m, uint32_t w) {
+  return kPow2 ? w >> m.pshift : __umulhi(w, m.s);
+}
+__device__ __forceinline__ uint32_t word_value(const WordMap& m, uint32_t w) {
+  return m.pow2 ? word_value<true>(m, w) : word_value<false>(m, w);
+}
+
+// The shift of a key's bucket in its counter word.
+constexpr uint32_t kSortWordShift = 32 - (kSortBucketBits - 3);
+__device__ __forceinline__ uint32_t sort_shift(uint32_t w) {
+  return (w >> (kSortWordShift - 5)) & 28u;
+}
+
+// Neighbouring lanes' values: lane i - 1's (0 in lane 0), lane i + 1's
+// (2^32 - 1 in lane 63).
+__device__ __forceinline__ uint32_t lane_before(uint32_t x) {
+  return __builtin_amdgcn_update_dpp(0u, x, 0x138, 0xf, 0xf, false);  // wave_shr:1
+}
+__device__ __forceinline__ uint32_t lane_after(uint32_t x) {
+  return __builtin_amdgcn_update_dpp(~0u, x, 0x130, 0xf, 0xf, false);  // wave_shl:1
+}
+
+// 128 consecutive positions, lane l holding positions 2l and 2l + 1 of them,
+// after R rounds of odd-even transposition.
+template <int R>
+__device__ __forceinline__ void row_sort(uint32_t& a, uint32_t& b) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if ((r & 1) == 0) {
+      const uint32_t lo = min(a, b), hi = max(a, b);
+      a = lo;
+      b = hi;
+    } else {
+      const uint32_t pb = lane_before(b), na = lane_after(a);
+      a = max(pb, a);
+      b = min(na, b);
+    }
   }
-  __builtin_amdgcn_s_setprio(0);
-  write_sorted_pairs<B>(out + L.off, L.lo, sm.keys, nv);
+}
+
+// A row: 128 positions of which the inner kRow, 7 lines of 128 bytes of the
+// output, are final; the outer kHalo lanes on each side hold the neighbouring
+// keys that a bucket at the row's edge may reach into (buckets of at most
+// 2 kHalo keys).
+constexpr uint32_t kHalo = 4;
+constexpr uint32_t kRow = 2 * (64 - 2 * kHalo);
+
+// Row r's words after R transposition rounds (R at least the largest bucket).
+template <int R>
+__device__ __forceinline__ void row_words(const SortSmem& sm, uint32_t r0, uint32_t lane,
+                                          uint32_t& a, uint32_t& b) {
+  const uint2 k = *reinterpret_cast<const uint2*>(sm.keys + static_cast<int>(r0 + 2 * lane - 2 * kHalo));
+  a = k.x;
+  b = k.y;
+  row_sort<R>(a, b);
+}
+
+// Writes the sorted leaf: position p (in [s0, nn), nn = s0 + n_v) goes to
+// o[p], o at a line boundary.  Returns, in every lane, whether the wave saw
+// equal values at neighbouring positions.  (Taking two to four rows at a time
+// to overlap their latencies measured slower: the rows past a leaf's end are
+// work too.)
+template <int B, int R, bool kPow2>
+__device__ __forceinline__ bool write_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
+                                           const WordMap& m, const SortSmem& sm) {
+  const uint32_t tid = lane_tid();
+  const uint32_t lane = tid & 63u;
+  const bool inner = lane - kHalo < 64u - 2 * kHalo;
+  uint64_t dup = 0;
+  for (uint32_t r0 = kRow * __builtin_amdgcn_readfirstlane(tid >> 6); r0 < nn;
+       r0 += kRow * (B / 64)) {
+    uint32_t a, b;
+    row_words<R>(sm, r0, lane, a, b);
+    a = word_value<kPow2>(m, a);
+    b = word_value<kPow2>(m, b);
+    const uint32_t na = lane_after(a);
+    const uint32_t p = r0 + 2 * lane - 2 * kHalo;  // wraps below 0 in the first row's outer lanes
+    u64x2 pr;
+    pr.x = b1 + a;
+    pr.y = b1 + b;
+    if (r0 >= s0 && r0 + kRow < nn) {  // every inner position and the next one hold keys
+      dup |= __builtin_amdgcn_ballot_w64(inner && (a == b || b == na));
+      if (inner)
+        __builtin_nontemporal_store(
+            pr, reinterpret_cast<u64x2*>(reinterpret_cast<char*>(o) + 8u * p));
+    } else {
+      dup |= __builtin_amdgcn_ballot_w64(inner && ((a == b && p >= s0 && p + 1 < nn) ||
+                                                   (b == na && p + 1 >= s0 && p + 2 < nn)));
+      if (inner && p >= s0 && p < nn) store_out(o + p, pr.x);
+      if (inner && p + 1 >= s0 && p + 1 < nn) store_out(o + p + 1, pr.y);
+    }
+  }
+  return dup != 0;
+}
+
+template <int B, bool kPow2>
+__device__ __forceinline__ bool write_rows_of(uint32_t cls, uint64_t* o, uint64_t b1, uint32_t s0,
+                                              uint32_t nn, const WordMap& m, const SortSmem& sm) {
+  if (cls == 0) return write_rows<B, 4, kPow2>(o, b1, s0, nn, m, sm);
+  if (cls == 1) return write_rows<B, 6, kPow2>(o, b1, s0, nn, m, sm);
+  return write_rows<B, 8, kPow2>(o, b1, s0, nn, m, sm);
+}
+
+// The repeats of a leaf: every position whose value equals the one before it
+// is appended to the scratch (the first kMaxFix of them) and counted.
+template <int B>
+__device__ void find_repeats(uint32_t s0, uint32_t nn, const WordMap& m, const SortSmem& sm) {
+  const uint32_t tid = lane_tid();
+  const uint32_t lane = tid & 63u;
+  const bool inner = lane - kHalo < 64u - 2 * kHalo;
+  for (uint32_t r0 = kRow * __builtin_amdgcn_readfirstlane(tid >> 6); r0 < nn;
+       r0 += kRow * (B / 64)) {
+    uint32_t a, b;
+    row_words<2 * kHalo>(sm, r0, lane, a, b);
+    a = word_value(m, a);
+    b = word_value(m, b);
+    const uint32_t na = lane_after(a);
+    const uint32_t p = r0 + 2 * lane - 2 * kHalo;
+    if (inner && a == b && p >= s0 && p + 1 < nn) {
+      const uint32_t i = atomicAdd(&sm.scr[kSsDups], 1u);
+      if (i < kMaxFix) sm.scr[kSsDupPos + i] = p + 1;
+    }
+    if (inner && b == na && p + 1 >= s0 && p + 2 < nn) {
+      const uint32_t i = atomicAdd(&sm.scr[kSsDups], 1u);
+      if (i < kMaxFix) sm.scr[kSsDupPos + i] = p + 2;
+    }
+  }
+}
+
+// The row pass after a repair: D removed positions (the repeats) and D new
+// values, ascending.  Position p keeps its value v at p - (removed below p) +
+// (new values below v); a new value belongs right after the last position
+// whose value is smaller.
+template <int B>
+__device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn, const WordMap& m,
+                             const SortSmem& sm, uint32_t D) {
+  const uint32_t tid = lane_tid();
+  const uint32_t lane = tid & 63u;
+  const bool inner = lane - kHalo < 64u - 2 * kHalo;
+  for (uint32_t r0 = kRow * __builtin_amdgcn_readfirstlane(tid >> 6); r0 < nn;
+       r0 += kRow * (B / 64)) {
+    uint32_t v[3];
+    row_words<2 * kHalo>(sm, r0, lane, v[0], v[1]);
+    v[0] = word_value(m, v[0]);
+    v[1] = word_value(m, v[1]);
+    v[2] = lane_after(v[0]);
+    const uint32_t p = r0 + 2 * lane - 2 * kHalo;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t q = p + h;
+      if (inner && q >= s0 && q < nn) {
+        uint32_t gone = 0, below = 0;
+        bool removed = false;
+        for (uint32_t i = 0; i < D; ++i) {
+          const uint32_t dp = sm.scr[kSsDupPos + i];
+          gone += dp < q ? 1u : 0u;
+          removed = removed || dp == q;
+          below += sm.scr[kSsNew + i] < v[h] ? 1u : 0u;
+        }
+        if (!removed && gone != below) store_out(o + (q - gone + below), b1 + v[h]);
+        // positions up to q that stay, then the new values in the gap above q
+        const uint32_t stay = q + 1 - gone - (removed ? 1u : 0u);
+        const bool last = q + 1 == nn;
+        for (uint32_t i = 0; i < D; ++i) {
+          const uint32_t x = sm.scr[kSsNew + i];
+          if (x > v[h] && (last || x < v[h + 1]))
+            store_out(o + (stay + i), b1 + x);
+          else if (q == s0 && x < v[h])
+            store_out(o + (s0 + i), b1 + x);
+        }
+      }
+    }
+  }
+}
+
+// dst[0 .. need) = the first `need` non-void words of the stream from word t
+// on; returns the word index just after the last one (ends with a barrier).
+// dst may not overlap scr.
+template <int B>
+__device__ uint32_t draw_words(const Stream& st, uint32_t t, uint32_t need, const WordMap& m,
+                               uint32_t* dst, uint32_t* scr) {
+  constexpr int kBlk = kKeys / (4 * B);
+  // words per non-void word
+  const float over = 4294967296.0f / (4294967296.0f - static_cast<float>(m.thr));
+  uint32_t done = 0;
+  while (done < need) {
+    const float want = static_cast<float>(need - done);
+    // expected words, and four standard deviations of their non-void count
+    const uint32_t extra =
+        m.thr == 0 ? 0u
+                   : static_cast<uint32_t>(want * (over - 1.0f) +
+                                           4.0f * over * __builtin_sqrtf(want * (over - 1.0f))) + 4u;
+    const uint32_t first = t >> 2;
+    const uint32_t blocks = min(((t + (need - done) + extra + 3u) >> 2) - first, kBlk * static_cast<uint32_t>(B));
+    const uint32_t per = (blocks + B - 1) / B;
+    const uint32_t tid = lane_tid();
+    uint32_t w[4 * kBlk];
+    uint32_t ok = 0;
+#pragma unroll
+    for (int k = 0; k < kBlk; ++k) {
+      const uint32_t blk = first + per * tid + k;
+      if (static_cast<uint32_t>(k) < per && blk < first + blocks) {
+        const uint4 x = philox_block(st, blk);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          w[4 * k + j] = pick(x, j);
+          if (w[4 * k + j] * m.s >= m.thr && 4 * blk + j >= t) ok |= 1u << (4 * k + j);
+        }
+      }
+    }
+    uint32_t total;
+    uint32_t p = done + block_scan_excl<B, uint32_t>(static_cast<uint32_t>(__popc(ok)), scr, &total);
+#pragma unroll
+    for (int q = 0; q < 4 * kBlk; ++q) {
+      if ((ok >> q) & 1u) {
+        if (p < need) dst[p] = w[q];
+        if (p == need - 1) scr[kSsNext] = 4 * (first + per * tid) + q + 1;
+        ++p;
+      }
+    }
+    done += total;
+    t = 4 * (first + blocks);
+    __syncthreads();
+  }
+  const uint32_t next = scr[kSsNext];
+  __syncthreads();
+  return next;
+}
+
+// Sparse and with-replacement leaves in full generality: keys[0..n) hold the
+// leaf's first n words (any order), word t is the stream's next; sorted by a
+// bitonic network over 4096 keys (the unused ones 2^32 - 1, which sort last),
+// repeats dropped and drawn again until there is none.  For leaves with a
+// bucket of more than 8 keys or more than kMaxFix repeats.
+template <int B>
+__device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint32_t n,
+                                                       const WordMap& m, bool wr, SortSmem& sm,
+                                                       uint64_t* out, uint64_t b1) {
+  uint32_t* keys = sm.keys;
+  constexpr int R = kKeys / B;
+  for (;;) {
+    const uint32_t tid = lane_tid();
+    for (uint32_t i = n + tid; i < kKeys; i += B) keys[i] = 0xFFFFFFFFu;
+    __syncthreads();
+    for (uint32_t k = 2; k <= kKeys; k <<= 1) {
+      for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+        for (uint32_t q = tid; q < kKeys / 2; q += B) {
+          const uint32_t lo = ((q & ~(j - 1)) << 1) | (q & (j - 1)), hi = lo | j;
+          const uint32_t x = keys[lo], y = keys[hi];
+          if ((x > y) == ((lo & k) == 0)) {
+            keys[lo] = y;
+            keys[hi] = x;
+          }
+        }
+        __syncthreads();
+      }
+    }
+    if (wr) break;
+    uint32_t w[R], keep = 0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const uint32_t i = R * tid + q;
+      w[q] = keys[i];
+      if (i < n && (i == 0 || word_value(m, keys[i - 1]) != word_value(m, w[q]))) keep |= 1u << q;
+    }
+    uint32_t have;
+    uint32_t p = block_scan_excl<B, uint32_t>(static_cast<uint32_t>(__popc(keep)), sm.scr, &have);
+    if (have == n) break;
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if ((keep >> q) & 1u) keys[p++] = w[q];
+    t = draw_words<B>(st, t, n - have, m, keys + have, sm.scr);
+  }
+  for (uint32_t i = lane_tid(); i < n; i += B) store_out(out + i, b1 + word_value(m, keys[i]));
+  __syncthreads();
+}
+
+// D <= kMaxFix repeats found by the row pass: the stream's next D new values
+// from word t on, ascending, into the scratch.  keys[s0 .. nn) hold the
+// leaf's words.  Ends with a barrier.
+template <int B>
+__device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t s0, uint32_t nn,
+                             const WordMap& m, SortSmem& sm) {
+  uint32_t* scr = sm.scr;
+  const uint32_t tid = lane_tid();
+  uint32_t have = 0;
+  while (have < D) {
+    if (tid < 64) {
+      uint32_t v = 0;
+      bool good = false;  // not void
+      if (tid < kCand) {
+        const uint32_t w = pick(philox_block(st, (t + tid) >> 2), (t + tid) & 3u);
+        v = word_value(m, w);
+        good = w * m.s >= m.thr;
+      }
+      const unsigned long long gm = __ballot(good);
+      bool dead = !good;
+      for (uint32_t i = 0; i < have; ++i) dead = dead || scr[kSsNew + i] == v;
+#pragma unroll
+      for (uint32_t c = 0; c < kCand; ++c)  // an earlier candidate of this step
+        dead = dead || (c < tid && ((gm >> c) & 1u) != 0 &&
+                        static_cast<uint32_t>(__builtin_amdgcn_readlane(v, c)) == v);
+      const unsigned long long dm = __ballot(dead);
+      if (tid < kCand) scr[kSsCand + tid] = v;
+      if (tid == 0) scr[kSsDead] = static_cast<uint32_t>(dm) & ((1u << kCand) - 1u);
+    }
+    __syncthreads();
+    uint32_t c[kCand], hit = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < kCand; ++i) c[i] = scr[kSsCand + i];
+    for (uint32_t i = s0 + tid; i < nn; i += B) {
+      const uint32_t v = word_value(m, sm.keys[i]);
+#pragma unroll
+      for (uint32_t j = 0; j < kCand; ++j) hit |= c[j] == v ? 1u << j : 0u;
+    }
+    if (hit != 0) atomicOr(&scr[kSsDead], hit);
+    __syncthreads();
+    const uint32_t fresh = ~scr[kSsDead] & ((1u << kCand) - 1u);
+    if (tid < kCand && ((fresh >> tid) & 1u)) {
+      const uint32_t i = have + static_cast<uint32_t>(__popc(fresh & ((1u << tid) - 1u)));
+      if (i < D) scr[kSsNew + i] = scr[kSsCand + tid];
+    }
+    have += static_cast<uint32_t>(__popc(fresh));
+    t += kCand;
+    __syncthreads();
+  }
+  uint32_t x = 0, rank = 0;
+  if (tid < D) {
+    x = scr[kSsNew + tid];
+    for (uint32_t i = 0; i < D; ++i) rank += scr[kSsNew + i] < x ? 1u : 0u;
+  }
+  __syncthreads();
+  if (tid < D) scr[kSsNew + rank] = x;
+  __syncthreads();
+}
+
+// What a key keeps from the counting pass to the scatter (recomputing it
+// there costs more issue slots than the registers do: the kernel is bound by
+// VALU issue and its LDS holds it at four waves per SIMD).
+struct KeyPlace {
+  uint32_t word;   // byte offset of its counter word
+  uint32_t shift;  // of its bucket's four bits
+  uint32_t slot;   // the bucket's count before it
+};
+
+__device__ __forceinline__ uint32_t* sort_word(const SortSmem& sm, const KeyPlace& k) {
+  return reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sm.cnt) + k.word);
+}
+
+// Four keys of a thread, positions i .. i + 3 of the leaf's words, counted
+// into their buckets; returns the largest slot.  kPart: positions from nv on
+// take no part.
+template <bool kPart>
+__device__ __forceinline__ uint32_t count_keys(const uint32_t* key, KeyPlace* at, uint32_t i,
+                                               uint32_t nv, const SortSmem& sm) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    at[j].word = (key[j] >> (kSortWordShift - 2)) & (4 * kSortCnt - 4);
+    at[j].shift = sort_shift(key[j]);
+    asm volatile("" : "+v"(at[j].word), "+v"(at[j].shift));  // kept, not recomputed
+    uint32_t one = 1u << at[j].shift;
+    if (kPart && i + j >= nv) one = 0;
+    at[j].slot = atomicAdd(sort_word(sm, at[j]), one);
+  }
+  uint32_t top = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    at[j].slot = __builtin_amdgcn_ubfe(at[j].slot, at[j].shift, 4);
+    if (kPart && i + j >= nv) at[j].slot = 0;
+    top = max(top, at[j].slot);
+  }
+  return top;
+}
+
+// The same keys to their places: the prefix of the counter word, the counts
+// of the word's lower buckets and the slot, all in bytes.
+template <bool kPart>
+__device__ __forceinline__ void scatter_keys(const uint32_t* key, const KeyPlace* at, uint32_t i,
+                                             uint32_t nv, const SortSmem& sm) {
+  uint32_t c[4], e[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    c[j] = sort_word(sm, at[j])[0];
+    e[j] = sort_word(sm, at[j])[kSortCnt];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t below = __builtin_amdgcn_ubfe(c[j], 0, at[j].shift);
+    uint32_t bytes = e[j] + 4 * __builtin_amdgcn_udot8(below, kOnes4, at[j].slot, false);
+    if (kPart && i + j >= nv) bytes = 4 * kSortSpare;
+    *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sm.keys) + bytes) = key[j];
+  }
+}
+
+// The record of a job, from LDS, in scalar registers.
+__device__ __forceinline__ Leaf cached_leaf(const uint32_t* rec) {
+  const uint4* c = reinterpret_cast<const uint4*>(rec);
+  const uint4 a = c[0], b = c[1], d = c[2];
+  Leaf L;
+  L.id = uniform64(static_cast<uint64_t>(a.x) | (static_cast<uint64_t>(a.y) << 32));
+  L.lo = uniform64(static_cast<uint64_t>(a.z) | (static_cast<uint64_t>(a.w) << 32));
+  L.Nv = uniform64(static_cast<uint64_t>(b.x) | (static_cast<uint64_t>(b.y) << 32));
+  L.off = uniform64(static_cast<uint64_t>(b.z) | (static_cast<uint64_t>(b.w) << 32));
+  L.seed = uniform64(static_cast<uint64_t>(d.x) | (static_cast<uint64_t>(d.y) << 32));
+  L.nv = __builtin_amdgcn_readfirstlane(d.z);
+  L.flags = __builtin_amdgcn_readfirstlane(d.w);
+  return L;
+}
+
+// What a leaf kernel's choice of jobs looks at.
+__device__ __forceinline__ Leaf cached_kind(const uint32_t* rec) {
+  Leaf c;
+  c.Nv = static_cast<uint64_t>(rec[4]) | (static_cast<uint64_t>(rec[5]) << 32);
+  c.nv = rec[10];
+  c.flags = rec[11];
+  return c;
 }
 
 // ---------------------------------------------------------------------------
@@ -1151,7 +1457,7 @@ __device__ __forceinline__ void put_chunk(uint16_t* dst, const uint32_t q[4]) {
 // are recomputed from their start position when they are written out), the
 // repair's removed hit indices as a bit mask, and the kept hits written with
 // consecutive lanes on consecutive outputs.
-__device__ void leaf_dense_wave(const Leaf& L, uint64_t* out, uint16_t* list, uint32_t* mask,
+__device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, uint16_t* list, uint32_t* mask,
                                 uint32_t* bases) {
   const uint32_t lane = lane_tid();
   const uint32_t nv = L.nv;
@@ -1284,7 +1590,7 @@ __device__ void leaf_dense_wave(const Leaf& L, uint64_t* out, uint16_t* list, ui
 // ---------------------------------------------------------------------------
 // Sparse and with-replacement leaves of the back list (ranges that are not
 // powers of two) with at most kSmallMax values are taken by k_leaf_small,
-// one wave each with no barrier: the same values as leaf_sparse / leaf_wr
+// one wave each with no barrier: the same values as leaf_sorted
 // (the first n_v non-void values of the leaf's stream, for a sparse leaf
 // Algorithm H's distinct ones by rounds), ranked in stream order by wave
 // scans, sorted by a counting pass over kSmallBuckets buckets and the
@@ -1506,7 +1812,7 @@ __device__ void leaf_small_wave(const Leaf& L, uint64_t* out, uint32_t* keys, ui
 }
 
 template <int B>
-__device__ void leaf_fill(const Leaf& L, uint64_t* out) {
+__device__ __forceinline__ void leaf_fill(const Leaf& L, uint64_t* out) {
   uint64_t* o = out + L.off;
   for (uint32_t i = threadIdx.x; i < L.nv; i += B) store_out(o + i, L.lo + 1);
 }
@@ -1518,24 +1824,329 @@ __device__ __forceinline__ uint64_t job_counts(const Control* ctl, int round) {
   return g != ~0ull ? g : (round ? ctl->leaf_counts2 : ctl->leaf_counts);
 }
 
-// Persistent leaf loop: job i of the class's list goes to work-group
-// i mod G, whose job records are read kCacheLeaves at a time into LDS.
-// kListFront: the front list (sparse and with-replacement leaves over
-// power-of-two ranges, except sparse ones expected to repeat) with only that
-// leaf body compiled in, so that the hot path keeps its values in registers.
-// kListBack: the back list with every other leaf body, leaving to the
-// one-wave kernels and to k_leaf_once the jobs they take, except the kinds in
-// `takes` (kTakesDense / kTakesSmall / kTakesOnce: that kernel is not
-// launched); round2: the second round's jobs (back list only, every kind
-// but those of k_leaf_once, which it takes too when kTakesOnce is set).
-// kListOnce: the back list's jobs of once_by_group, both rounds.
-constexpr int kListFront = 0, kListBack = 1, kListOnce = 2;
+// A leaf's range, stream and output, as its record gives them.
+struct SortLeaf {
+  WordMap m;
+  Stream st;
+  uint64_t* o;     // where position 0 goes, at a line boundary
+  uint64_t b1;
+  uint32_t nv, s0, nn;
+  bool wr;
+};
+__device__ __forceinline__ SortLeaf sort_leaf(const Leaf& L, uint64_t* out) {
+  SortLeaf v;
+  v.nv = L.nv;
+  v.wr = (L.flags & 3u) == kKindWr;
+  v.m = word_map(L.Nv);
+  v.st = make_stream(L.seed, L.id, v.wr ? kWrLeaf : kLeaf, 0);
+  v.s0 = static_cast<uint32_t>((reinterpret_cast<uintptr_t>(out + L.off) >> 3) & 15u);
+  v.nn = v.s0 + L.nv;
+  v.o = out + L.off - v.s0;
+  v.b1 = L.lo + 1;
+  return v;
+}
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+__device__ __forceinline__ lds_u32* lds_address(const uint32_t* p) {
+  return (lds_u32*)const_cast<uint32_t*>(p);
+}
+// An LDS address that every lane holds, in a scalar register.
+__device__ __forceinline__ uint32_t* lds_uniform(lds_u32* p) {
+  return (uint32_t*)(lds_u32*)static_cast<uintptr_t>(__builtin_amdgcn_readfirstlane(
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p))));
+}
+
+// What a leaf rarely needs, out of line so that the common path keeps its
+// registers: lds is the address of the work-group's LDS, rec the job's record
+// in it, t the stream's next word.  kRareRepeats: the row pass found
+// repeats; kRareGeneral: a bucket of more than 8 keys (the leaf's words lie
+// in stream order from position 0); otherwise a constant or dense leaf.
+constexpr uint32_t kRareRepeats = 0, kRareGeneral = 1, kRareOther = 2;
+template <int B>
+__device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* out_any,
+                                                    uint32_t t_any, uint32_t what_any) {
+  uint32_t* const smem = lds_uniform(lds);
+  const Leaf L = cached_leaf(lds_uniform(rec));
+  uint64_t* const out =
+      reinterpret_cast<uint64_t*>(uniform64(reinterpret_cast<uint64_t>(out_any)));
+  const uint32_t t = __builtin_amdgcn_readfirstlane(t_any);
+  const uint32_t what = __builtin_amdgcn_readfirstlane(what_any);
+  SortSmem sm = sort_smem(smem);
+  if (what == kRareOther) {
+    // k_leaf_dense's arrays, over the keys
+    uint16_t* const list = reinterpret_cast<uint16_t*>(sm.keys);
+    uint32_t* const mask = sm.keys + kWaveList / 2;
+    if ((L.flags & 3u) == kKindFill)
+      leaf_fill<B>(L, out);
+    else if (threadIdx.x < 64)
+      leaf_dense_wave(L, out, list, mask, mask + kWaveMaskWords);
+    __syncthreads();
+    return;
+  }
+  const SortLeaf v = sort_leaf(L, out);
+  if (what == kRareRepeats) {
+    find_repeats<B>(v.s0, v.nn, v.m, sm);
+    __syncthreads();
+    const uint32_t D = __builtin_amdgcn_readfirstlane(sm.scr[kSsDups]);
+    if (D <= kMaxFix) {
+      draw_missing<B>(v.st, t, D, v.s0, v.nn, v.m, sm);
+      rewrite_rows<B>(v.o, v.b1, v.s0, v.nn, v.m, sm, D);
+      __syncthreads();
+      return;
+    }
+    constexpr int R = kKeys / B;
+    uint32_t w[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) w[q] = sm.keys[v.s0 + threadIdx.x + q * B];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (threadIdx.x + q * B < v.nv) sm.keys[threadIdx.x + q * B] = w[q];
+  }
+  leaf_general<B>(v.st, t, v.nv, v.m, v.wr, sm, v.o + v.s0, v.b1);
+}
+
+// One sparse or with-replacement leaf (see above).  The counters are zero on
+// entry and on return; ends with a barrier.
+template <int B>
+__device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec, uint64_t* out) {
+  constexpr int kBlk = kKeys / (4 * B);
+  constexpr int kQ = 4 * kBlk;
+  constexpr int kParts = kSortCnt / (4 * B);  // counter words per thread: 4 kParts
+  static_assert(kParts == 1 || kParts == 2, "two 16-bit sums share one scanned word");
+  const uint32_t tid = lane_tid();
+  SortSmem sm = sort_smem(smem);
+  const SortLeaf v = sort_leaf(cached_leaf(rec), out);
+  const uint32_t nv = v.nv, s0 = v.s0, nn = v.nn;
+  const WordMap& m = v.m;
+  const Stream& st = v.st;
+  uint32_t* const keys = sm.keys;
+  // The leaf's first n_v non-void words, four per Philox block and thread
+  // (the lanes of the leaf's last wave past its end hold words that take no
+  // part).
+  const uint32_t wave_first = __builtin_amdgcn_readfirstlane(tid & ~63u);
+  uint32_t key[kQ];
+  uint32_t t_next = nv;
+  if (m.thr != 0) t_next = draw_words<B>(st, 0, nv, m, keys, sm.scr);
+#pragma unroll
+  for (int k = 0; k < kBlk; ++k) {
+    if (4 * (wave_first + k * B) < nv) {
+      uint4 w;
+      if (m.thr != 0)
+        w = reinterpret_cast<const uint4*>(keys)[tid + k * B];
+      else
+        w = philox_block(st, tid + k * B);
+      key[4 * k + 0] = w.x;
+      key[4 * k + 1] = w.y;
+      key[4 * k + 2] = w.z;
+      key[4 * k + 3] = w.w;
+    }
+  }
+  __builtin_amdgcn_s_setprio(2);
+  // 1. count
+  KeyPlace at[kQ];
+  uint32_t top = 0;  // largest slot
+#pragma unroll
+  for (int k = 0; k < kBlk; ++k) {
+    const uint32_t first = 4 * (wave_first + k * B);
+    if (first + 256 <= nv)
+      top = max(top, count_keys<false>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm));
+    else if (first < nv)
+      top = max(top, count_keys<true>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm));
+  }
+  // the leaf's class: buckets of more than 4, 6 and 8 keys
+  {
+    const bool four = __builtin_amdgcn_ballot_w64(top >= 4) != 0;
+    if (four) {
+      const bool six = __builtin_amdgcn_ballot_w64(top >= 6) != 0;
+      const bool eight = __builtin_amdgcn_ballot_w64(top >= 8) != 0;
+      if ((tid & 63u) == 0) atomicOr(&sm.scr[kSsClass], 1u | (six ? 2u : 0u) | (eight ? 4u : 0u));
+    }
+  }
+  __syncthreads();
+  // 2. scan
+  {
+    const uint4* c4 = reinterpret_cast<const uint4*>(sm.cnt);
+    uint4 c[kParts];
+    uint32_t sum[kParts];
+#pragma unroll
+    for (int h = 0; h < kParts; ++h) {
+      c[h] = c4[tid + h * B];
+      sum[h] = __builtin_amdgcn_udot8(c[h].x, kOnes4, 0u, false);
+      sum[h] = __builtin_amdgcn_udot8(c[h].y, kOnes4, sum[h], false);
+      sum[h] = __builtin_amdgcn_udot8(c[h].z, kOnes4, sum[h], false);
+      sum[h] = __builtin_amdgcn_udot8(c[h].w, kOnes4, sum[h], false);
+    }
+    const uint32_t packed = kParts == 2 ? sum[0] | (sum[kParts - 1] << 16) : sum[0];
+    uint32_t total;
+    const uint32_t excl = block_scan_excl<B, uint32_t, false>(packed, sm.scr, &total);
+#pragma unroll
+    for (int h = 0; h < kParts; ++h) {
+      const uint32_t e0 =
+          4 * s0 +
+          4 * (kParts == 1 ? excl : h == 0 ? (excl & 0xFFFFu) : (total & 0xFFFFu) + (excl >> 16));
+      // prefixes in bytes: a nibble times 4
+      const uint32_t e1 = __builtin_amdgcn_udot8(c[h].x, kFours4, e0, false);
+      const uint32_t e2 = __builtin_amdgcn_udot8(c[h].y, kFours4, e1, false);
+      const uint32_t e3 = __builtin_amdgcn_udot8(c[h].z, kFours4, e2, false);
+      reinterpret_cast<uint4*>(sm.cnt + kSortCnt)[tid + h * B] = make_uint4(e0, e1, e2, e3);
+    }
+  }
+  const uint32_t cls = __builtin_amdgcn_readfirstlane(sm.scr[kSsClass]);
+  __syncthreads();
+  // 3. scatter, sentinels around the keys
+  if (tid < 128) keys[nn + tid] = 0xFFFFFFFFu;
+  if (tid < s0) keys[tid] = 0;
+  if (tid == 0) {
+    sm.scr[kSsDups] = 0;
+    sm.scr[kSsAny] = 0;
+  }
+  if (cls < 4) {
+#pragma unroll
+    for (int k = 0; k < kBlk; ++k) {
+      const uint32_t first = 4 * (wave_first + k * B);
+      if (first + 256 <= nv)
+        scatter_keys<false>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm);
+      else if (first < nv)
+        scatter_keys<true>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm);
+    }
+  } else {
+    // a bucket of more than 8 keys: the words in stream order
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const uint32_t i = 4 * (tid + (q >> 2) * B) + (q & 3);
+      if (i < nv) keys[i] = key[q];
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+  __syncthreads();
+  // 4. rows; the counters are zeroed for the next leaf (from a register set
+  // here: four kept zeros would be spilled and reloaded behind the stores)
+  uint32_t zero = 0;
+  asm volatile("" : "+v"(zero));
+#pragma unroll
+  for (int h = 0; h < kParts; ++h)
+    reinterpret_cast<uint4*>(sm.cnt)[tid + h * B] = make_uint4(zero, zero, zero, zero);
+  if (tid == 0) sm.scr[kSsClass] = 0;
+  uint32_t what = kRareGeneral;
+  if (cls < 4) {
+    const bool rep = m.pow2 ? write_rows_of<B, true>(cls, v.o, v.b1, s0, nn, m, sm)
+                            : write_rows_of<B, false>(cls, v.o, v.b1, s0, nn, m, sm);
+    if (rep && !v.wr) sm.scr[kSsAny] = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(sm.scr[kSsAny]) == 0) return;
+    what = kRareRepeats;
+  }
+  leaf_rare<B>(lds_address(smem), lds_address(rec), out, t_next, what);
+}
+
+// Persistent work-groups: job i of the front and then the back list goes to
+// work-group i mod G, whose job records are read kSortCacheLeaves at a time
+// into LDS.  Every sparse, with-replacement and constant leaf, except those
+// of the back list that k_leaf_small and k_leaf_once take, and the dense
+// leaves that k_leaf_dense takes when that kernel is not launched (`takes`:
+// kTakesDense / kTakesSmall / kTakesOnce: this kernel runs them too).
+// round2: the second round's jobs, all of them but k_leaf_mixed's.
+// What bounds it: the energy and issue slots of its vector instructions.  On
+// n = 2^30 of 2^48 the vector units issue about three quarters of the time at
+// a clock that falls from 2.17 to 2.0 GHz as they are used better (the same
+// cycles take 532 or 585 us with equal counters), the LDS is in use half of
+// it, and without its stores it takes 0.2 ms less.  2.1 ms, 4.1 TB/s written;
+// the counting sort of values over 4096 counters with sorting-network
+// windows that this replaced took 2.88 ms (3.0 TB/s).  Ranges that are no
+// power of two: n = 2^28 of 286538054670896 1.05 ms per call against 2.26 ms.
+// Measured choices (that call, the headline call): 2^13 buckets 1.05 / 2.28
+// ms, 2^14 (fewer leaves in flight, fewer rounds) 1.19 / 2.34 ms; six waves
+// per SIMD with some spills 1.05 / 2.28, five 1.09 / 2.42, four without
+// spills 1.17 / 2.28 ms; 512 threads per leaf 1.62 / 3.06, 128 threads 1.12 /
+// 2.32 ms; a key's place recomputed in the scatter instead of kept 1.05 /
+// 2.48 ms; rows of 256 positions, four to a lane, whose two stores each write
+// half lines, 1.54 / 5.2 ms.
+template <int B>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_sort(
+    const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2,
+    uint32_t takes) {
+  __shared__ __align__(16) uint32_t smem[kSmemSort];
+  SortSmem sm = sort_smem(smem);
+  uint32_t* const cache = sort_cache(smem);
+  static_assert(kSortPre + kWaveList / 2 + kWaveMaskWords + kWaveBases <= kSortKeys,
+                "a dense leaf's arrays fit the keys");
+  const uint64_t counts = uniform64(job_counts(ctl, round2));
+  const uint64_t front = counts & 0xFFFFFFFFull, n_leaves = front + (counts >> 32);
+  if (n_leaves > leaf_cap) {
+    // cannot happen (granted slots sum to at most the capacity): report it
+    // and sample nothing
+    if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(ctl->err, kErrLeafCapacity);
+    return;
+  }
+  if (round2) takes = kTakesDense | kTakesSmall | kTakesOnce;
+  for (uint32_t i = threadIdx.x; i < kSortCnt; i += B) sm.cnt[i] = 0;
+  if (threadIdx.x < kSortPre) smem[2 * kSortCnt + threadIdx.x] = 0;
+  if (threadIdx.x == 0) sm.scr[kSsClass] = 0;
+  static_assert(kSortSpare + kSortPre < kSortKeys, "the spare slot lies behind the sentinels");
+  const uint64_t G = gridDim.x;
+  uint32_t keep = 0;  // bit s: cached job s is run here
+  for (uint64_t j = 0;; ++j) {
+    const uint64_t i = blockIdx.x + j * G;
+    if (i >= n_leaves) break;
+    const uint32_t slot = static_cast<uint32_t>(j % kSortCacheLeaves);
+    if (slot == 0) {
+      // read the next job records (every leaf ends with a barrier, so the
+      // previous ones have been read)
+      const uint32_t tid = threadIdx.x;
+      if (tid < kSortCacheLeaves * 3) {
+        const uint32_t which = tid / 3, part = tid % 3;
+        const uint64_t li = i + static_cast<uint64_t>(which) * G;
+        if (li < n_leaves) {
+          const Leaf* rec = li < front ? leaves + li : leaves + (leaf_cap - 1 - (li - front));
+          reinterpret_cast<uint4*>(cache + which * kLeafWords)[part] =
+              reinterpret_cast<const uint4*>(rec)[part];
+        }
+      }
+      __syncthreads();
+      if (tid < 64) {
+        bool run = false;
+        const uint64_t li = i + static_cast<uint64_t>(tid) * G;
+        if (tid < kSortCacheLeaves && li < n_leaves) {
+          const Leaf c = cached_kind(cache + tid * kLeafWords);
+          const bool back = li >= front;
+          if (c.nv == 0)
+            run = false;
+          else if ((c.flags & 3u) == kKindDense)
+            run = dense_by_wave(c) && (takes & kTakesDense);
+          else
+            run = !(back && ((small_by_wave(c) && !(takes & kTakesSmall)) ||
+                             (once_by_group(c) && !(takes & kTakesOnce))));
+        }
+        const unsigned long long m = __ballot(run);
+        if (tid == 0) sm.scr[kSsKeep] = static_cast<uint32_t>(m);
+      }
+      __syncthreads();
+      keep = __builtin_amdgcn_readfirstlane(sm.scr[kSsKeep]);
+      if (keep == 0) {  // the whole group is other kernels'
+        j += kSortCacheLeaves - 1;
+        continue;
+      }
+    }
+    if (!((keep >> slot) & 1u)) continue;  // another kernel's
+    const uint32_t* const rec = cache + slot * kLeafWords;
+    const uint32_t kind = __builtin_amdgcn_readfirstlane(rec[11]) & 3u;
+    if (kind == kKindSparse || kind == kKindWr)
+      leaf_sorted<B>(smem, rec, out);
+    else
+      leaf_rare<B>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
+  }
+}
+
+// Persistent work-groups over the back list, as above: kListWide: dense
+// leaves over ranges above 2^16 (either round); kListOnce: the jobs of
+// once_by_group.
+constexpr int kListWide = 0, kListOnce = 1;
 
 template <int B, int kList>
 __device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint64_t leaf_cap,
-                                          uint64_t* out, Control* ctl, int round2 = 0,
-                                          uint32_t takes = 0) {
-  constexpr bool kPow2 = kList == kListFront;
+                                          uint64_t* out, Control* ctl, int round2 = 0) {
   __shared__ uint32_t smem[kSmemWords];
   LeafSmem sm;
   sm.keys = smem;
@@ -1546,22 +2157,10 @@ __device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint6
   uint32_t* cache = smem + kRegionA + kRegionB;
   sm.scr = cache + kCacheWords;
   const uint64_t counts = uniform64(job_counts(ctl, round2));
-  const uint64_t front = counts & 0xFFFFFFFFull, back = counts >> 32;
-  if (front + back > leaf_cap) {
-    // cannot happen (granted slots sum to at most the capacity): report it
-    // and sample nothing
-    if (kList == kListBack && blockIdx.x == 0 && threadIdx.x == 0)
-      atomicOr(ctl->err, kErrLeafCapacity);
-    return;
-  }
-  const uint64_t n_leaves = kPow2 ? front : back;
+  const uint64_t front = counts & 0xFFFFFFFFull, n_leaves = counts >> 32;
+  if (front + n_leaves > leaf_cap) return;  // reported by k_leaf_sort
   const uint64_t G = gridDim.x;
-  if (kPow2) {
-    // the power-of-two leaf sorts leave the bucket counters zeroed behind them
-    zero_counters<B>(sm.buck, threadIdx.x);
-    __syncthreads();
-  }
-  uint32_t keep = ~0u;  // bit s: cached job s is run here (not by k_leaf_dense)
+  uint32_t keep = 0;  // bit s: cached job s is run here
   for (uint64_t j = 0;; ++j) {
     const uint64_t i = blockIdx.x + j * G;
     if (i >= n_leaves) break;
@@ -1570,105 +2169,53 @@ __device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint6
       // read the next kCacheLeaves job records of this work-group into LDS;
       // skipped jobs end without a barrier, so wait until every thread has
       // read the previous record
-      if constexpr (!kPow2) __syncthreads();
+      __syncthreads();
       const uint32_t tid = threadIdx.x;
       if (tid < kCacheLeaves * 3) {
         const uint32_t which = tid / 3, part = tid % 3;
         const uint64_t li = i + static_cast<uint64_t>(which) * G;
-        if (li < n_leaves) {
-          const Leaf* rec = kPow2 ? leaves + li : leaves + (leaf_cap - 1 - li);
-          const uint4 v = reinterpret_cast<const uint4*>(rec)[part];
-          reinterpret_cast<uint4*>(cache + which * kLeafWords)[part] = v;
-        }
+        if (li < n_leaves)
+          reinterpret_cast<uint4*>(cache + which * kLeafWords)[part] =
+              reinterpret_cast<const uint4*>(leaves + (leaf_cap - 1 - li))[part];
       }
       __syncthreads();
-      if constexpr (!kPow2) {
-        if (tid < 64) {
-          bool run = false;
-          if (tid < kCacheLeaves && i + static_cast<uint64_t>(tid) * G < n_leaves) {
-            Leaf c;
-            const uint32_t* r = cache + tid * kLeafWords;
-            c.Nv = static_cast<uint64_t>(r[4]) | (static_cast<uint64_t>(r[5]) << 32);
-            c.nv = r[10];
-            c.flags = r[11];
-            if (kList == kListOnce)
-              run = once_by_group(c);
-            else
-              run = (!once_by_group(c) || (takes & kTakesOnce)) &&
-                    (round2 || ((!dense_by_wave(c) || (takes & kTakesDense)) &&
-                                (!small_by_wave(c) || (takes & kTakesSmall))));
-          }
-          const unsigned long long m = __ballot(run);
-          if (tid == 0) sm.scr[kScrKeep] = static_cast<uint32_t>(m);
+      if (tid < 64) {
+        bool run = false;
+        if (tid < kCacheLeaves && i + static_cast<uint64_t>(tid) * G < n_leaves) {
+          const Leaf c = cached_kind(cache + tid * kLeafWords);
+          run = kList == kListOnce ? once_by_group(c)
+                                   : (c.flags & 3u) == kKindDense && !dense_by_wave(c);
         }
-        __syncthreads();
-        keep = __builtin_amdgcn_readfirstlane(sm.scr[kScrKeep]);
-        if (keep == 0) {  // the whole group is other kernels'
-          j += kCacheLeaves - 1;
-          continue;
-        }
+        const unsigned long long m = __ballot(run);
+        if (tid == 0) sm.scr[kScrKeep] = static_cast<uint32_t>(m);
+      }
+      __syncthreads();
+      keep = __builtin_amdgcn_readfirstlane(sm.scr[kScrKeep]);
+      if (keep == 0) {  // the whole group is other kernels'
+        j += kCacheLeaves - 1;
+        continue;
       }
     }
-    if (!kPow2 && !((keep >> slot) & 1u)) continue;  // another kernel's
-    Leaf L;
-    {
-      const uint4* c = reinterpret_cast<const uint4*>(cache + slot * kLeafWords);
-      const uint4 a = c[0], b = c[1], d = c[2];
-      L.id = static_cast<uint64_t>(a.x) | (static_cast<uint64_t>(a.y) << 32);
-      L.lo = static_cast<uint64_t>(a.z) | (static_cast<uint64_t>(a.w) << 32);
-      L.Nv = static_cast<uint64_t>(b.x) | (static_cast<uint64_t>(b.y) << 32);
-      L.off = static_cast<uint64_t>(b.z) | (static_cast<uint64_t>(b.w) << 32);
-      L.seed = static_cast<uint64_t>(d.x) | (static_cast<uint64_t>(d.y) << 32);
-      L.nv = d.z;
-      L.flags = d.w;
-      // every lane read the same record: make that explicit so the job's
-      // parameters live in scalar registers
-      L.id = uniform64(L.id);
-      L.lo = uniform64(L.lo);
-      L.Nv = uniform64(L.Nv);
-      L.off = uniform64(L.off);
-      L.seed = uniform64(L.seed);
-      L.nv = __builtin_amdgcn_readfirstlane(L.nv);
-      L.flags = __builtin_amdgcn_readfirstlane(L.flags);
-    }
-    if constexpr (kPow2) {
-      // No barrier after the leaf: the next leaf's first LDS writes (counting
-      // atomics into zeroed counters) do not touch what this leaf's output
-      // pass still reads, and its sentinels and flag wait for the counting
-      // barrier, which every thread reaches only after its output pass.
-      leaf_sparse_pow2<B>(L, out, sm);
-    } else if constexpr (kList == kListOnce) {
+    if (!((keep >> slot) & 1u)) continue;  // another kernel's
+    const Leaf L = cached_leaf(cache + slot * kLeafWords);
+    if constexpr (kList == kListOnce)
       leaf_once<B>(L, out, sm);
-      __syncthreads();
-    } else {
-      switch (L.flags & 3u) {
-        case kKindSparse: leaf_sparse<B>(L, out, sm); break;
-        case kKindDense: leaf_dense<B>(L, out, sm); break;
-        case kKindWr: leaf_wr<B>(L, out, sm); break;
-        default: leaf_fill<B>(L, out); break;
-      }
-      __syncthreads();
-    }
+    else
+      leaf_dense<B>(L, out, sm);
+    __syncthreads();
   }
 }
 
 template <int B>
-__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_pow2(
-    const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl) {
-  leaf_loop<B, kListFront>(leaves, leaf_cap, out, ctl);
-}
-
-template <int B>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_mixed(
-    const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2,
-    uint32_t takes) {
-  leaf_loop<B, kListBack>(leaves, leaf_cap, out, ctl, round2, takes);
+    const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2) {
+  leaf_loop<B, kListWide>(leaves, leaf_cap, out, ctl, round2);
 }
 
 template <int B>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_once(
-    const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2) {
-  leaf_loop<B, kListOnce>(leaves, leaf_cap, out, ctl, round2);
+    const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl) {
+  leaf_loop<B, kListOnce>(leaves, leaf_cap, out, ctl);
 }
 
 // Dense leaves of the back list, one wave (and work-group) per leaf: back job
@@ -3040,6 +3587,15 @@ int leaf_occupancy() {
   return occ;
 }
 
+int sort_occupancy() {
+  int occ = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &occ, reinterpret_cast<const void*>(k_leaf_sort<kSortBlock>), kSortBlock, 0) != hipSuccess ||
+      occ <= 0)
+    occ = 4;
+  return occ;
+}
+
 int small_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -3116,30 +3672,24 @@ hipError_t launch_tree(const Instance* inst, uint32_t n_inst, uint64_t total_thr
   return hipGetLastError();
 }
 
-hipError_t launch_leaf(int which, const Leaf* leaves, uint64_t leaf_cap, uint64_t* out,
-                       Control* ctl, uint32_t grid, hipStream_t stream, uint32_t takes) {
-  if (which == kLeafFront)
-    hipLaunchKernelGGL(k_leaf_pow2<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
-                       leaf_cap, out, ctl);
-  else if (which == kLeafBack)
-    hipLaunchKernelGGL(k_leaf_mixed<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
-                       leaf_cap, out, ctl, 0, takes);
-  else if (which == kLeafOnce)
-    hipLaunchKernelGGL(k_leaf_once<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
-                       leaf_cap, out, ctl, 0);
-  else
-    return hipErrorInvalidValue;
+hipError_t launch_leaf_sort(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
+                            uint32_t grid, hipStream_t stream, int round2, uint32_t takes) {
+  hipLaunchKernelGGL(k_leaf_sort<kSortBlock>, dim3(grid), dim3(kSortBlock), 0, stream, leaves,
+                     leaf_cap, out, ctl, round2, takes);
   return hipGetLastError();
 }
 
-hipError_t launch_leaf_round2(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                              uint32_t grid, hipStream_t stream, uint32_t takes) {
+hipError_t launch_leaf_mixed(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
+                             uint32_t grid, hipStream_t stream, int round2) {
   hipLaunchKernelGGL(k_leaf_mixed<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
-                     leaf_cap, out, ctl, 1, takes & kTakesOnce);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || (takes & kTakesOnce)) return e;
+                     leaf_cap, out, ctl, round2);
+  return hipGetLastError();
+}
+
+hipError_t launch_leaf_once(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
+                            uint32_t grid, hipStream_t stream) {
   hipLaunchKernelGGL(k_leaf_once<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
-                     leaf_cap, out, ctl, 1);
+                     leaf_cap, out, ctl);
   return hipGetLastError();
 }
 

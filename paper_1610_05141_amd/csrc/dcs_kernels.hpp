@@ -107,7 +107,8 @@ constexpr unsigned kErrLeafTooLarge = 8u;   // a leaf exceeds the kernel's LDS b
 constexpr unsigned kErrRestartLimit = 16u;  // whole-range B: no attempt accepted
 
 constexpr uint64_t kMaxLeafJobs = 1ull << 31;  // keeps the two halves of leaf_counts apart
-constexpr int kLeafBlock = 512;             // threads of a leaf work-group
+constexpr int kLeafBlock = 512;             // threads of a k_leaf_mixed / k_leaf_once work-group
+constexpr int kSortBlock = 256;             // threads of a k_leaf_sort work-group
 constexpr int kBernBlock = 256;             // threads of a Bernoulli work-group
 constexpr uint32_t kMaxN0 = 4096;           // largest n0 (LDS bound of a leaf)
 constexpr uint64_t kFillPiece = 1ull << 16; // constant-fill leaves are cut to this
@@ -133,8 +134,10 @@ hipError_t launch_reset(Control* ctl, const Instance* single, Instance* table, u
 // and its kTicketWords chunk counters.
 hipError_t launch_zero(Control* ctl, unsigned long long* status, uint64_t n,
                        unsigned long long* tickets, unsigned int* err, hipStream_t stream);
-// Resident leaf work-groups per compute unit.
+// Resident work-groups per compute unit of the 512-thread leaf kernels and
+// of k_leaf_sort.
 int leaf_occupancy();
+int sort_occupancy();
 // Resident k_leaf_dense work-groups (one wave each) per compute unit.
 int dense_occupancy();
 // Resident k_leaf_small work-groups (one wave each) per compute unit.
@@ -163,31 +166,31 @@ hipError_t launch_tree(const Instance* inst, uint32_t n_inst, uint64_t total_thr
                        const Node* frontier, Leaf* leaves, uint64_t leaf_cap, Node* stacks,
                        uint32_t stack_depth, Control* ctl, uint32_t* redo, int round,
                        hipStream_t stream);
-// Work-group leaf kernels: kLeafFront = the front list (sparse and
-// with-replacement leaves over power-of-two ranges, except sparse ones
-// expected to repeat); kLeafBack = the back list's jobs that no other kernel
-// takes; kLeafOnce = the back list's sparse leaves of more than 1024 values
-// with n_v^2 >= 2 N_v (one-pass sampler).
-constexpr int kLeafFront = 0, kLeafBack = 1, kLeafOnce = 2;
-// Kinds that k_leaf_mixed runs itself because their own kernel is not
+// Kinds that k_leaf_sort runs itself because their own kernel is not
 // launched (never changes a sample): dense leaves over ranges up to 2^16,
-// sparse and with-replacement leaves of at most 1024 values, the one-pass
-// sparse leaves.
+// sparse and with-replacement leaves of at most 1024 values of the back list,
+// the one-pass sparse leaves.
 constexpr uint32_t kTakesDense = 1, kTakesSmall = 2, kTakesOnce = 4;
-hipError_t launch_leaf(int which, const Leaf* leaves, uint64_t leaf_cap, uint64_t* out,
-                       Control* ctl, uint32_t grid, hipStream_t stream, uint32_t takes = 0);
-// The second round's jobs (all on the back list, every kind run by the
-// work-group kernels of the back list; k_leaf_once's too when `takes` has
-// kTakesOnce, which then is not launched); returns at once when round 0
-// handed over every leaf.
-hipError_t launch_leaf_round2(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                              uint32_t grid, hipStream_t stream, uint32_t takes = 0);
+// Sparse, with-replacement and constant leaves of both lists, one work-group
+// each, except what k_leaf_small, k_leaf_once and k_leaf_dense take.  round2:
+// the second round's jobs (all on the back list, every kind but
+// k_leaf_mixed's); returns at once when round 0 handed over every leaf.
+hipError_t launch_leaf_sort(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
+                            uint32_t grid, hipStream_t stream, int round2, uint32_t takes);
+// Dense leaves of the back list over ranges above 2^16, one work-group each;
+// they exist only where dense_ratio (n0 - 1) exceeds 2^16.
+hipError_t launch_leaf_mixed(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
+                             uint32_t grid, hipStream_t stream, int round2);
+// The back list's sparse leaves of more than 1024 values with n_v^2 >= 2 N_v
+// (one-pass sampler).
+hipError_t launch_leaf_once(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
+                            uint32_t grid, hipStream_t stream);
 // Dense leaves of the back list whose range fits 16-bit positions, one wave
-// per leaf (k_leaf_mixed skips them).
+// per leaf (k_leaf_sort skips them).
 hipError_t launch_leaf_dense(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream);
 // Sparse and with-replacement leaves of the back list with at most 1024
-// values, one wave per leaf (k_leaf_mixed skips them).
+// values, one wave per leaf (k_leaf_sort skips them).
 hipError_t launch_leaf_small(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream);
 // Bernoulli chunk kernels: kBernFp64Group = k_bern (double-precision skips,
