@@ -1322,12 +1322,10 @@ __device__ void leaf_dense(const Leaf& L, uint64_t* out, LeafSmem& sm) {
       for (uint32_t blk0 = 0;; blk0 += B) {
         const uint4 w = philox_block(st, blk0 + tid);
         uint32_t inc[4];
+        geom_skips32(w, cg, inc);
         uint32_t sum = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          inc[j] = static_cast<uint32_t>(geom_skip32(pick(w, j), cg)) + 1u;
-          sum += inc[j];
-        }
+        for (int j = 0; j < 4; ++j) sum += ++inc[j];
         uint32_t total;
         const uint32_t q0 = last + block_scan_excl<B, uint32_t>(sum, sm.scr, &total);
         uint32_t q = q0, in = 0;
@@ -1427,12 +1425,10 @@ __device__ __forceinline__ uint32_t skip_chunk(const Stream& st, uint32_t c, uin
                                                float cg, uint32_t q_base, uint32_t q[4]) {
   const uint4 w = philox_block(st, c * (kWaveChunk / 4) + lane);
   uint32_t inc[4];
+  geom_skips32(w, cg, inc);
   uint32_t sum = 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    inc[j] = static_cast<uint32_t>(geom_skip32(pick(w, j), cg)) + 1u;
-    sum += inc[j];
-  }
+  for (int j = 0; j < 4; ++j) sum += ++inc[j];
   const uint32_t incl = wave_scan_incl(sum);
   uint32_t x = q_base + incl - sum;
 #pragma unroll
@@ -3023,10 +3019,12 @@ constexpr uint32_t kBernWaveList = kBernWaveGroup * kBernWaveGroups;
 __device__ __forceinline__ uint32_t bern_group(const Stream& st, uint32_t c, uint32_t lane,
                                                float c32, uint32_t inc[4]) {
   const uint4 w = philox_block(st, c * (kBernWaveGroup / 4) + lane);
+  uint32_t skip[4];
+  geom_skips32(w, c32, skip);
   uint32_t sum = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    inc[j] = static_cast<uint32_t>(geom_skip32(pick(w, j), c32)) + 1u;
+    inc[j] = skip[j] + 1u;
     sum += inc[j];
   }
   return sum;
