@@ -322,65 +322,48 @@ constexpr double kD1 = 0x1.b72cd3f331398p+0;  // 2 sqrt(2/e)
 constexpr double kD2 = 0x1.cc3ebd3bc711ap-1;  // 3 - 2 sqrt(3/e)
 constexpr uint64_t kInversionMax = 16;
 
-// 2 ln U, computed before T so that its dependent chain overlaps T's (the
-// wave waits for its slowest lane, and some lane of a wave usually needs it).
-__device__ __forceinline__ double rou_log2u(double u) {
-  double l = 2.0 * log64(u);
-  asm volatile("" : "+v"(l));  // keep it here, not sunk into the test below
-  return l;
-}
-
-// Accept/reject for 2 ln U <= T with the two squeezes; lu2 = rou_log2u(u).
-__device__ __forceinline__ bool rou_accept(double u, double T, double lu2, bool* reject) {
-  *reject = false;
+// Accept/reject for 2 ln U <= T with the two squeezes; lu2 = 2 ln U.
+__device__ __forceinline__ bool rou_accept(double u, double T, double lu2) {
   if (u * (4.0 - u) - 3.0 <= T) return true;
-  if (u * (u - T) >= 1.0) { *reject = true; return false; }
+  if (u * (u - T) >= 1.0) return false;
   return lu2 <= T;
 }
 
-// Broadcast of lane j's value within each aligned quad of lanes (DPP
-// quad_perm), for a double.
-template <int j>
-__device__ __forceinline__ double quad_lane(double x) {
-  constexpr int ctrl = j | (j << 2) | (j << 4) | (j << 6);
-  const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
-  const uint32_t lo = static_cast<uint32_t>(
-      __builtin_amdgcn_update_dpp(0, static_cast<int>(b), ctrl, 0xf, 0xf, false));
-  const uint32_t hi = static_cast<uint32_t>(
-      __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), ctrl, 0xf, 0xf, false));
-  return __longlong_as_double(static_cast<long long>(static_cast<uint64_t>(lo) |
-                                                     (static_cast<uint64_t>(hi) << 32)));
-}
+// An attempt's outcome as a cheaper evaluation sees it.
+enum RouOutcome : int { kRouReject = 0, kRouAccept = 1, kRouUnsure = 2 };
 
 // The ratio-of-uniforms loop: attempt a takes draws 2a (U) and 2a+1 (V),
 // i.e. Philox block a, and the deviate is the first accepted attempt.
-// kWave: the lanes of a wave form aligned groups of G = 2^d.gbits lanes
-// (the whole wave when gbits = 6), each group sampling one deviate, and the
-// group takes its lowest accepted attempt (the same deviate, found in one
-// round instead of one attempt after another).  With G >= 4 each aligned
-// quad of lanes shares one attempt (quad q of a group: attempt G/4 * j + q
-// in round j) and its lanes compute the attempt's ln-factorial terms side by
-// side (attempt(u, v, sub, true, &k), sub = lane mod 4); with G = 2 each
-// lane tries one attempt (attempt 2j + r in round j).
-template <bool kWave, class Attempt>
-__device__ __forceinline__ uint64_t rou_first_accepted(Draws64& d, Attempt attempt) {
+// quick(u, v, &k) decides an attempt (nearly always), exact(u, v, &k) decides
+// the ones it leaves open.  kWave: the lanes of a wave form aligned groups of
+// G = 2^d.gbits lanes (the whole wave when gbits = 6), each group sampling one
+// deviate: lane r of a group tries attempt G j + r in round j, and the group
+// takes its lowest accepted attempt (the same deviate, found in one round
+// instead of one attempt after another).
+template <bool kWave, class Quick, class Exact>
+__device__ __forceinline__ uint64_t rou_first_accepted(Draws64& d, Quick quick, Exact exact) {
+  uint32_t r = 0, base = 0, step = 1;
+  unsigned long long gmask = 0;
   if constexpr (kWave) {
     uint32_t lane = threadIdx.x & 63u;
     asm volatile("" : "+v"(lane));
-    const uint32_t size = 1u << d.gbits;
-    const uint32_t r = lane & (size - 1u);
-    const uint32_t base = lane - r;
-    const unsigned long long gmask = d.gbits >= 6 ? ~0ull : (1ull << size) - 1ull;
-    const bool quad = size >= 4;
-    const uint32_t per_round = quad ? size >> 2 : size;
-    const uint32_t slot = quad ? r >> 2 : r;
-    for (uint32_t round = 0;; ++round) {
-      const uint4 b = philox_block(d.s, round * per_round + slot);
-      const double u = unit_open0(static_cast<uint64_t>(b.x) | (static_cast<uint64_t>(b.y) << 32));
-      const double v = unit_closed0(static_cast<uint64_t>(b.z) | (static_cast<uint64_t>(b.w) << 32));
-      uint64_t k = 0;
-      const bool ok = attempt(u, v, static_cast<int>(lane & 3u), quad, &k);
-      const unsigned long long m = (__ballot(ok) >> base) & gmask;
+    step = 1u << d.gbits;
+    r = lane & (step - 1u);
+    base = lane - r;
+    gmask = d.gbits >= 6 ? ~0ull : (1ull << step) - 1ull;
+  }
+  for (uint32_t a = r;; a += step) {
+    const uint4 b = philox_block(d.s, a);
+    const double u = unit_open0(static_cast<uint64_t>(b.x) | (static_cast<uint64_t>(b.y) << 32));
+    const double v = unit_closed0(static_cast<uint64_t>(b.z) | (static_cast<uint64_t>(b.w) << 32));
+    uint64_t k = 0;
+    int got = quick(u, v, &k);
+    if constexpr (kWave) {
+      unsigned long long m = (__builtin_amdgcn_ballot_w64(got == kRouAccept) >> base) & gmask;
+      // an open attempt matters only ahead of the group's first accepted one
+      if (got == kRouUnsure && (m & ((1ull << r) - 1ull)) == 0)
+        got = exact(u, v, &k) ? kRouAccept : kRouReject;
+      m = (__builtin_amdgcn_ballot_w64(got == kRouAccept) >> base) & gmask;
       if (m != 0) {
         const uint32_t f = static_cast<uint32_t>(__ffsll(static_cast<long long>(m)) - 1);
         uint32_t lo, hi;
@@ -393,15 +376,140 @@ __device__ __forceinline__ uint64_t rou_first_accepted(Draws64& d, Attempt attem
         }
         return static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32);
       }
-    }
-  } else {
-    for (;;) {
-      const double u = unit_open0(d.next());
-      const double v = unit_closed0(d.next());
-      uint64_t k = 0;
-      if (attempt(u, v, 0, false, &k)) return k;
+    } else {
+      if (got == kRouUnsure) got = exact(u, v, &k) ? kRouAccept : kRouReject;
+      if (got == kRouAccept) return k;
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Quick evaluation of an attempt.  The defined steps (about 1000 dependent
+// double-precision instructions: four ln-factorial differences with two
+// logarithms and five correctly rounded divisions each) decide two things: the
+// integer k = floor(x) and the sign of T - 2 ln U.  Both are read off cheaper
+// values with proven error bounds; where a bound does not decide, the defined
+// steps do.
+//
+// With delta = k - mode every ln-factorial difference is a sum of ln z over
+// |delta| consecutive z, centred at z_i; over a centred run
+//   sum ln(z + j) = delta ln z - sum j^2/(2 z^2) - sum j^4/(4 z^4) - ...
+// so T = delta ln(z2 z3 / (z1 z4)) + the runs' corrections: one logarithm of a
+// ratio near 1 instead of eight, and single-precision corrections.
+// ---------------------------------------------------------------------------
+// 1/d and sqrt(x) to about 2^-45.
+__device__ __forceinline__ double quick_rcp(double d) {
+  const double y = __builtin_amdgcn_rcp(d);
+  return __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+}
+__device__ __forceinline__ double quick_sqrt(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y, h = 0.5 * y;
+  return __builtin_fma(g, __builtin_fma(-h, g, 0.5), g);
+}
+
+// floor(x y / z) for a quotient below 2^41 and z below 2^61: the quick
+// quotient is off by one at most, and the remainder (below 2^63 in size, so
+// its low 64 bits hold it) says which way.
+__device__ __forceinline__ uint64_t quick_muldiv(uint64_t x, uint64_t y, uint64_t z) {
+  const double e = (static_cast<double>(x) * static_cast<double>(y)) *
+                   quick_rcp(static_cast<double>(z));
+  uint64_t q = static_cast<uint64_t>(e);
+  const int64_t r = static_cast<int64_t>(x * y - q * z);
+  if (r < 0)
+    --q;
+  else if (r >= static_cast<int64_t>(z))
+    ++q;
+  return q;
+}
+
+// One centred run's correction divided by delta (d2 = delta^2), with h =
+// delta^2 / z^2 and R = 1/z^2:
+//   (h - R)/24 + (h - R)(3h - 7R)/960 + (h - R)(3h^2 - 18hR + 31R^2)/8064;
+// the next term is about h^4 / 18432.
+__device__ __forceinline__ float run_correction(float d2, float z) {
+  const float r = __builtin_amdgcn_rcpf(z);
+  const float R = r * r, h = d2 * R;
+  const float e = __builtin_fmaf(h, __builtin_fmaf(h, 3.0f, -18.0f * R), 31.0f * R * R);
+  const float f = __builtin_fmaf(h, 3.0f / 960.0f, __builtin_fmaf(R, -7.0f / 960.0f, 1.0f / 24.0f));
+  return (h - R) * __builtin_fmaf(e, 1.0f / 8064.0f, f);
+}
+
+// What the quick evaluation keeps of a deviate: x = a + s (V - 1/2) / U, its
+// mode, the largest outcome q, and kcap ~ a + 16 sqrt(var + 1/2).
+struct RouQuick {
+  double a, s, kcap, q, mode;
+  bool on;  // within the bounds' range
+};
+
+// The attempt's outcome; z1 .. z4 (at delta) from zs(delta, z), runs 2 and 4
+// without corrections for a binomial (kRuns = 2: constants).
+template <int kRuns, class Zs>
+__device__ __forceinline__ int rou_quick(const RouQuick& g, double u, double v, uint64_t* out,
+                                         Zs zs) {
+  if (!g.on) return kRouUnsure;
+  const double off = (g.s * (v - 0.5)) * quick_rcp(u);
+  const double x = g.a + off;
+  // |x - the defined x| <= eps: a and s differ by less than 2^-44 of
+  // themselves from the defined ones, the quotient by 2^-44 more
+  const double eps = g.a * 0x1p-43 + __builtin_fabs(off) * 0x1p-42;
+  const double k = __builtin_floor(x);
+  const double fr = x - k;
+  if (x < -eps) return kRouReject;
+  if (!(fr > eps && fr < 1.0 - eps)) return kRouUnsure;
+  if (k > g.q || k > g.kcap + 2.0) return kRouReject;
+  if (k < 0.0 || k > g.kcap - 2.0) return kRouUnsure;
+  *out = static_cast<uint64_t>(k);
+  const double delta = k - g.mode;
+  double z[4];
+  zs(delta, z);
+  const double Q = z[0] * z[3];
+  const double num = __builtin_fma(z[1], z[2], -Q), den = __builtin_fma(z[1], z[2], Q);
+  const double t = num * quick_rcp(den);  // ln(z2 z3 / (z1 z4)) = 2 atanh t
+  const double t2 = t * t;
+  double p = __builtin_fma(t2, 2.0 / 9.0, 2.0 / 7.0);
+  p = __builtin_fma(t2, p, 2.0 / 5.0);
+  p = __builtin_fma(t2, p, 2.0 / 3.0);
+  p = __builtin_fma(t2, p, 2.0) * t;
+  const float df = static_cast<float>(delta), d2 = df * df;
+  const float z1 = static_cast<float>(z[0]), z3 = static_cast<float>(z[2]);
+  float zmin = fminf(z1, z3);
+  float corr = run_correction(d2, z1) - run_correction(d2, z3);
+  if (kRuns == 4) {
+    const float z2 = static_cast<float>(z[1]), z4 = static_cast<float>(z[3]);
+    zmin = fminf(zmin, fminf(z2, z4));
+    corr += run_correction(d2, z4) - run_correction(d2, z2);
+  }
+  const float lu2 = __builtin_amdgcn_logf(static_cast<float>(u)) * 0x1.62e43p+0f;  // 2 ln U
+  if (!(zmin >= 8.0f && 4.0f * d2 <= zmin * zmin && t2 <= 1.0 / 9.0)) {
+    // Far from the mode.  Each step away from it multiplies the mass by at
+    // most the factors by which two of the four counts fall below their
+    // value at the mode, so T <= -D (D - 1)/2 (1/A + 1/B), D = |delta|, A and
+    // B those counts at the mode.
+    const float D = __builtin_fabsf(df);
+    const float up = static_cast<float>(0.5 * (delta + 1.0)), down = up - 1.0f;
+    const float A = df > 0 ? z3 + down : z1 - up;
+    float inv = __builtin_amdgcn_rcpf(A);
+    if (kRuns == 4)
+      inv += __builtin_amdgcn_rcpf(df > 0 ? static_cast<float>(z[1]) + down
+                                          : static_cast<float>(z[3]) - up);
+    return D * (D - 1.0f) * inv * -0.499f < lu2 * 1.001f - 1e-3f ? kRouReject : kRouUnsure;
+  }
+  const double T = delta * (p + static_cast<double>(corr));
+  // Errors: for |delta| <= z/8 and |t| <= 1/8, T's corrections 2.7e-9 |delta|
+  // (single precision; they are below 2.6e-3 |delta|) and its series 2.2e-11
+  // |delta|; up to |delta| = z/2 and |t| = 1/3 the terms left out, 2.5e-6
+  // |delta|; the defined T's own roundings 1e-13 |delta|; 2 ln U from single
+  // precision 5.2e-7 of itself and 1.2e-7.  (Both squeezes of the defined
+  // test follow the comparison wherever it is decided by more than rounding:
+  // u(4-u) - 3 >= 2 ln u >= u - 1/u on (0, 1].)
+  const double margin = T - static_cast<double>(lu2);
+  const bool near = 64.0f * d2 <= zmin * zmin && t2 <= 1.0 / 64.0;
+  const double err = __builtin_fabs(delta) * (near ? 4e-9 : 1e-5) +
+                     static_cast<double>(lu2 * -1e-6f) + 5e-7;
+  if (margin > err) return kRouAccept;
+  if (margin < -err) return kRouReject;
+  return kRouUnsure;
 }
 
 // Hypergeometric core for 1 <= n, M <= N/2.
@@ -426,53 +534,68 @@ __device__ __forceinline__ uint64_t hyp_core(uint64_t n, uint64_t M, uint64_t N,
       }
     }
   }
-  const double pm = static_cast<double>(M) / static_cast<double>(N);
-  const double mu = static_cast<double>(n) * pm;
-  const double var = (mu * (1.0 - pm)) * (static_cast<double>(N - n) / static_cast<double>(N - 1));
-  const double a = mu + 0.5;
-  const double w = __builtin_sqrt(var + 0.5);
-  const double s = kD1 * w + kD2;
-  const uint64_t mode = floor_muldiv(n + 1, M + 1, N + 2);
-  const double kcap = floor(a + 16.0 * w);
-  uint64_t kmax = q + 1;
-  if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
-  const double kmax_d = static_cast<double>(kmax);
+  RouQuick g;
   const uint64_t rest = N - M - n;
-  return rou_first_accepted<kWave>(d, [&](double u, double v, int sub, bool quad,
-                                          uint64_t* out) {
-    const double x = a + (s * (v - 0.5)) / u;
-    if (x < 0.0 || x >= kmax_d) return false;  // the same in every lane of a quad
-    const uint64_t k = static_cast<uint64_t>(floor(x));
-    const double lu2 = rou_log2u(u);
-    double T;
-    if (quad) {
-      // term `sub` in this lane, then the sum in the sequential order
-      uint64_t ta, tb;
-      if (sub == 0) {
-        ta = mode;
-        tb = k;
-      } else if (sub == 1) {
-        ta = M - mode;
-        tb = M - k;
-      } else if (sub == 2) {
-        ta = n - mode;
-        tb = n - k;
-      } else {
-        ta = rest + mode;
-        tb = rest + k;
-      }
-      const double t = lnfact_diff(ta, tb);
-      T = ((quad_lane<0>(t) + quad_lane<1>(t)) + quad_lane<2>(t)) + quad_lane<3>(t);
-    } else {
-      T = lnfact_diff(mode, k);
-      T = T + lnfact_diff(M - mode, M - k);
-      T = T + lnfact_diff(n - mode, n - k);
-      T = T + lnfact_diff(rest + mode, rest + k);
-    }
-    bool rej;
-    *out = k;
-    return rou_accept(u, T, lu2, &rej);
-  });
+  const double nd = static_cast<double>(n), Md = static_cast<double>(M);
+  const double Nd = static_cast<double>(N), rd = static_cast<double>(rest);
+  {
+    const double pm = Md * quick_rcp(Nd);
+    const double mu = nd * pm;
+    const double var = (mu * (1.0 - pm)) *
+                       (static_cast<double>(N - n) * quick_rcp(static_cast<double>(N - 1)));
+    const double w = quick_sqrt(var + 0.5);
+    g.a = mu + 0.5;
+    g.s = __builtin_fma(kD1, w, kD2);
+    g.kcap = __builtin_fma(16.0, w, g.a);
+    g.q = static_cast<double>(q);
+    g.on = N < (1ull << 60) && mu < 0x1p40;
+    g.mode = g.on ? static_cast<double>(quick_muldiv(n + 1, M + 1, N + 2)) : 0.0;
+  }
+  return rou_first_accepted<kWave>(
+      d,
+      [&](double u, double v, uint64_t* out) {
+        return rou_quick<4>(g, u, v, out, [&](double delta, double (&z)[4]) {
+          const double up = g.mode + 0.5 * (delta + 1.0), down = g.mode + 0.5 * (delta - 1.0);
+          z[0] = up;
+          z[1] = Md - down;
+          z[2] = nd - down;
+          z[3] = rd + up;
+        });
+      },
+      [&](double u, double v, uint64_t* out) {  // the defined steps
+        const double pm = static_cast<double>(M) / static_cast<double>(N);
+        const double mu = static_cast<double>(n) * pm;
+        const double var =
+            (mu * (1.0 - pm)) * (static_cast<double>(N - n) / static_cast<double>(N - 1));
+        const double a = mu + 0.5;
+        const double w = __builtin_sqrt(var + 0.5);
+        const double s = kD1 * w + kD2;
+        const double x = a + (s * (v - 0.5)) / u;
+        const double kcap = floor(a + 16.0 * w);
+        uint64_t kmax = q + 1;
+        if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
+        if (x < 0.0 || x >= static_cast<double>(kmax)) return false;
+        const uint64_t k = static_cast<uint64_t>(floor(x));
+        const uint64_t mode = floor_muldiv(n + 1, M + 1, N + 2);
+        double T = 0.0;
+#pragma nounroll
+        for (int i = 0; i < 4; ++i) {
+          uint64_t ta = mode, tb = k;
+          if (i == 1) {
+            ta = M - mode;
+            tb = M - k;
+          } else if (i == 2) {
+            ta = n - mode;
+            tb = n - k;
+          } else if (i == 3) {
+            ta = rest + mode;
+            tb = rest + k;
+          }
+          T = T + lnfact_diff(ta, tb);  // 0.0 + the first term is that term
+        }
+        *out = k;
+        return rou_accept(u, T, 2.0 * log64(u));
+      });
 }
 
 // Hyp(n, M, N): successes among n draws without replacement from N items, M
@@ -517,40 +640,53 @@ __device__ __forceinline__ uint64_t binom_core(uint64_t n, uint64_t l, uint64_t 
       }
     }
   }
-  const double pp = static_cast<double>(l) / static_cast<double>(Nv);
-  const double mu = static_cast<double>(n) * pp;
-  const double var = mu * (1.0 - pp);
-  const double a = mu + 0.5;
-  const double w = __builtin_sqrt(var + 0.5);
-  const double s = kD1 * w + kD2;
-  const uint64_t mode = floor_muldiv(n + 1, l, Nv);
-  const double kcap = floor(a + 16.0 * w);
-  uint64_t kmax = n + 1;
-  if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
-  const double kmax_d = static_cast<double>(kmax);
-  const double lodds = log1p64(
-      static_cast<double>(static_cast<int64_t>(2 * l) - static_cast<int64_t>(Nv)) /
-      static_cast<double>(r));
-  return rou_first_accepted<kWave>(d, [&](double u, double v, int sub, bool quad,
-                                          uint64_t* out) {
-    const double x = a + (s * (v - 0.5)) / u;
-    if (x < 0.0 || x >= kmax_d) return false;  // the same in every lane of a quad
-    const uint64_t k = static_cast<uint64_t>(floor(x));
-    const double lu2 = rou_log2u(u);
-    double T = static_cast<double>(static_cast<int64_t>(k) - static_cast<int64_t>(mode)) * lodds;
-    if (quad) {
-      // lanes 0 and 1 of the quad: one ln-factorial term each
-      const double t = sub == 0 ? lnfact_diff(mode, k) : sub == 1 ? lnfact_diff(n - mode, n - k)
-                                                                  : 0.0;
-      T = (T + quad_lane<0>(t)) + quad_lane<1>(t);
-    } else {
-      T = T + lnfact_diff(mode, k);
-      T = T + lnfact_diff(n - mode, n - k);
-    }
-    bool rej;
-    *out = k;
-    return rou_accept(u, T, lu2, &rej);
-  });
+  RouQuick g;
+  const double nd = static_cast<double>(n), ld = static_cast<double>(l);
+  const double rd = static_cast<double>(r);
+  {
+    const double pp = ld * quick_rcp(static_cast<double>(Nv));
+    const double mu = nd * pp;
+    const double w = quick_sqrt(mu * (1.0 - pp) + 0.5);
+    g.a = mu + 0.5;
+    g.s = __builtin_fma(kD1, w, kD2);
+    g.kcap = __builtin_fma(16.0, w, g.a);
+    g.q = nd;
+    g.on = Nv < (1ull << 60) && mu < 0x1p40;
+    g.mode = g.on ? static_cast<double>(quick_muldiv(n + 1, l, Nv)) : 0.0;
+  }
+  return rou_first_accepted<kWave>(
+      d,
+      [&](double u, double v, uint64_t* out) {
+        return rou_quick<2>(g, u, v, out, [&](double delta, double (&z)[4]) {
+          z[0] = g.mode + 0.5 * (delta + 1.0);
+          z[1] = ld;
+          z[2] = nd - (g.mode + 0.5 * (delta - 1.0));
+          z[3] = rd;
+        });
+      },
+      [&](double u, double v, uint64_t* out) {  // the defined steps
+        const double pp = static_cast<double>(l) / static_cast<double>(Nv);
+        const double mu = static_cast<double>(n) * pp;
+        const double var = mu * (1.0 - pp);
+        const double a = mu + 0.5;
+        const double w = __builtin_sqrt(var + 0.5);
+        const double s = kD1 * w + kD2;
+        const double x = a + (s * (v - 0.5)) / u;
+        const double kcap = floor(a + 16.0 * w);
+        uint64_t kmax = n + 1;
+        if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
+        if (x < 0.0 || x >= static_cast<double>(kmax)) return false;
+        const uint64_t k = static_cast<uint64_t>(floor(x));
+        const uint64_t mode = floor_muldiv(n + 1, l, Nv);
+        const double lodds = log1p64(
+            static_cast<double>(static_cast<int64_t>(2 * l) - static_cast<int64_t>(Nv)) /
+            static_cast<double>(r));
+        double T = static_cast<double>(static_cast<int64_t>(k) - static_cast<int64_t>(mode)) * lodds;
+        T = T + lnfact_diff(mode, k);
+        T = T + lnfact_diff(n - mode, n - k);
+        *out = k;
+        return rou_accept(u, T, 2.0 * log64(u));
+      });
 }
 
 // Bin(n, l/Nv) from stream (seed, node, WRSPLIT, 0).  kWave: called by
