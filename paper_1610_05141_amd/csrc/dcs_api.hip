@@ -484,7 +484,7 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
                           uint32_t n_inst, uint64_t threads, uint64_t top_threads,
                           uint64_t leaf_cap, uint32_t stack_depth, uint64_t* out, hipStream_t s,
                           unsigned int* err, uint32_t leaf_wgs_per_cu, bool wide_dense,
-                          uint64_t* part_out, const Instance* whole) {
+                          uint64_t* part_out, const Instance* whole, bool edges) {
   if (leaf_cap >= dcs::kMaxLeafJobs) return DCS_ENOMEM;
   char* base = static_cast<char*>(ws);
   Control* ctl = reinterpret_cast<Control*>(base + L.ctl);
@@ -495,7 +495,7 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   uint32_t* redo = L.redo_words ? reinterpret_cast<uint32_t*>(base + L.redo) : nullptr;
   Timing t0{}, t1{}, t2{};
   timing_begin(0, s, &t0);
-  hipError_t e = dcs::launch_reset(ctl, single, inst, err, redo, L.redo_words, out, s);
+  hipError_t e = dcs::launch_reset(ctl, single, inst, err, redo, L.redo_words, out, edges, s);
   timing_end(s, &t0);
   if (e != hipSuccess) return DCS_EHIP;
   timing_begin(1, s, &t1);
@@ -522,18 +522,19 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   timing_begin(2, s, &t2);
   timing_begin(4, s, &t4);
   e = dcs::launch_leaf_sort(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(sort_want), s, 0,
-                            takes);
+                            takes, edges);
   timing_end(s, &t4);
   if (e == hipSuccess) {
     timing_begin(5, s, &t5);
     if (wide_dense)
-      e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 0);
+      e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 0,
+                                 edges);
     timing_end(s, &t5);
   }
   Timing t13{};
   if (e == hipSuccess && !(takes & dcs::kTakesOnce)) {
     timing_begin(13, s, &t13);
-    e = dcs::launch_leaf_once(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s);
+    e = dcs::launch_leaf_once(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, edges);
     timing_end(s, &t13);
   }
   Timing t6{};
@@ -542,7 +543,7 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
     if (c->leaf_grid > 0) waves = static_cast<uint64_t>(c->leaf_grid) * (dcs::kLeafBlock / 64);
     waves = std::max<uint64_t>(1, std::min<uint64_t>(waves, leaf_cap));
     timing_begin(6, s, &t6);
-    e = dcs::launch_leaf_dense(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(waves), s);
+    e = dcs::launch_leaf_dense(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(waves), s, edges);
     timing_end(s, &t6);
   }
   Timing t12{};
@@ -551,7 +552,7 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
     if (c->leaf_grid > 0) waves = static_cast<uint64_t>(c->leaf_grid) * (dcs::kLeafBlock / 64);
     waves = std::max<uint64_t>(1, std::min<uint64_t>(waves, leaf_cap));
     timing_begin(12, s, &t12);
-    e = dcs::launch_leaf_small(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(waves), s);
+    e = dcs::launch_leaf_small(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(waves), s, edges);
     timing_end(s, &t12);
   }
   // Second round: the tree threads marked in `redo` run again into the
@@ -562,9 +563,10 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
                          ctl, redo, 1, s);
   if (e == hipSuccess && redo != nullptr)
     e = dcs::launch_leaf_sort(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(sort_want), s, 1,
-                              takes);
+                              takes, edges);
   if (e == hipSuccess && redo != nullptr && wide_dense)
-    e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 1);
+    e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 1,
+                               edges);
   timing_end(s, &t2);
   if (e != hipSuccess) return DCS_EHIP;
   return DCS_OK;
@@ -572,11 +574,9 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
 
 std::mutex& lock() { return g_mu; }
 
-// noalloc: run in this device's static scratch array (DCS_ENOMEM if the
-// call needs more); the call then allocates no device memory.
 int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, const dcs_params* params,
-                    uint64_t* out, void* workspace, size_t ws_bytes, void* stream,
-                    bool noalloc = false) {
+                    uint64_t* out, void* workspace, size_t ws_bytes, void* stream, bool noalloc,
+                    bool edges) {
   Params P;
   if (read_params(params, &P) != DCS_OK) return DCS_EINVAL;
   if (N > DCS_MAX_UNIVERSE) return DCS_EINVAL;
@@ -616,7 +616,7 @@ int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, con
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out, static_cast<hipStream_t>(stream),
                            error_word(c, stream), leaf_wgs_for(c, variant, n),
-                           has_wide_dense(variant, P.n0, P.dense_ratio));
+                           has_wide_dense(variant, P.n0, P.dense_ratio), nullptr, nullptr, edges);
 }
 
 struct BernLayout {
@@ -669,6 +669,79 @@ BernLayout bern_layout(uint64_t n_chunks) {
   o = align_up(o + sizeof(unsigned long long) * n_chunks);
   L.total = o;
   return L;
+}
+
+int32_t sample_bernoulli(double p, uint64_t N, uint64_t seed, const dcs_params* params,
+                                uint64_t* out_dev, uint64_t capacity, uint64_t* count_dev,
+                                void* workspace, size_t ws_bytes, void* stream, bool edges) {
+  Params P;
+  if (read_params(params, &P) != DCS_OK) return DCS_EINVAL;
+  if (!(p >= 0.0 && p <= 1.0) || N > DCS_MAX_BERNOULLI_UNIVERSE) return DCS_EINVAL;
+  if (count_dev == nullptr || (capacity > 0 && out_dev == nullptr)) return DCS_EINVAL;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  std::lock_guard<std::mutex> lk(g_mu);
+  DeviceCtx* c;
+  int32_t rc = device_ctx(&c);
+  if (rc) return rc;
+  if (p == 0.0 || N == 0) {
+    return hip_status(hipMemsetAsync(count_dev, 0, sizeof(uint64_t), s));
+  }
+  if (p == 1.0) return hip_status(dcs::launch_bernoulli_fill(N, out_dev, capacity, count_dev, edges,
+                                                      s));
+  const uint64_t chunk = bern_chunk_len(p, P.n0);
+  const uint64_t n_chunks = (N + chunk - 1) / chunk;
+  const BernLayout L = bern_layout(n_chunks);
+  void* ws = workspace;
+  if (ws == nullptr) {
+    rc = own_workspace(c, L.total, &ws);
+    if (rc) return rc;
+  } else if (ws_bytes < L.total) {
+    return DCS_ENOMEM;
+  }
+  char* base = static_cast<char*>(ws);
+  Control* ctl = reinterpret_cast<Control*>(base + L.ctl);
+  unsigned long long* status = reinterpret_cast<unsigned long long*>(base + L.status);
+  unsigned long long* tickets = reinterpret_cast<unsigned long long*>(base + L.tickets);
+  const double c64 = 1.0 / host_log1p_series(-p);
+  const float c32 = static_cast<float>(c64);
+  const int fp32 = p >= 0x1p-10 ? 1 : 0;
+  Timing t0{}, t1{};
+  timing_begin(0, s, &t0);
+  hipError_t e = dcs::launch_zero(ctl, status, n_chunks, tickets, error_word(c, stream), s);
+  timing_end(s, &t0);
+  if (e != hipSuccess) return DCS_EHIP;
+  // LDS offsets per double-precision chunk: 2 n0 + 64, or fewer when a full
+  // chunk expects fewer hits (chunks clamped at 2^32 for small p); a chunk
+  // with more hits writes the rest in a second pass, so this choice never
+  // changes the sample, only how many work-groups stay resident.  The grid
+  // never exceeds the resident work-groups (the look-back needs them all).
+  uint32_t lds_cap = 2 * P.n0 + 64;
+  if (!fp32) {
+    const double m = static_cast<double>(chunk) * p;
+    const double want = m + 10.0 * sqrt(m) + 64.0;
+    if (want < static_cast<double>(lds_cap))
+      lds_cap = (static_cast<uint32_t>(want) + 63u) & ~63u;
+  }
+  const uint32_t forced_list = g_debug_bern_list.load();
+  if (!fp32 && forced_list != 0) lds_cap = forced_list;
+  // chunks expecting few hits (a short LDS list) take one wave each
+  const int kind = fp32 ? dcs::kBernFp32Wave
+                        : (lds_cap <= dcs::kBern64WaveMaxList ? dcs::kBernFp64Wave
+                                                              : dcs::kBernFp64Group);
+  const uint64_t occ = static_cast<uint64_t>(
+      kind == dcs::kBernFp32Wave   ? c->bern_wave_occupancy
+      : kind == dcs::kBernFp64Wave ? dcs::bern64_wave_occupancy(lds_cap)
+                                   : dcs::bern_occupancy(lds_cap));
+  const uint32_t grid = static_cast<uint32_t>(
+      std::max<uint64_t>(1, std::min<uint64_t>(n_chunks, static_cast<uint64_t>(c->cus) * occ)));
+  timing_begin(3, s, &t1);
+  const uint32_t help = g_debug_help_polls.load();
+  e = dcs::launch_bernoulli(p, N, seed, chunk, n_chunks, kind, c64, c32, status, out_dev, capacity,
+                            count_dev, ctl, tickets, grid, lds_cap,
+                            help != 0 ? help : dcs::kHelpPolls, edges, s);
+  timing_end(s, &t1);
+  if (e != hipSuccess) return DCS_EHIP;
+  return DCS_OK;
 }
 
 }  // namespace host
@@ -912,73 +985,8 @@ uint64_t dcs_bernoulli_capacity_hint(double p, uint64_t N) {
 int32_t dcs_sample_bernoulli_ex(double p, uint64_t N, uint64_t seed, const dcs_params* params,
                                 uint64_t* out_dev, uint64_t capacity, uint64_t* count_dev,
                                 void* workspace, size_t ws_bytes, void* stream) {
-  Params P;
-  if (read_params(params, &P) != DCS_OK) return DCS_EINVAL;
-  if (!(p >= 0.0 && p <= 1.0) || N > DCS_MAX_BERNOULLI_UNIVERSE) return DCS_EINVAL;
-  if (count_dev == nullptr || (capacity > 0 && out_dev == nullptr)) return DCS_EINVAL;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  std::lock_guard<std::mutex> lk(g_mu);
-  DeviceCtx* c;
-  int32_t rc = device_ctx(&c);
-  if (rc) return rc;
-  if (p == 0.0 || N == 0) {
-    return hip_status(hipMemsetAsync(count_dev, 0, sizeof(uint64_t), s));
-  }
-  if (p == 1.0) return hip_status(dcs::launch_bernoulli_fill(N, out_dev, capacity, count_dev, s));
-  const uint64_t chunk = bern_chunk_len(p, P.n0);
-  const uint64_t n_chunks = (N + chunk - 1) / chunk;
-  const BernLayout L = bern_layout(n_chunks);
-  void* ws = workspace;
-  if (ws == nullptr) {
-    rc = own_workspace(c, L.total, &ws);
-    if (rc) return rc;
-  } else if (ws_bytes < L.total) {
-    return DCS_ENOMEM;
-  }
-  char* base = static_cast<char*>(ws);
-  Control* ctl = reinterpret_cast<Control*>(base + L.ctl);
-  unsigned long long* status = reinterpret_cast<unsigned long long*>(base + L.status);
-  unsigned long long* tickets = reinterpret_cast<unsigned long long*>(base + L.tickets);
-  const double c64 = 1.0 / host_log1p_series(-p);
-  const float c32 = static_cast<float>(c64);
-  const int fp32 = p >= 0x1p-10 ? 1 : 0;
-  Timing t0{}, t1{};
-  timing_begin(0, s, &t0);
-  hipError_t e = dcs::launch_zero(ctl, status, n_chunks, tickets, error_word(c, stream), s);
-  timing_end(s, &t0);
-  if (e != hipSuccess) return DCS_EHIP;
-  // LDS offsets per double-precision chunk: 2 n0 + 64, or fewer when a full
-  // chunk expects fewer hits (chunks clamped at 2^32 for small p); a chunk
-  // with more hits writes the rest in a second pass, so this choice never
-  // changes the sample, only how many work-groups stay resident.  The grid
-  // never exceeds the resident work-groups (the look-back needs them all).
-  uint32_t lds_cap = 2 * P.n0 + 64;
-  if (!fp32) {
-    const double m = static_cast<double>(chunk) * p;
-    const double want = m + 10.0 * sqrt(m) + 64.0;
-    if (want < static_cast<double>(lds_cap))
-      lds_cap = (static_cast<uint32_t>(want) + 63u) & ~63u;
-  }
-  const uint32_t forced_list = g_debug_bern_list.load();
-  if (!fp32 && forced_list != 0) lds_cap = forced_list;
-  // chunks expecting few hits (a short LDS list) take one wave each
-  const int kind = fp32 ? dcs::kBernFp32Wave
-                        : (lds_cap <= dcs::kBern64WaveMaxList ? dcs::kBernFp64Wave
-                                                              : dcs::kBernFp64Group);
-  const uint64_t occ = static_cast<uint64_t>(
-      kind == dcs::kBernFp32Wave   ? c->bern_wave_occupancy
-      : kind == dcs::kBernFp64Wave ? dcs::bern64_wave_occupancy(lds_cap)
-                                   : dcs::bern_occupancy(lds_cap));
-  const uint32_t grid = static_cast<uint32_t>(
-      std::max<uint64_t>(1, std::min<uint64_t>(n_chunks, static_cast<uint64_t>(c->cus) * occ)));
-  timing_begin(3, s, &t1);
-  const uint32_t help = g_debug_help_polls.load();
-  e = dcs::launch_bernoulli(p, N, seed, chunk, n_chunks, kind, c64, c32, status, out_dev, capacity,
-                            count_dev, ctl, tickets, grid, lds_cap,
-                            help != 0 ? help : dcs::kHelpPolls, s);
-  timing_end(s, &t1);
-  if (e != hipSuccess) return DCS_EHIP;
-  return DCS_OK;
+  return sample_bernoulli(p, N, seed, params, out_dev, capacity, count_dev, workspace, ws_bytes,
+                          stream);
 }
 
 int32_t dcs_sample_bernoulli(double p, uint64_t N, uint64_t seed, uint64_t* out_dev,

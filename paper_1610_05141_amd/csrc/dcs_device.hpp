@@ -257,6 +257,53 @@ __device__ __forceinline__ void geom_skips32(const uint4& w, float c, uint32_t (
       skip[j] = static_cast<uint32_t>(geom_skip32(pick(w, j), c));
 }
 
+// Double-precision skips.  The defined skip is the floor of x = log64(U) c
+// (at most 2^33); nearly always it can be read off x' = ln'(U) c with
+//   ln'(U) = e ln 2 + T_i + (r - r^2/2 + r^3/3 - r^4/4 + r^5/5),
+// U = 2^e m, i the leading 7 bits of m, r = m / c_i - 1 (|r| <= 2^-8) and
+// T_i = ln c_i from a table of 128 entries.  Both logarithms lie within 2^-46
+// of ln U (|ln U| < 37), so |x' - x| < 2^-45 |c| + x 2^-52 < 2^-44 |c|, and
+// where no integer lies within 2^-43 |c| of x' the floors are equal;
+// otherwise the defined skip is taken.
+struct LogEntry {
+  double inv, ln;  // 1/c_i, -ln of it
+};
+constexpr uint32_t kLogEntries = 128;
+__device__ __forceinline__ LogEntry log_entry(uint32_t i) {
+  LogEntry t;
+  t.inv = 1.0 / (1.0 + (static_cast<double>(i) + 0.5) * (1.0 / kLogEntries));
+  t.ln = -log64(t.inv);
+  return t;
+}
+
+// The skip of one 64-bit draw as a double (every lane of a wave); half =
+// 1/2 - 2^-43 |c|.
+__device__ __forceinline__ double geom_skip64(uint64_t draw, double c, double half,
+                                              const LogEntry* tab) {
+  // 2^64 U = the draw's leading 53 bits plus one, exact
+  const double lo = static_cast<double>(static_cast<uint32_t>(draw) & 0xFFFFF800u) + 2048.0;
+  const double x64 = __builtin_fma(static_cast<double>(static_cast<uint32_t>(draw >> 32)),
+                                   0x1p32, lo);
+  const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(x64));
+  const uint32_t hi = static_cast<uint32_t>(bits >> 32);
+  const LogEntry t = tab[(hi >> 13) & (kLogEntries - 1)];
+  const double m = __longlong_as_double(static_cast<long long>(
+      (bits & 0xFFFFFFFFull) |
+      (static_cast<uint64_t>((hi & 0x000FFFFFu) | 0x3FF00000u) << 32)));
+  const double e = static_cast<double>(static_cast<int>(hi >> 20) - (1023 + 64));
+  const double r = __builtin_fma(m, t.inv, -1.0);
+  double p = __builtin_fma(r, 1.0 / 5.0, -1.0 / 4.0);
+  p = __builtin_fma(r, p, 1.0 / 3.0);
+  p = __builtin_fma(r, p, -1.0 / 2.0);
+  p = __builtin_fma(r * r, p, r);
+  const double x = __builtin_fma(e, 0x1.62e42fefa39efp-1, t.ln + p) * c;
+  const double fr = __builtin_amdgcn_fract(x);
+  double g = x - fr;
+  if (__builtin_amdgcn_ballot_w64(!(__builtin_fabs(fr - 0.5) <= half)) != 0)
+    g = __builtin_floor(log64(unit_open0(draw)) * c);
+  return __builtin_fmin(g, 0x1p33);
+}
+
 // ---------------------------------------------------------------------------
 // ln(a!) - ln(b!)
 // ---------------------------------------------------------------------------
@@ -406,6 +453,36 @@ __device__ __forceinline__ double quick_sqrt(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double g = x * y, h = 0.5 * y;
   return __builtin_fma(g, __builtin_fma(-h, g, 0.5), g);
+}
+
+// ---------------------------------------------------------------------------
+// Edges of a graph (Sec. 7): pair (u, v), v < u, of edge index k < 2^62, u the
+// integer with u(u-1)/2 <= k < u(u+1)/2, i.e. the floor of (1 + sqrt(8k+1))/2,
+// as one word (u at the lower address).  The quick root (2^-47 of itself, 8k+1
+// formed in double) puts that floor within one of u < 2^32; one comparison
+// with the triangular numbers each way makes it exact.  An index outside the
+// range (no sample value gives one) becomes the pair (2^32-1, 2^32-1).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint64_t edge_pair(uint64_t k) {
+  if (k >= (1ull << 62)) return ~0ull;
+  const double x = __builtin_fma(static_cast<double>(k), 8.0, 1.0);
+  uint32_t u = static_cast<uint32_t>(__builtin_fma(quick_sqrt(x), 0.5, 0.5));
+  uint64_t t = (static_cast<uint64_t>(u) * (u - 1u)) >> 1;  // u >= 1
+  if (t > k) {
+    --u;
+    t -= u;
+  } else if (k - t >= u) {
+    t += u;
+    ++u;
+  }
+  return static_cast<uint64_t>(u) | ((k - t) << 32);
+}
+
+// What a sample's value lo + 1 + v is written as: itself, or with kEdges the
+// pair of edge index lo + v (b1 = lo + 1).
+template <bool kEdges>
+__device__ __forceinline__ uint64_t out_value(uint64_t b1, uint64_t v) {
+  return kEdges ? edge_pair(b1 - 1 + v) : b1 + v;
 }
 
 // floor(x y / z) for a quotient below 2^41 and z below 2^61: the quick

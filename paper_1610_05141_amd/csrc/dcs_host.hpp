@@ -114,6 +114,7 @@ int32_t device_ctx(DeviceCtx** out);
 // Leaf work-groups: DCS_LEAF_GRID if set, else cus * leaf_wgs_per_cu (both
 // leaf kernels use it).
 // wide_dense: some instance's tree satisfies has_wide_dense.
+// edges: write the values as the vertex pairs of edge indices.
 // whole: an instance whose canonical tree holds every leaf of the launch
 // (the sample whose parts the instances are); with `single` it decides which
 // specialised leaf kernels can be left out.
@@ -122,10 +123,22 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
                           uint64_t leaf_cap, uint32_t stack_depth, uint64_t* out, hipStream_t s,
                           unsigned int* err, uint32_t leaf_wgs_per_cu,
                           bool wide_dense, uint64_t* part_out = nullptr,
-                          const Instance* whole = nullptr);
+                          const Instance* whole = nullptr, bool edges = false);
 // Whether an instance's tree can hold dense leaves over ranges above 2^16
 // (dense_ratio n_v >= N_v > 2^16 with n_v < n0), which k_leaf_mixed runs.
 bool has_wide_dense(uint32_t variant, uint32_t n0, uint32_t dense_ratio);
+
+// The calls behind dcs_sample_ex (variant 0) / dcs_sample_replacement_ex (1)
+// and dcs_sample_bernoulli_ex; edges: the values are written as the vertex
+// pairs (u, v) of edge indices (value k + 1 <-> index k).
+// noalloc: run in this device's static scratch array (DCS_ENOMEM if the call
+// needs more); the call then allocates no device memory.
+int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed,
+                    const dcs_params* params, uint64_t* out, void* workspace, size_t ws_bytes,
+                    void* stream, bool noalloc = false, bool edges = false);
+int32_t sample_bernoulli(double p, uint64_t N, uint64_t seed, const dcs_params* params,
+                         uint64_t* out, uint64_t capacity, uint64_t* count, void* workspace,
+                         size_t ws_bytes, void* stream, bool edges = false);
 
 // Kernel timing with pooled HIP events on the launch stream (dcs_profile_*):
 // kinds as listed at dcs_profile_read; caller holds lock().

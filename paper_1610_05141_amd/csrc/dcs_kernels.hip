@@ -56,6 +56,30 @@ __device__ __forceinline__ uint64_t wave_scan_incl(uint64_t x) {
   return x;
 }
 
+__device__ __forceinline__ double wave_scan_incl(double x) {
+  const auto step = [&](auto move) {
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
+    const uint32_t lo = move(static_cast<uint32_t>(b)), hi = move(static_cast<uint32_t>(b >> 32));
+    x += __longlong_as_double(static_cast<long long>(
+        static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32)));
+  };
+  step([](uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xf, 0xf, false); });
+  step([](uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xf, 0xf, false); });
+  step([](uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xf, 0xf, false); });
+  step([](uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, 0x118, 0xf, 0xf, false); });
+  step([](uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, 0x142, 0xa, 0xf, false); });
+  step([](uint32_t v) { return __builtin_amdgcn_update_dpp(0u, v, 0x143, 0xc, 0xf, false); });
+  return x;
+}
+
+__device__ __forceinline__ double uniform_double(double x, int lane) {
+  const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(b >> 32), lane);
+  return __longlong_as_double(
+      static_cast<long long>(static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32)));
+}
+
 // kTail = false drops the closing barrier that guards `scratch` against the
 // next scan; the caller then guarantees a barrier before scratch is written
 // again.
@@ -522,14 +546,6 @@ __device__ uint32_t compact_distinct(uint32_t* keys, uint32_t* tmp, uint32_t* sc
   return total;
 }
 
-// out[i] = base + 1 + vals[i] for i < n, coalesced.
-template <int B>
-__device__ __forceinline__ void write_sorted(uint64_t* out, uint64_t base, const uint32_t* vals,
-                                             uint32_t n) {
-  for (uint32_t i = threadIdx.x; i < n; i += B)
-    store_out(out + i, base + 1 + static_cast<uint64_t>(vals[i]));
-}
-
 // Buckets for keys < range: the top 12 of the key's kb = bits(range - 1)
 // bits (all of them when kb <= 12), at most 4096 buckets.
 __device__ __forceinline__ void bucket_params(uint64_t range, uint32_t n, uint32_t* shift,
@@ -545,21 +561,21 @@ __device__ __forceinline__ void bucket_params(uint64_t range, uint32_t n, uint32
 // out[i] = base + 1 + vals[i] for i < n with 16-byte stores where the
 // destination allows (out is 8-byte aligned; pairs start at an even index of
 // the destination).
-template <int B>
+template <int B, bool kEdges>
 __device__ __forceinline__ void write_sorted_pairs(uint64_t* out, uint64_t base,
                                                    const uint32_t* vals, uint32_t n) {
   const uint32_t s0 = static_cast<uint32_t>((reinterpret_cast<uintptr_t>(out) >> 3) & 1u);
   const uint64_t b1 = base + 1;
   const uint32_t tid = lane_tid();
-  if (s0 && tid == 0 && n > 0) store_out(out, b1 + vals[0]);
+  if (s0 && tid == 0 && n > 0) store_out(out, out_value<kEdges>(b1, vals[0]));
   for (uint32_t e = s0 + 2 * tid; e < n; e += 2 * B) {
     if (e + 1 < n) {
       u64x2 pr;
-      pr.x = b1 + vals[e];
-      pr.y = b1 + vals[e + 1];
+      pr.x = out_value<kEdges>(b1, vals[e]);
+      pr.y = out_value<kEdges>(b1, vals[e + 1]);
       __builtin_nontemporal_store(pr, reinterpret_cast<u64x2*>(out + e));
     } else {
-      store_out(out + e, b1 + vals[e]);
+      store_out(out + e, out_value<kEdges>(b1, vals[e]));
     }
   }
 }
@@ -780,7 +796,7 @@ __device__ const uint32_t* leaf_sparse_once(const Stream& st, uint32_t nv, const
 // expected to repeat (n_v^2 >= 2 N_v, any range) run in k_leaf_once, in one
 // pass; k_leaf_mixed skips them, so that its own leaf bodies keep their
 // registers.
-template <int B>
+template <int B, bool kEdges>
 __device__ void leaf_once(const Leaf& L, uint64_t* out, LeafSmem& sm) {
   const uint32_t nv = L.nv;
   const RangeInfo ri = range_info(L.Nv);
@@ -790,7 +806,7 @@ __device__ void leaf_once(const Leaf& L, uint64_t* out, LeafSmem& sm) {
   __builtin_amdgcn_s_setprio(2);  // the passes ahead of other work-groups
   const uint32_t* sorted = leaf_sparse_once<B>(st, nv, ri, shift, nb, sm);
   __builtin_amdgcn_s_setprio(0);
-  write_sorted_pairs<B>(out + L.off, L.lo, sorted, nv);
+  write_sorted_pairs<B, kEdges>(out + L.off, L.lo, sorted, nv);
 }
 
 // ---------------------------------------------------------------------------
@@ -934,7 +950,7 @@ __device__ __forceinline__ void row_words(const SortSmem& sm, uint32_t r0, uint3
 // equal values at neighbouring positions.  (Taking two to four rows at a time
 // to overlap their latencies measured slower: the rows past a leaf's end are
 // work too.)
-template <int B, int R, bool kPow2>
+template <int B, int R, bool kPow2, bool kEdges>
 __device__ __forceinline__ bool write_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
                                            const WordMap& m, const SortSmem& sm) {
   const uint32_t tid = lane_tid();
@@ -950,8 +966,8 @@ __device__ __forceinline__ bool write_rows(uint64_t* o, uint64_t b1, uint32_t s0
     const uint32_t na = lane_after(a);
     const uint32_t p = r0 + 2 * lane - 2 * kHalo;  // wraps below 0 in the first row's outer lanes
     u64x2 pr;
-    pr.x = b1 + a;
-    pr.y = b1 + b;
+    pr.x = out_value<kEdges>(b1, a);
+    pr.y = out_value<kEdges>(b1, b);
     if (r0 >= s0 && r0 + kRow < nn) {  // every inner position and the next one hold keys
       dup |= __builtin_amdgcn_ballot_w64(inner && (a == b || b == na));
       if (inner)
@@ -967,12 +983,12 @@ __device__ __forceinline__ bool write_rows(uint64_t* o, uint64_t b1, uint32_t s0
   return dup != 0;
 }
 
-template <int B, bool kPow2>
+template <int B, bool kPow2, bool kEdges>
 __device__ __forceinline__ bool write_rows_of(uint32_t cls, uint64_t* o, uint64_t b1, uint32_t s0,
                                               uint32_t nn, const WordMap& m, const SortSmem& sm) {
-  if (cls == 0) return write_rows<B, 4, kPow2>(o, b1, s0, nn, m, sm);
-  if (cls == 1) return write_rows<B, 6, kPow2>(o, b1, s0, nn, m, sm);
-  return write_rows<B, 8, kPow2>(o, b1, s0, nn, m, sm);
+  if (cls == 0) return write_rows<B, 4, kPow2, kEdges>(o, b1, s0, nn, m, sm);
+  if (cls == 1) return write_rows<B, 6, kPow2, kEdges>(o, b1, s0, nn, m, sm);
+  return write_rows<B, 8, kPow2, kEdges>(o, b1, s0, nn, m, sm);
 }
 
 // The repeats of a leaf: every position whose value equals the one before it
@@ -1005,7 +1021,7 @@ __device__ void find_repeats(uint32_t s0, uint32_t nn, const WordMap& m, const S
 // values, ascending.  Position p keeps its value v at p - (removed below p) +
 // (new values below v); a new value belongs right after the last position
 // whose value is smaller.
-template <int B>
+template <int B, bool kEdges>
 __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn, const WordMap& m,
                              const SortSmem& sm, uint32_t D) {
   const uint32_t tid = lane_tid();
@@ -1031,16 +1047,16 @@ __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
           removed = removed || dp == q;
           below += sm.scr[kSsNew + i] < v[h] ? 1u : 0u;
         }
-        if (!removed && gone != below) store_out(o + (q - gone + below), b1 + v[h]);
+        if (!removed && gone != below) store_out(o + (q - gone + below), out_value<kEdges>(b1, v[h]));
         // positions up to q that stay, then the new values in the gap above q
         const uint32_t stay = q + 1 - gone - (removed ? 1u : 0u);
         const bool last = q + 1 == nn;
         for (uint32_t i = 0; i < D; ++i) {
           const uint32_t x = sm.scr[kSsNew + i];
           if (x > v[h] && (last || x < v[h + 1]))
-            store_out(o + (stay + i), b1 + x);
+            store_out(o + (stay + i), out_value<kEdges>(b1, x));
           else if (q == s0 && x < v[h])
-            store_out(o + (s0 + i), b1 + x);
+            store_out(o + (s0 + i), out_value<kEdges>(b1, x));
         }
       }
     }
@@ -1106,7 +1122,7 @@ __device__ uint32_t draw_words(const Stream& st, uint32_t t, uint32_t need, cons
 // bitonic network over 4096 keys (the unused ones 2^32 - 1, which sort last),
 // repeats dropped and drawn again until there is none.  For leaves with a
 // bucket of more than 8 keys or more than kMaxFix repeats.
-template <int B>
+template <int B, bool kEdges>
 __device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint32_t n,
                                                        const WordMap& m, bool wr, SortSmem& sm,
                                                        uint64_t* out, uint64_t b1) {
@@ -1145,7 +1161,7 @@ __device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint3
       if ((keep >> q) & 1u) keys[p++] = w[q];
     t = draw_words<B>(st, t, n - have, m, keys + have, sm.scr);
   }
-  for (uint32_t i = lane_tid(); i < n; i += B) store_out(out + i, b1 + word_value(m, keys[i]));
+  for (uint32_t i = lane_tid(); i < n; i += B) store_out(out + i, out_value<kEdges>(b1, word_value(m, keys[i])));
   __syncthreads();
 }
 
@@ -1293,7 +1309,7 @@ __device__ __forceinline__ Leaf cached_kind(const uint32_t* rec) {
 // ---------------------------------------------------------------------------
 // Dense leaf: Algorithm B with geometric skips and repair.
 // ---------------------------------------------------------------------------
-template <int B>
+template <int B, bool kEdges>
 __device__ void leaf_dense(const Leaf& L, uint64_t* out, LeafSmem& sm) {
   const uint32_t tid = lane_tid();
   const uint32_t nv = L.nv;
@@ -1390,7 +1406,7 @@ __device__ void leaf_dense(const Leaf& L, uint64_t* out, LeafSmem& sm) {
       if (i < hits && !((sm.mask[i >> 5] >> (i & 31)) & 1u)) sm.kept[o++] = full ? i : pos[i];
     }
     __syncthreads();
-    write_sorted_pairs<B>(out + L.off, L.lo, sm.kept, nv);
+    write_sorted_pairs<B, kEdges>(out + L.off, L.lo, sm.kept, nv);
     break;
   }
 }
@@ -1453,6 +1469,7 @@ __device__ __forceinline__ void put_chunk(uint16_t* dst, const uint32_t q[4]) {
 // are recomputed from their start position when they are written out), the
 // repair's removed hit indices as a bit mask, and the kept hits written with
 // consecutive lanes on consecutive outputs.
+template <bool kEdges>
 __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, uint16_t* list, uint32_t* mask,
                                 uint32_t* bases) {
   const uint32_t lane = lane_tid();
@@ -1572,7 +1589,7 @@ __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, ui
         const bool kept = k < cnt && !((rm[t] >> (k & 31u)) & 1u);
         const unsigned long long K = __ballot(kept);
         const uint32_t at = done + lane_rank(K);
-        if (kept && at < nv) store_out(o0 + at, b1 + pos[t]);
+        if (kept && at < nv) store_out(o0 + at, out_value<kEdges>(b1, pos[t]));
         done += static_cast<uint32_t>(__popcll(K));
       }
     }
@@ -1787,6 +1804,7 @@ __device__ uint32_t compact_wave(uint32_t* keys, uint32_t n, uint32_t lane) {
   return d;
 }
 
+template <bool kEdges>
 __device__ void leaf_small_wave(const Leaf& L, uint64_t* out, uint32_t* keys, uint32_t* cnt) {
   const uint32_t lane = lane_tid();
   const uint32_t nv = L.nv;
@@ -1804,7 +1822,7 @@ __device__ void leaf_small_wave(const Leaf& L, uint64_t* out, uint32_t* keys, ui
   }
   const uint64_t b1 = L.lo + 1;
   uint64_t* o = out + L.off;
-  for (uint32_t i = lane; i < nv; i += 64) store_out(o + i, b1 + keys[i]);
+  for (uint32_t i = lane; i < nv; i += 64) store_out(o + i, out_value<kEdges>(b1, keys[i]));
 }
 
 template <int B>
@@ -1858,7 +1876,7 @@ __device__ __forceinline__ uint32_t* lds_uniform(lds_u32* p) {
 // repeats; kRareGeneral: a bucket of more than 8 keys (the leaf's words lie
 // in stream order from position 0); otherwise a constant or dense leaf.
 constexpr uint32_t kRareRepeats = 0, kRareGeneral = 1, kRareOther = 2;
-template <int B>
+template <int B, bool kEdges>
 __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* out_any,
                                                     uint32_t t_any, uint32_t what_any) {
   uint32_t* const smem = lds_uniform(lds);
@@ -1875,7 +1893,7 @@ __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* 
     if ((L.flags & 3u) == kKindFill)
       leaf_fill<B>(L, out);
     else if (threadIdx.x < 64)
-      leaf_dense_wave(L, out, list, mask, mask + kWaveMaskWords);
+      leaf_dense_wave<kEdges>(L, out, list, mask, mask + kWaveMaskWords);
     __syncthreads();
     return;
   }
@@ -1886,7 +1904,7 @@ __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* 
     const uint32_t D = __builtin_amdgcn_readfirstlane(sm.scr[kSsDups]);
     if (D <= kMaxFix) {
       draw_missing<B>(v.st, t, D, v.s0, v.nn, v.m, sm);
-      rewrite_rows<B>(v.o, v.b1, v.s0, v.nn, v.m, sm, D);
+      rewrite_rows<B, kEdges>(v.o, v.b1, v.s0, v.nn, v.m, sm, D);
       __syncthreads();
       return;
     }
@@ -1899,12 +1917,12 @@ __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* 
     for (int q = 0; q < R; ++q)
       if (threadIdx.x + q * B < v.nv) sm.keys[threadIdx.x + q * B] = w[q];
   }
-  leaf_general<B>(v.st, t, v.nv, v.m, v.wr, sm, v.o + v.s0, v.b1);
+  leaf_general<B, kEdges>(v.st, t, v.nv, v.m, v.wr, sm, v.o + v.s0, v.b1);
 }
 
 // One sparse or with-replacement leaf (see above).  The counters are zero on
 // entry and on return; ends with a barrier.
-template <int B>
+template <int B, bool kEdges>
 __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec, uint64_t* out) {
   constexpr int kBlk = kKeys / (4 * B);
   constexpr int kQ = 4 * kBlk;
@@ -2027,14 +2045,14 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
   if (tid == 0) sm.scr[kSsClass] = 0;
   uint32_t what = kRareGeneral;
   if (cls < 4) {
-    const bool rep = m.pow2 ? write_rows_of<B, true>(cls, v.o, v.b1, s0, nn, m, sm)
-                            : write_rows_of<B, false>(cls, v.o, v.b1, s0, nn, m, sm);
+    const bool rep = m.pow2 ? write_rows_of<B, true, kEdges>(cls, v.o, v.b1, s0, nn, m, sm)
+                            : write_rows_of<B, false, kEdges>(cls, v.o, v.b1, s0, nn, m, sm);
     if (rep && !v.wr) sm.scr[kSsAny] = 1;
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(sm.scr[kSsAny]) == 0) return;
     what = kRareRepeats;
   }
-  leaf_rare<B>(lds_address(smem), lds_address(rec), out, t_next, what);
+  leaf_rare<B, kEdges>(lds_address(smem), lds_address(rec), out, t_next, what);
 }
 
 // Persistent work-groups: job i of the front and then the back list goes to
@@ -2059,7 +2077,7 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
 // 2.32 ms; a key's place recomputed in the scatter instead of kept 1.05 /
 // 2.48 ms; rows of 256 positions, four to a lane, whose two stores each write
 // half lines, 1.54 / 5.2 ms.
-template <int B>
+template <int B, bool kEdges>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_sort(
     const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2,
     uint32_t takes) {
@@ -2129,9 +2147,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_l
     const uint32_t* const rec = cache + slot * kLeafWords;
     const uint32_t kind = __builtin_amdgcn_readfirstlane(rec[11]) & 3u;
     if (kind == kKindSparse || kind == kKindWr)
-      leaf_sorted<B>(smem, rec, out);
+      leaf_sorted<B, kEdges>(smem, rec, out);
     else
-      leaf_rare<B>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
+      leaf_rare<B, kEdges>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
   }
 }
 
@@ -2140,7 +2158,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_l
 // once_by_group.
 constexpr int kListWide = 0, kListOnce = 1;
 
-template <int B, int kList>
+template <int B, int kList, bool kEdges>
 __device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint64_t leaf_cap,
                                           uint64_t* out, Control* ctl, int round2 = 0) {
   __shared__ uint32_t smem[kSmemWords];
@@ -2195,27 +2213,28 @@ __device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint6
     if (!((keep >> slot) & 1u)) continue;  // another kernel's
     const Leaf L = cached_leaf(cache + slot * kLeafWords);
     if constexpr (kList == kListOnce)
-      leaf_once<B>(L, out, sm);
+      leaf_once<B, kEdges>(L, out, sm);
     else
-      leaf_dense<B>(L, out, sm);
+      leaf_dense<B, kEdges>(L, out, sm);
     __syncthreads();
   }
 }
 
-template <int B>
+template <int B, bool kEdges>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_mixed(
     const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2) {
-  leaf_loop<B, kListWide>(leaves, leaf_cap, out, ctl, round2);
+  leaf_loop<B, kListWide, kEdges>(leaves, leaf_cap, out, ctl, round2);
 }
 
-template <int B>
+template <int B, bool kEdges>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_once(
     const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl) {
-  leaf_loop<B, kListOnce>(leaves, leaf_cap, out, ctl);
+  leaf_loop<B, kListOnce, kEdges>(leaves, leaf_cap, out, ctl);
 }
 
 // Dense leaves of the back list, one wave (and work-group) per leaf: back job
 // i goes to wave i mod G; other jobs are left to k_leaf_mixed.
+template <bool kEdges>
 __global__ __launch_bounds__(64) void k_leaf_dense(const Leaf* __restrict__ leaves,
                                                    uint64_t leaf_cap, uint64_t* out, Control* ctl) {
   __shared__ __align__(16) uint16_t list[kWaveList];
@@ -2235,12 +2254,13 @@ __global__ __launch_bounds__(64) void k_leaf_dense(const Leaf* __restrict__ leav
     L.nv = __builtin_amdgcn_readfirstlane(rec->nv);
     L.flags = __builtin_amdgcn_readfirstlane(rec->flags);
     if (!dense_by_wave(L) || L.nv == 0) continue;
-    leaf_dense_wave(L, out, list, mask, bases);
+    leaf_dense_wave<kEdges>(L, out, list, mask, bases);
   }
 }
 
 // Small sparse and with-replacement leaves of the back list, one wave (and
 // work-group) per leaf: back job i goes to wave i mod G.
+template <bool kEdges>
 __global__ __launch_bounds__(64) void k_leaf_small(const Leaf* __restrict__ leaves,
                                                    uint64_t leaf_cap, uint64_t* out, Control* ctl) {
   __shared__ __align__(16) uint32_t keys[kSmallKeys];
@@ -2259,7 +2279,7 @@ __global__ __launch_bounds__(64) void k_leaf_small(const Leaf* __restrict__ leav
     L.Nv = uniform64(rec->Nv);
     L.off = uniform64(rec->off);
     L.seed = uniform64(rec->seed);
-    leaf_small_wave(L, out, keys, cnt);
+    leaf_small_wave<kEdges>(L, out, keys, cnt);
   }
 }
 
@@ -2296,7 +2316,8 @@ __device__ __forceinline__ bool leaf_inline_kind(const Node& v, const Instance& 
   return static_cast<uint64_t>(I.dense_ratio) * v.nv < v.Nv;  // sparse (dense stay jobs)
 }
 
-__device__ void leaf_inline(const Node& v, const Instance& I, uint64_t* out, uint32_t* row) {
+__device__ void leaf_inline(const Node& v, const Instance& I, uint64_t* out, bool edges,
+                            uint32_t* row) {
   const bool wr = I.variant == 1;
   const Stream st = make_stream(I.seed, v.id, wr ? kWrLeaf : kLeaf, 0);
   const uint32_t thr = range_threshold(v.Nv);
@@ -2318,7 +2339,8 @@ __device__ void leaf_inline(const Node& v, const Instance& I, uint64_t* out, uin
   }
   uint64_t* o = out + I.out_offset + v.off;
   const uint64_t b1 = v.lo + 1;
-  for (uint32_t i = 0; i < nv; ++i) store_out(o + i, b1 + row[i]);
+  for (uint32_t i = 0; i < nv; ++i)
+    store_out(o + i, edges ? out_value<true>(b1, row[i]) : b1 + row[i]);
 }
 
 // Hand leaf v over as a job (round 0: front or back list by kind; round 1:
@@ -2397,7 +2419,7 @@ __device__ __forceinline__ bool emit_or_mark(const Node& v, const Instance& I, L
                                              uint64_t cap, Control* ctl, int round, uint32_t* redo,
                                              uint64_t t, uint32_t* row) {
   if (leaf_inline_kind(v, I)) {
-    leaf_inline(v, I, ctl->out, row);
+    leaf_inline(v, I, ctl->out, ctl->edges != 0, row);
     return true;
   }
   if (emit(v, I, leaves, cap, ctl, round)) return true;
@@ -2640,19 +2662,22 @@ __device__ inline void start_control(Control* ctl, unsigned int* err) {
   ctl->leaf_counts2 = 0;
   ctl->granted2 = ~0ull;
   ctl->out = nullptr;
+  ctl->edges = 0;
   ctl->bern_count = 0;
   ctl->error = 0;
   ctl->err = err != nullptr ? err : &ctl->error;
 }
 
 __global__ void k_reset(Control* ctl, Instance single, int has_single, Instance* table,
-                        unsigned int* err, uint32_t* redo, uint64_t redo_words, uint64_t* out) {
+                        unsigned int* err, uint32_t* redo, uint64_t redo_words, uint64_t* out,
+                        int edges) {
   const uint64_t i0 = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   for (uint64_t i = i0; i < redo_words; i += static_cast<uint64_t>(gridDim.x) * blockDim.x)
     redo[i] = 0;
   if (i0 == 0) {
     start_control(ctl, err);
     ctl->out = out;
+    ctl->edges = static_cast<unsigned int>(edges);
     if (has_single) table[0] = single;
   }
 }
@@ -2684,9 +2709,12 @@ constexpr uint32_t kSpinLimit = 1u << 26;
 // k >= lds_cap are written straight to out (the chunk held more hits than LDS).
 // Skips are capped at 2^33 (anything that long ends the chunk).  Returns the
 // chunk's hit count.
-__device__ uint64_t bern_pass(const Stream& st, uint64_t len, double c64, uint32_t* pos,
-                              uint32_t lds_cap, bool write, uint64_t* out, uint64_t out_first,
-                              uint64_t capacity, uint64_t base, uint64_t* scr64, uint32_t* ends) {
+template <bool kEdges>
+__device__ uint64_t bern_pass(const Stream& st, uint64_t len, double c64, const LogEntry* tab,
+                              uint32_t* pos, uint32_t lds_cap, bool write, uint64_t* out,
+                              uint64_t out_first, uint64_t capacity, uint64_t base,
+                              uint64_t* scr64, uint32_t* ends) {
+  const double half = 0.5 - __builtin_fabs(c64) * 0x1p-43;
   constexpr int B = kBernBlock;
   constexpr uint32_t per = 2u;
   const uint32_t tid = threadIdx.x;
@@ -2701,9 +2729,7 @@ __device__ uint64_t bern_pass(const Stream& st, uint64_t len, double c64, uint32
     const uint64_t d1 = static_cast<uint64_t>(w.z) | (static_cast<uint64_t>(w.w) << 32);
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) {
-      const double g = floor(log64(unit_open0(j ? d1 : d0)) * c64);
-      const double gc = g < 0x1p33 ? g : 0x1p33;
-      inc[j] = static_cast<uint64_t>(gc) + 1;
+      inc[j] = static_cast<uint64_t>(geom_skip64(j ? d1 : d0, c64, half, tab)) + 1;
       sum += inc[j];
     }
     uint64_t total;
@@ -2720,7 +2746,7 @@ __device__ uint64_t bern_pass(const Stream& st, uint64_t len, double c64, uint32
         if (!write) {
           if (idx < lds_cap) pos[idx] = static_cast<uint32_t>(q - 1);
         } else if (idx >= lds_cap && out_first + idx < capacity) {
-          store_out(out + out_first + idx, base + static_cast<uint64_t>(q));
+          store_out(out + out_first + idx, out_value<kEdges>(base + static_cast<uint64_t>(q), 0));
         }
         ++in;
       }
@@ -2862,6 +2888,7 @@ __device__ uint64_t bern_lookback(unsigned long long* status, uint64_t j, uint64
 // c + n_cls, ... in order (one shared counter serializes the hand-out at
 // about one chunk per same-address atomic); a chunk held up is counted by
 // the waiting look-back itself.
+template <bool kEdges>
 __global__ __launch_bounds__(kBernBlock) void k_bern(uint64_t N, uint64_t seed, uint64_t chunk,
                                                      uint64_t n_chunks, double c64,
                                                      unsigned long long* status, uint64_t* out,
@@ -2873,6 +2900,8 @@ __global__ __launch_bounds__(kBernBlock) void k_bern(uint64_t N, uint64_t seed, 
   __shared__ uint64_t scr64[8];
   __shared__ uint32_t ends;
   __shared__ unsigned long long cur, excl;
+  __shared__ LogEntry tab[kLogEntries];
+  if (threadIdx.x < kLogEntries) tab[threadIdx.x] = log_entry(threadIdx.x);  // the loop's first barrier follows
   const uint32_t cls = blockIdx.x % n_cls;
   unsigned long long* const ticket = tickets + cls * kTicketStride;
   for (;;) {
@@ -2885,7 +2914,8 @@ __global__ __launch_bounds__(kBernBlock) void k_bern(uint64_t N, uint64_t seed, 
     const uint64_t len = (N - base) < chunk ? (N - base) : chunk;
     const Stream st = make_stream(seed, j, kBChunk, 0);
     const uint64_t cnt =
-        bern_pass(st, len, c64, pos, lds_cap, false, out, 0, capacity, base, scr64, &ends);
+        bern_pass<kEdges>(st, len, c64, tab, pos, lds_cap, false, out, 0, capacity, base, scr64,
+                          &ends);
     if (threadIdx.x < 64) {
       const uint64_t acc = bern_lookback(status, j, cnt, ctl, help_polls, [&](uint64_t i) {
         const uint64_t bi = i * chunk;
@@ -2904,60 +2934,70 @@ __global__ __launch_bounds__(kBernBlock) void k_bern(uint64_t N, uint64_t seed, 
     const uint64_t first = excl;
     const uint64_t held = cnt < lds_cap ? cnt : lds_cap;
     for (uint64_t i = threadIdx.x; i < held; i += kBernBlock)
-      if (first + i < capacity) store_out(out + first + i, base + static_cast<uint64_t>(pos[i]) + 1);
+      if (first + i < capacity)
+        store_out(out + first + i, out_value<kEdges>(base + 1, pos[i]));
     if (cnt > lds_cap)
-      bern_pass(st, len, c64, pos, lds_cap, true, out, first, capacity, base, scr64, &ends);
+      bern_pass<kEdges>(st, len, c64, tab, pos, lds_cap, true, out, first, capacity, base, scr64,
+                        &ends);
     __syncthreads();
   }
 }
 
 // One wave's pass over a double-precision chunk: the draws and positions of
 // bern_pass (64-bit draws 2b and 2b+1 of Philox block b; lane l takes block
-// 64r + l in round r, so the positions grow with lane and draw).  First pass
-// (out == nullptr): positions - 1 of hits below lds_cap go to pos[] and the
-// hit count is returned; second pass: the hits from lds_cap on are written
-// to out[first + k] as base + position.
-__device__ uint64_t bern64_pass(const Stream& st, uint64_t len, double c64, uint32_t lane,
-                                uint32_t* pos, uint32_t lds_cap, uint64_t* out, uint64_t first,
-                                uint64_t capacity, uint64_t base) {
-  uint64_t last = 0, count = 0;
+// 64r + l in round r, so the positions grow with lane and draw), the positions
+// as doubles (integers below 2^42, exact).  First pass (out == nullptr):
+// positions - 1 of hits below lds_cap go to pos[] and the hit count is
+// returned; second pass: the hits from lds_cap on are written to out[first +
+// k] as base + position.
+template <bool kEdges>
+__device__ __forceinline__ uint64_t bern64_pass(const Stream& st, uint64_t len64, double c64,
+                                                const LogEntry* tab, uint32_t lane, uint32_t* pos,
+                                                uint32_t lds_cap, uint64_t* out, uint64_t first,
+                                                uint64_t capacity, uint64_t base) {
+  const double len = static_cast<double>(len64);  // at most 2^32
+  const double half = 0.5 - __builtin_fabs(c64) * 0x1p-43;
+  double last = 0.0;
+  uint32_t count = 0;  // a chunk of 2^32 elements ends after at most as many draws
   for (uint32_t blk0 = 0;; blk0 += 64) {
     const uint4 w = philox_block(st, blk0 + lane);
     const uint64_t d0 = static_cast<uint64_t>(w.x) | (static_cast<uint64_t>(w.y) << 32);
     const uint64_t d1 = static_cast<uint64_t>(w.z) | (static_cast<uint64_t>(w.w) << 32);
-    uint64_t inc[2];
+    const double i0 = geom_skip64(d0, c64, half, tab) + 1.0;
+    const double i1 = geom_skip64(d1, c64, half, tab) + 1.0;
+    const double incl = wave_scan_incl(i0 + i1);
+    const double q1 = last + incl;
+    const double q0 = q1 - i1;
+    const double end = last + uniform_double(incl, 63);
+    const uint64_t idx0 = static_cast<uint64_t>(count) + 2 * lane;
+    const bool all = end <= len;
+    if (out == nullptr && all && count + 128u <= lds_cap) {
+      pos[idx0] = static_cast<uint32_t>(q0 - 1.0);
+      pos[idx0 + 1] = static_cast<uint32_t>(q1 - 1.0);
+    } else {
 #pragma unroll
-    for (uint32_t j = 0; j < 2; ++j) {
-      const double g = floor(log64(unit_open0(j ? d1 : d0)) * c64);
-      const double gc = g < 0x1p33 ? g : 0x1p33;
-      inc[j] = static_cast<uint64_t>(gc) + 1;
-    }
-    const uint64_t sum = inc[0] + inc[1];
-    const uint64_t incl = wave_scan_incl(sum);
-    const uint64_t total = uniform64(__shfl(incl, 63, 64));
-    const uint64_t q[2] = {last + incl - sum + inc[0], last + incl};
-    const uint64_t idx0 = count + 2ull * lane;
-#pragma unroll
-    for (uint32_t j = 0; j < 2; ++j) {
-      if (q[j] <= len) {
+      for (uint32_t j = 0; j < 2; ++j) {
+        const double q = j ? q1 : q0;
         const uint64_t idx = idx0 + j;
-        if (out == nullptr) {
-          if (idx < lds_cap) pos[idx] = static_cast<uint32_t>(q[j] - 1);
-        } else if (idx >= lds_cap && first + idx < capacity) {
-          store_out(out + first + idx, base + q[j]);
+        if (q <= len) {
+          if (out == nullptr) {
+            if (idx < lds_cap) pos[idx] = static_cast<uint32_t>(q - 1.0);
+          } else if (idx >= lds_cap && first + idx < capacity) {
+            store_out(out + first + idx, out_value<kEdges>(base + static_cast<uint64_t>(q), 0));
+          }
         }
       }
     }
-    if (last + total <= len) {
+    if (all) {
       count += 128;
-      last += total;
+      last = end;
       continue;
     }
     // hits are a prefix of the round's draws (positions increase)
-    const uint32_t in = (q[0] <= len ? 1u : 0u) + (q[1] <= len ? 1u : 0u);
-    const unsigned long long whole = __ballot(in == 2u);
-    const uint32_t nw = static_cast<uint32_t>(__popcll(whole));
-    return count + 2ull * nw + (nw < 64 ? static_cast<uint32_t>(__shfl(in, nw, 64)) : 0u);
+    const uint32_t in = static_cast<uint32_t>(
+        __popcll(__builtin_amdgcn_ballot_w64(q0 <= len)) +
+        __popcll(__builtin_amdgcn_ballot_w64(q1 <= len)));
+    return static_cast<uint64_t>(count) + in;
   }
 }
 
@@ -2966,6 +3006,7 @@ __device__ uint64_t bern64_pass(const Stream& st, uint64_t len, double c64, uint
 // definition, the first lds_cap positions kept in LDS while the look-back
 // runs, the rest recomputed when written; consecutive lanes write
 // consecutive outputs.
+template <bool kEdges>
 __global__ __launch_bounds__(64) void k_bern64_wave(uint64_t N, uint64_t seed, uint64_t chunk,
                                                     uint64_t n_chunks, double c64,
                                                     unsigned long long* status, uint64_t* out,
@@ -2974,7 +3015,9 @@ __global__ __launch_bounds__(64) void k_bern64_wave(uint64_t N, uint64_t seed, u
                                                     unsigned long long* tickets, uint32_t n_cls,
                                                     uint32_t help_polls) {
   extern __shared__ uint32_t pos[];  // lds_cap positions - 1 (dynamic)
+  __shared__ LogEntry tab[kLogEntries];
   const uint32_t lane = lane_tid();
+  for (uint32_t i = lane; i < kLogEntries; i += 64) tab[i] = log_entry(i);
   const uint32_t cls = blockIdx.x % n_cls;
   unsigned long long* const ticket = tickets + cls * kTicketStride;
   for (;;) {
@@ -2985,7 +3028,8 @@ __global__ __launch_bounds__(64) void k_bern64_wave(uint64_t N, uint64_t seed, u
     const uint64_t base = j * chunk;
     const uint64_t len = (N - base) < chunk ? (N - base) : chunk;
     const Stream st = make_stream(seed, j, kBChunk, 0);
-    const uint64_t cnt = bern64_pass(st, len, c64, lane, pos, lds_cap, nullptr, 0, 0, 0);
+    const uint64_t cnt =
+        bern64_pass<kEdges>(st, len, c64, tab, lane, pos, lds_cap, nullptr, 0, 0, 0);
     const uint64_t first = bern_lookback(status, j, cnt, ctl, help_polls, [&](uint64_t i) {
       const uint64_t bi = i * chunk;
       return bern_count64_wave(make_stream(seed, i, kBChunk, 0),
@@ -2997,8 +3041,9 @@ __global__ __launch_bounds__(64) void k_bern64_wave(uint64_t N, uint64_t seed, u
     }
     const uint64_t held = cnt < lds_cap ? cnt : lds_cap;
     for (uint64_t i = lane; i < held; i += 64)
-      if (first + i < capacity) store_out(out + first + i, base + static_cast<uint64_t>(pos[i]) + 1);
-    if (cnt > lds_cap) bern64_pass(st, len, c64, lane, pos, lds_cap, out, first, capacity, base);
+      if (first + i < capacity) store_out(out + first + i, out_value<kEdges>(base + 1, pos[i]));
+    if (cnt > lds_cap)
+      bern64_pass<kEdges>(st, len, c64, tab, lane, pos, lds_cap, out, first, capacity, base);
   }
 }
 
@@ -3060,6 +3105,7 @@ __device__ uint32_t bern_count32_wave(const Stream& st, uint32_t len, float c32,
   }
 }
 
+template <bool kEdges>
 __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uint64_t chunk,
                                                   uint64_t n_chunks, float c32,
                                                   unsigned long long* status, uint64_t* out,
@@ -3159,7 +3205,8 @@ __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uin
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const uint32_t k = k0 + 64u * t + lane;
-          if (k < cnt && first + k < capacity) store_out(out + first + k, base + qb + v[t]);
+          if (k < cnt && first + k < capacity)
+            store_out(out + first + k, out_value<kEdges>(base + qb, v[t]));
         }
       } else {
         uint32_t incl[4];
@@ -3168,7 +3215,8 @@ __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uin
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const uint32_t k = k0 + 64u * t + lane;
-          if (k < cnt && first + k < capacity) store_out(out + first + k, base + qb + incl[t]);
+          if (k < cnt && first + k < capacity)
+            store_out(out + first + k, out_value<kEdges>(base + qb, incl[t]));
           qb += __builtin_amdgcn_readlane(incl[t], 63);
         }
       }
@@ -3176,11 +3224,12 @@ __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uin
   }
 }
 
+template <bool kEdges>
 __global__ void k_bern_fill(uint64_t N, uint64_t* out, uint64_t capacity, uint64_t* count_dev) {
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
   const uint64_t lim = N < capacity ? N : capacity;
   for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < lim; i += stride)
-    store_out(out + i, i + 1);
+    store_out(out + i, out_value<kEdges>(1, i));
   if (blockIdx.x == 0 && threadIdx.x == 0) *count_dev = N;
 }
 
@@ -3554,7 +3603,8 @@ hipError_t error_slots(unsigned int** out) {
 }
 
 hipError_t launch_reset(Control* ctl, const Instance* single, Instance* table, unsigned int* err,
-                        uint32_t* redo, uint64_t redo_words, uint64_t* out, hipStream_t stream) {
+                        uint32_t* redo, uint64_t redo_words, uint64_t* out, bool edges,
+                        hipStream_t stream) {
   Instance one{};
   if (single) one = *single;
   if (redo == nullptr) redo_words = 0;
@@ -3562,7 +3612,7 @@ hipError_t launch_reset(Control* ctl, const Instance* single, Instance* table, u
   if (blocks < 1) blocks = 1;
   if (blocks > 1024) blocks = 1024;
   hipLaunchKernelGGL(k_reset, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, stream, ctl, one,
-                     single ? 1 : 0, table, err, redo, redo_words, out);
+                     single ? 1 : 0, table, err, redo, redo_words, out, edges ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -3579,7 +3629,7 @@ hipError_t launch_zero(Control* ctl, unsigned long long* status, uint64_t n,
 int leaf_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_mixed<kLeafBlock>), kLeafBlock, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_leaf_mixed<kLeafBlock, false>), kLeafBlock, 0) != hipSuccess ||
       occ <= 0)
     occ = 2;
   return occ;
@@ -3588,7 +3638,7 @@ int leaf_occupancy() {
 int sort_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_sort<kSortBlock>), kSortBlock, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_leaf_sort<kSortBlock, false>), kSortBlock, 0) != hipSuccess ||
       occ <= 0)
     occ = 4;
   return occ;
@@ -3597,22 +3647,22 @@ int sort_occupancy() {
 int small_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_small), 64, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_leaf_small<false>), 64, 0) != hipSuccess ||
       occ <= 0)
     occ = 8;
   return occ;
 }
 
 hipError_t launch_leaf_small(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                             uint32_t grid, hipStream_t stream) {
-  hipLaunchKernelGGL(k_leaf_small, dim3(grid), dim3(64), 0, stream, leaves, leaf_cap, out, ctl);
+                             uint32_t grid, hipStream_t stream, bool edges) {
+  hipLaunchKernelGGL((edges ? k_leaf_small<true> : k_leaf_small<false>), dim3(grid), dim3(64), 0, stream, leaves, leaf_cap, out, ctl);
   return hipGetLastError();
 }
 
 int dense_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_dense), 64, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_leaf_dense<false>), 64, 0) != hipSuccess ||
       occ <= 0)
     occ = 8;
   return occ;
@@ -3621,7 +3671,7 @@ int dense_occupancy() {
 int bern_wave_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_bern_wave), 64, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_bern_wave<false>), 64, 0) != hipSuccess ||
       occ <= 0)
     occ = 8;
   return occ;
@@ -3630,7 +3680,7 @@ int bern_wave_occupancy() {
 int bern64_wave_occupancy(uint32_t lds_cap) {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_bern64_wave), 64,
+          &occ, reinterpret_cast<const void*>(k_bern64_wave<false>), 64,
           static_cast<size_t>(lds_cap) * sizeof(uint32_t)) != hipSuccess ||
       occ <= 0)
     occ = 1;
@@ -3640,7 +3690,7 @@ int bern64_wave_occupancy(uint32_t lds_cap) {
 int bern_occupancy(uint32_t lds_cap) {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_bern), kBernBlock,
+          &occ, reinterpret_cast<const void*>(k_bern<false>), kBernBlock,
           static_cast<size_t>(lds_cap) * sizeof(uint32_t)) != hipSuccess ||
       occ <= 0)
     occ = 1;
@@ -3671,22 +3721,22 @@ hipError_t launch_tree(const Instance* inst, uint32_t n_inst, uint64_t total_thr
 }
 
 hipError_t launch_leaf_sort(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                            uint32_t grid, hipStream_t stream, int round2, uint32_t takes) {
-  hipLaunchKernelGGL(k_leaf_sort<kSortBlock>, dim3(grid), dim3(kSortBlock), 0, stream, leaves,
+                            uint32_t grid, hipStream_t stream, int round2, uint32_t takes, bool edges) {
+  hipLaunchKernelGGL((edges ? k_leaf_sort<kSortBlock, true> : k_leaf_sort<kSortBlock, false>), dim3(grid), dim3(kSortBlock), 0, stream, leaves,
                      leaf_cap, out, ctl, round2, takes);
   return hipGetLastError();
 }
 
 hipError_t launch_leaf_mixed(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                             uint32_t grid, hipStream_t stream, int round2) {
-  hipLaunchKernelGGL(k_leaf_mixed<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
+                             uint32_t grid, hipStream_t stream, int round2, bool edges) {
+  hipLaunchKernelGGL((edges ? k_leaf_mixed<kLeafBlock, true> : k_leaf_mixed<kLeafBlock, false>), dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
                      leaf_cap, out, ctl, round2);
   return hipGetLastError();
 }
 
 hipError_t launch_leaf_once(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                            uint32_t grid, hipStream_t stream) {
-  hipLaunchKernelGGL(k_leaf_once<kLeafBlock>, dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
+                            uint32_t grid, hipStream_t stream, bool edges) {
+  hipLaunchKernelGGL((edges ? k_leaf_once<kLeafBlock, true> : k_leaf_once<kLeafBlock, false>), dim3(grid), dim3(kLeafBlock), 0, stream, leaves,
                      leaf_cap, out, ctl);
   return hipGetLastError();
 }
@@ -3700,8 +3750,8 @@ hipError_t launch_part_roots(const Instance& I, uint32_t depth, Node* roots, hip
 }
 
 hipError_t launch_leaf_dense(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                             uint32_t grid, hipStream_t stream) {
-  hipLaunchKernelGGL(k_leaf_dense, dim3(grid), dim3(64), 0, stream, leaves, leaf_cap, out, ctl);
+                             uint32_t grid, hipStream_t stream, bool edges) {
+  hipLaunchKernelGGL((edges ? k_leaf_dense<true> : k_leaf_dense<false>), dim3(grid), dim3(64), 0, stream, leaves, leaf_cap, out, ctl);
   return hipGetLastError();
 }
 
@@ -3709,19 +3759,19 @@ hipError_t launch_bernoulli(double p, uint64_t N, uint64_t seed, uint64_t chunk,
                             int fp32, double c64, float c32, unsigned long long* status,
                             uint64_t* out, uint64_t capacity, uint64_t* count_dev, Control* ctl,
                             unsigned long long* tickets, uint32_t grid, uint32_t lds_cap,
-                            uint32_t help_polls, hipStream_t stream) {
+                            uint32_t help_polls, bool edges, hipStream_t stream) {
   (void)p;
   const uint32_t n_cls = grid < kTicketClasses ? grid : kTicketClasses;
   if (fp32 == kBernFp32Wave)
-    hipLaunchKernelGGL(k_bern_wave, dim3(grid), dim3(64), 0, stream, N, seed, chunk, n_chunks, c32,
+    hipLaunchKernelGGL((edges ? k_bern_wave<true> : k_bern_wave<false>), dim3(grid), dim3(64), 0, stream, N, seed, chunk, n_chunks, c32,
                        status, out, capacity, count_dev, ctl, tickets, n_cls, help_polls);
   else if (fp32 == kBernFp64Wave)
-    hipLaunchKernelGGL(k_bern64_wave, dim3(grid), dim3(64),
+    hipLaunchKernelGGL((edges ? k_bern64_wave<true> : k_bern64_wave<false>), dim3(grid), dim3(64),
                        static_cast<size_t>(lds_cap) * sizeof(uint32_t), stream, N, seed, chunk,
                        n_chunks, c64, status, out, capacity, count_dev, ctl, lds_cap, tickets,
                        n_cls, help_polls);
   else
-    hipLaunchKernelGGL(k_bern, dim3(grid), dim3(kBernBlock),
+    hipLaunchKernelGGL((edges ? k_bern<true> : k_bern<false>), dim3(grid), dim3(kBernBlock),
                        static_cast<size_t>(lds_cap) * sizeof(uint32_t), stream, N, seed, chunk,
                        n_chunks, c64, status, out, capacity, count_dev, ctl, lds_cap, tickets,
                        n_cls, help_polls);
@@ -3798,8 +3848,8 @@ int wb_occupancy() {
 }
 
 hipError_t launch_bernoulli_fill(uint64_t N, uint64_t* out, uint64_t capacity, uint64_t* count_dev,
-                                 hipStream_t stream) {
-  hipLaunchKernelGGL(k_bern_fill, dim3(1024), dim3(256), 0, stream, N, out, capacity, count_dev);
+                                 bool edges, hipStream_t stream) {
+  hipLaunchKernelGGL((edges ? k_bern_fill<true> : k_bern_fill<false>), dim3(1024), dim3(256), 0, stream, N, out, capacity, count_dev);
   return hipGetLastError();
 }
 

@@ -79,7 +79,7 @@ struct Control {
   // 2^32 (capacity plus threads).
   unsigned long long granted;
   unsigned int error;              // this call's own error bits (see `err`)
-  unsigned int pad;
+  unsigned int edges;              // 1: outputs are edge pairs (the tree kernels' own leaves)
   unsigned long long bern_count;   // Bernoulli: total hits (copied to the caller)
   // second round (tree threads whose leaves did not all get a slot, run
   // again): its jobs, all on the back list, as leaf_counts and granted
@@ -127,9 +127,11 @@ constexpr uint32_t kTicketWords = kTicketClasses * kTicketStride;
 // error word); if `single` is non-null, also store that instance as entry 0
 // of the instance table.
 // redo (may be null): the second round's bitmap over tree threads, redo_words
-// 32-bit words, zeroed here too.  out: the call's output.
+// 32-bit words, zeroed here too.  out: the call's output; edges (here and
+// below): values are written as the vertex pairs of edge indices.
 hipError_t launch_reset(Control* ctl, const Instance* single, Instance* table, unsigned int* err,
-                        uint32_t* redo, uint64_t redo_words, uint64_t* out, hipStream_t stream);
+                        uint32_t* redo, uint64_t redo_words, uint64_t* out, bool edges,
+                        hipStream_t stream);
 // launch_reset for a Bernoulli call plus zeroing of its look-back status words
 // and its kTicketWords chunk counters.
 hipError_t launch_zero(Control* ctl, unsigned long long* status, uint64_t n,
@@ -176,23 +178,23 @@ constexpr uint32_t kTakesDense = 1, kTakesSmall = 2, kTakesOnce = 4;
 // the second round's jobs (all on the back list, every kind but
 // k_leaf_mixed's); returns at once when round 0 handed over every leaf.
 hipError_t launch_leaf_sort(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                            uint32_t grid, hipStream_t stream, int round2, uint32_t takes);
+                            uint32_t grid, hipStream_t stream, int round2, uint32_t takes, bool edges);
 // Dense leaves of the back list over ranges above 2^16, one work-group each;
 // they exist only where dense_ratio (n0 - 1) exceeds 2^16.
 hipError_t launch_leaf_mixed(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                             uint32_t grid, hipStream_t stream, int round2);
+                             uint32_t grid, hipStream_t stream, int round2, bool edges);
 // The back list's sparse leaves of more than 1024 values with n_v^2 >= 2 N_v
 // (one-pass sampler).
 hipError_t launch_leaf_once(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                            uint32_t grid, hipStream_t stream);
+                            uint32_t grid, hipStream_t stream, bool edges);
 // Dense leaves of the back list whose range fits 16-bit positions, one wave
 // per leaf (k_leaf_sort skips them).
 hipError_t launch_leaf_dense(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                             uint32_t grid, hipStream_t stream);
+                             uint32_t grid, hipStream_t stream, bool edges);
 // Sparse and with-replacement leaves of the back list with at most 1024
 // values, one wave per leaf (k_leaf_sort skips them).
 hipError_t launch_leaf_small(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
-                             uint32_t grid, hipStream_t stream);
+                             uint32_t grid, hipStream_t stream, bool edges);
 // Bernoulli chunk kernels: kBernFp64Group = k_bern (double-precision skips,
 // one work-group per chunk), kBernFp32Wave = k_bern_wave (p >= 2^-10),
 // kBernFp64Wave = k_bern64_wave (double precision, one wave per chunk, for
@@ -205,7 +207,7 @@ hipError_t launch_bernoulli(double p, uint64_t N, uint64_t seed, uint64_t chunk,
                             uint64_t n_chunks, int fp32, double c64, float c32,
                             unsigned long long* status, uint64_t* out, uint64_t capacity,
                             uint64_t* count_dev, Control* ctl, unsigned long long* tickets,
-                            uint32_t grid, uint32_t lds_cap, uint32_t help_polls,
+                            uint32_t grid, uint32_t lds_cap, uint32_t help_polls, bool edges,
                             hipStream_t stream);
 // Polls of a Bernoulli look-back on a chunk that has published nothing
 // before the waiting wave counts that chunk itself.
@@ -269,7 +271,7 @@ hipError_t launch_wb_write(uint64_t N, uint64_t seed, uint64_t chunk, uint64_t n
 // Resident one-wave work-groups per compute unit of the count and write passes.
 int wb_occupancy();
 hipError_t launch_bernoulli_fill(uint64_t N, uint64_t* out, uint64_t capacity,
-                                 uint64_t* count_dev, hipStream_t stream);
+                                 uint64_t* count_dev, bool edges, hipStream_t stream);
 hipError_t launch_debug(int op, const void* x, const void* x2, void* y, uint64_t count,
                         uint64_t p0, uint64_t p1, uint64_t p2, uint64_t p3, hipStream_t stream);
 
