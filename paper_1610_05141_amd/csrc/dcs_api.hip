@@ -705,11 +705,6 @@ int32_t sample_bernoulli(double p, uint64_t N, uint64_t seed, const dcs_params* 
   const double c64 = 1.0 / host_log1p_series(-p);
   const float c32 = static_cast<float>(c64);
   const int fp32 = p >= 0x1p-10 ? 1 : 0;
-  Timing t0{}, t1{};
-  timing_begin(0, s, &t0);
-  hipError_t e = dcs::launch_zero(ctl, status, n_chunks, tickets, error_word(c, stream), s);
-  timing_end(s, &t0);
-  if (e != hipSuccess) return DCS_EHIP;
   // LDS offsets per double-precision chunk: 2 n0 + 64, or fewer when a full
   // chunk expects fewer hits (chunks clamped at 2^32 for small p); a chunk
   // with more hits writes the rest in a second pass, so this choice never
@@ -728,12 +723,22 @@ int32_t sample_bernoulli(double p, uint64_t N, uint64_t seed, const dcs_params* 
   const int kind = fp32 ? dcs::kBernFp32Wave
                         : (lds_cap <= dcs::kBern64WaveMaxList ? dcs::kBernFp64Wave
                                                               : dcs::kBernFp64Group);
+  // one status word per unit: a work-group's chunks
+  const uint32_t waves = kind == dcs::kBernFp64Wave   ? dcs::kBern64Waves
+                         : kind == dcs::kBernFp32Wave ? dcs::kBernWaves
+                                                      : 1u;
+  const uint64_t units = (n_chunks + waves - 1) / waves;
+  Timing t0{}, t1{};
+  timing_begin(0, s, &t0);
+  hipError_t e = dcs::launch_zero(ctl, status, units, tickets, error_word(c, stream), s);
+  timing_end(s, &t0);
+  if (e != hipSuccess) return DCS_EHIP;
   const uint64_t occ = static_cast<uint64_t>(
       kind == dcs::kBernFp32Wave   ? c->bern_wave_occupancy
       : kind == dcs::kBernFp64Wave ? dcs::bern64_wave_occupancy(lds_cap)
                                    : dcs::bern_occupancy(lds_cap));
   const uint32_t grid = static_cast<uint32_t>(
-      std::max<uint64_t>(1, std::min<uint64_t>(n_chunks, static_cast<uint64_t>(c->cus) * occ)));
+      std::max<uint64_t>(1, std::min<uint64_t>(units, static_cast<uint64_t>(c->cus) * occ)));
   timing_begin(3, s, &t1);
   const uint32_t help = g_debug_help_polls.load();
   e = dcs::launch_bernoulli(p, N, seed, chunk, n_chunks, kind, c64, c32, status, out_dev, capacity,

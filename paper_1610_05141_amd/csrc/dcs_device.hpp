@@ -276,14 +276,12 @@ __device__ __forceinline__ LogEntry log_entry(uint32_t i) {
   return t;
 }
 
-// The skip of one 64-bit draw as a double (every lane of a wave); half =
-// 1/2 - 2^-43 |c|.
-__device__ __forceinline__ double geom_skip64(uint64_t draw, double c, double half,
-                                              const LogEntry* tab) {
+// x' of one 64-bit draw.
+__device__ __forceinline__ double geom_quick64(uint32_t dlo, uint32_t dhi, double c,
+                                               const LogEntry* tab) {
   // 2^64 U = the draw's leading 53 bits plus one, exact
-  const double lo = static_cast<double>(static_cast<uint32_t>(draw) & 0xFFFFF800u) + 2048.0;
-  const double x64 = __builtin_fma(static_cast<double>(static_cast<uint32_t>(draw >> 32)),
-                                   0x1p32, lo);
+  const double lo = static_cast<double>(dlo & 0xFFFFF800u) + 2048.0;
+  const double x64 = __builtin_fma(static_cast<double>(dhi), 0x1p32, lo);
   const uint64_t bits = static_cast<uint64_t>(__double_as_longlong(x64));
   const uint32_t hi = static_cast<uint32_t>(bits >> 32);
   const LogEntry t = tab[(hi >> 13) & (kLogEntries - 1)];
@@ -296,12 +294,27 @@ __device__ __forceinline__ double geom_skip64(uint64_t draw, double c, double ha
   p = __builtin_fma(r, p, 1.0 / 3.0);
   p = __builtin_fma(r, p, -1.0 / 2.0);
   p = __builtin_fma(r * r, p, r);
-  const double x = __builtin_fma(e, 0x1.62e42fefa39efp-1, t.ln + p) * c;
-  const double fr = __builtin_amdgcn_fract(x);
-  double g = x - fr;
-  if (__builtin_amdgcn_ballot_w64(!(__builtin_fabs(fr - 0.5) <= half)) != 0)
-    g = __builtin_floor(log64(unit_open0(draw)) * c);
-  return __builtin_fmin(g, 0x1p33);
+  return __builtin_fma(e, 0x1.62e42fefa39efp-1, t.ln + p) * c;
+}
+
+// The skips of a Philox block's two 64-bit draws as doubles, not yet cut at
+// 2^33 (every lane of a wave); half = 1/2 - 2^-43 |c|.
+__device__ __forceinline__ void geom_skips64(const uint4& w, double c, double half,
+                                             const LogEntry* tab, double g[2]) {
+  const double x0 = geom_quick64(w.x, w.y, c, tab), x1 = geom_quick64(w.z, w.w, c, tab);
+  const double f0 = __builtin_amdgcn_fract(x0), f1 = __builtin_amdgcn_fract(x1);
+  g[0] = x0 - f0;
+  g[1] = x1 - f1;
+  if (__builtin_amdgcn_ballot_w64(!(__builtin_fabs(f0 - 0.5) <= half) ||
+                                  !(__builtin_fabs(f1 - 0.5) <= half)) != 0) {
+#pragma unroll 1
+    for (int j = 0; j < 2; ++j) {
+      const uint64_t d = static_cast<uint64_t>(j ? w.z : w.x) |
+                         (static_cast<uint64_t>(j ? w.w : w.y) << 32);
+      const double x = __builtin_floor(log64(unit_open0(d)) * c);
+      (j ? g[1] : g[0]) = x;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -458,31 +471,31 @@ __device__ __forceinline__ double quick_sqrt(double x) {
 // ---------------------------------------------------------------------------
 // Edges of a graph (Sec. 7): pair (u, v), v < u, of edge index k < 2^62, u the
 // integer with u(u-1)/2 <= k < u(u+1)/2, i.e. the floor of (1 + sqrt(8k+1))/2,
-// as one word (u at the lower address).  The quick root (2^-47 of itself, 8k+1
-// formed in double) puts that floor within one of u < 2^32; one comparison
-// with the triangular numbers each way makes it exact.  An index outside the
-// range (no sample value gives one) becomes the pair (2^32-1, 2^32-1).
+// as one word (u at the lower address).  The index is base + v (base, -1 or
+// more, usually
+// the same for a whole row); 8k + 1 is formed in double and its quick root is
+// within 2^-47 of itself, so (1 + root)/2, less 2^-14, never exceeds the exact
+// value and misses it by less than one: the floor is u or u - 1, and one
+// comparison with the triangular number says which.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t edge_pair(uint64_t k) {
-  if (k >= (1ull << 62)) return ~0ull;
-  const double x = __builtin_fma(static_cast<double>(k), 8.0, 1.0);
-  uint32_t u = static_cast<uint32_t>(__builtin_fma(quick_sqrt(x), 0.5, 0.5));
-  uint64_t t = (static_cast<uint64_t>(u) * (u - 1u)) >> 1;  // u >= 1
-  if (t > k) {
-    --u;
-    t -= u;
-  } else if (k - t >= u) {
-    t += u;
-    ++u;
-  }
-  return static_cast<uint64_t>(u) | ((k - t) << 32);
+template <class V>
+__device__ __forceinline__ uint64_t edge_pair(uint64_t base, V v) {
+  const double x = __builtin_fma(static_cast<double>(v), 8.0,
+                                 __builtin_fma(static_cast<double>(static_cast<int64_t>(base)), 8.0, 1.0));
+  uint32_t u = static_cast<uint32_t>(__builtin_fma(quick_sqrt(x), 0.5, 0.5 - 0x1p-14));
+  const uint64_t d = base + v - ((static_cast<uint64_t>(u) * (u - 1u)) >> 1);  // 0 if u is 0
+  const bool next = d >= u;
+  uint32_t r = static_cast<uint32_t>(d);
+  r -= next ? u : 0u;
+  u += next ? 1u : 0u;
+  return static_cast<uint64_t>(u) | (static_cast<uint64_t>(r) << 32);
 }
 
 // What a sample's value lo + 1 + v is written as: itself, or with kEdges the
 // pair of edge index lo + v (b1 = lo + 1).
-template <bool kEdges>
-__device__ __forceinline__ uint64_t out_value(uint64_t b1, uint64_t v) {
-  return kEdges ? edge_pair(b1 - 1 + v) : b1 + v;
+template <bool kEdges, class V>
+__device__ __forceinline__ uint64_t out_value(uint64_t b1, V v) {
+  return kEdges ? edge_pair(b1 - 1, v) : b1 + v;
 }
 
 // floor(x y / z) for a quotient below 2^41 and z below 2^61: the quick

@@ -57,7 +57,7 @@ struct DeviceCtx {
   int cus = 256;
   int leaf_occupancy = 2;
   int sort_occupancy = 4;
-  int bern_wave_occupancy = 8;
+  int bern_wave_occupancy = 2;
   int dense_occupancy = 8;
   int wb_occupancy = 8;
   int small_occupancy = 8;

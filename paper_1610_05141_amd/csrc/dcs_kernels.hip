@@ -72,6 +72,25 @@ __device__ __forceinline__ double wave_scan_incl(double x) {
   return x;
 }
 
+// Saturating 32-bit forms (v_cvt_u32_f64 clamps).
+__device__ __forceinline__ uint32_t cvt_sat(double x) {
+  uint32_t r;
+  asm("v_cvt_u32_f64 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) {
+  return __builtin_elementwise_add_sat(a, b);
+}
+__device__ __forceinline__ uint32_t wave_scan_sat(uint32_t x) {
+  x = add_sat(x, __builtin_amdgcn_update_dpp(0u, x, 0x111, 0xf, 0xf, true));
+  x = add_sat(x, __builtin_amdgcn_update_dpp(0u, x, 0x112, 0xf, 0xf, true));
+  x = add_sat(x, __builtin_amdgcn_update_dpp(0u, x, 0x114, 0xf, 0xf, true));
+  x = add_sat(x, __builtin_amdgcn_update_dpp(0u, x, 0x118, 0xf, 0xf, true));
+  x = add_sat(x, __builtin_amdgcn_update_dpp(0u, x, 0x142, 0xa, 0xf, false));
+  x = add_sat(x, __builtin_amdgcn_update_dpp(0u, x, 0x143, 0xc, 0xf, false));
+  return x;
+}
+
 __device__ __forceinline__ double uniform_double(double x, int lane) {
   const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
   const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(b), lane);
@@ -2700,6 +2719,16 @@ constexpr unsigned long long kFlagAgg = 1ull << 62;
 constexpr unsigned long long kFlagIncl = 2ull << 62;
 constexpr unsigned long long kValueMask = (1ull << 62) - 1;
 constexpr uint32_t kSpinLimit = 1u << 26;
+// Words per step of a look-back.  Status words are read past the L2 while all
+// other work-groups write and poll theirs, and what is read slows everyone:
+// 64 / 32 / 16 / 8 / 4 words took 1202 / 1172 / 1141 / 1090 / 1120 us for
+// p = 1/100 of 2^36 (reading 256 at once 1490), and a two-level look-back of
+// one read 1290.  Double-precision chunks are shorter, so more of them are
+// under way and a narrow step needs more steps: 1226 / 1215 / 1231 / 1307 us
+// at 64 / 32 / 16 / 8 words for G(n, p) of 2^28 edges.
+constexpr uint32_t kLookWidth64 = 32;
+constexpr uint32_t kLookWidth32 = 8;
+constexpr int kLookSleep = 8;  // s_sleep units between polls (4 to 64: within 1 %)
 
 // Double-precision Bernoulli chunks (p < 2^-10), one work-group per chunk:
 // one pass over the chunk's geometric stream.  Hit k of the chunk sits at
@@ -2725,11 +2754,11 @@ __device__ uint64_t bern_pass(const Stream& st, uint64_t len, double c64, const 
     const uint4 w = philox_block(st, blk0 + tid);
     uint64_t inc[per];
     uint64_t sum = 0;
-    const uint64_t d0 = static_cast<uint64_t>(w.x) | (static_cast<uint64_t>(w.y) << 32);
-    const uint64_t d1 = static_cast<uint64_t>(w.z) | (static_cast<uint64_t>(w.w) << 32);
+    double g[per];
+    geom_skips64(w, c64, half, tab, g);
 #pragma unroll
     for (uint32_t j = 0; j < per; ++j) {
-      inc[j] = static_cast<uint64_t>(geom_skip64(j ? d1 : d0, c64, half, tab)) + 1;
+      inc[j] = static_cast<uint64_t>(__builtin_fmin(g[j], 0x1p33)) + 1;
       sum += inc[j];
     }
     uint64_t total;
@@ -2746,7 +2775,7 @@ __device__ uint64_t bern_pass(const Stream& st, uint64_t len, double c64, const 
         if (!write) {
           if (idx < lds_cap) pos[idx] = static_cast<uint32_t>(q - 1);
         } else if (idx >= lds_cap && out_first + idx < capacity) {
-          store_out(out + out_first + idx, out_value<kEdges>(base + static_cast<uint64_t>(q), 0));
+          store_out(out + out_first + idx, out_value<kEdges>(base + 1, q - 1));
         }
         ++in;
       }
@@ -2803,8 +2832,9 @@ __device__ uint64_t bern_count64_wave(const Stream& st, uint64_t len, double c64
 
 // Decoupled look-back (one wave): chunk j's exclusive prefix is the sum of the
 // aggregates of its predecessors back to the nearest one that has published an
-// inclusive prefix.  Each step reads 64 predecessors at once.  Returns the
-// exclusive prefix in every lane; lane 0 publishes j's inclusive prefix.
+// inclusive prefix.  Each step reads kWidth predecessors at once; a step that
+// lacks a word polls that word alone.  Returns the exclusive prefix in every
+// lane; lane 0 publishes j's inclusive prefix.
 // A status word carries its whole message (flag and value in one 64-bit
 // atomic), so relaxed agent-scope atomics suffice; release/acquire would add
 // a write-back and an invalidation of the whole L2 per access.
@@ -2814,7 +2844,7 @@ __device__ uint64_t bern_count64_wave(const Stream& st, uint64_t len, double c64
 // (Sec. 4.7: chunks are independent); the count is offered to other waves
 // (compare-and-swap, only over an empty word) and the look-back goes on, so
 // it ends whatever runs beside it.  From then on the wave helps at once.
-template <class CountOf>
+template <uint32_t kWidth, class CountOf>
 __device__ uint64_t bern_lookback(unsigned long long* status, uint64_t j, uint64_t cnt,
                                   Control* ctl, uint32_t help_polls, CountOf count_of) {
   const uint32_t lane = threadIdx.x & 63;
@@ -2825,32 +2855,41 @@ __device__ uint64_t bern_lookback(unsigned long long* status, uint64_t j, uint64
   }
   if (lane == 0)
     __hip_atomic_store(&status[j], kFlagAgg | cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  uint64_t acc = 0;
+  uint64_t mine = 0;  // this lane's share of the prefix
   long long top = static_cast<long long>(j) - 1;
   uint32_t spins = 0;
   bool helping = false;
   // this lane's predecessor counted by this wave (valid while `helped` is
-  // set, for the current window of 64)
+  // set, for the nearest window)
   bool helped = false;
   uint64_t own = 0;
   for (;;) {
     const long long i = top - static_cast<long long>(lane);
     // Positions before chunk 0 read as an inclusive prefix of 0.
-    unsigned long long s =
-        i >= 0 ? __hip_atomic_load(&status[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-               : kFlagIncl;
+    unsigned long long s = kFlagAgg;
+    if (lane < kWidth)
+      s = i >= 0 ? __hip_atomic_load(&status[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                 : kFlagIncl;
     if (helped && (s & ~kValueMask) == 0) s = kFlagAgg | own;
     const unsigned long long flag = s & ~kValueMask;
-    const unsigned long long incl = __ballot(flag == kFlagIncl);
-    const unsigned long long none = __ballot(flag == 0);
+    const unsigned long long incl = __builtin_amdgcn_ballot_w64(flag == kFlagIncl);
+    const unsigned long long none = __builtin_amdgcn_ballot_w64(flag == 0);
     const uint32_t first = incl ? static_cast<uint32_t>(__builtin_ctzll(incl)) : 64u;
     const unsigned long long upto = first >= 63 ? ~0ull : ((2ull << first) - 1);
     if (none & upto) {
-      if (helping || ++spins > help_polls) {
-        helping = true;
-        // the nearest predecessor without a word
-        const uint32_t h = static_cast<uint32_t>(__builtin_ctzll(none & upto));
-        const uint64_t ih = static_cast<uint64_t>(top) - h;
+      // the nearest predecessor without a word
+      const uint32_t h = static_cast<uint32_t>(__builtin_ctzll(none & upto));
+      const uint64_t ih = static_cast<uint64_t>(top) - h;
+      unsigned long long word = 0;
+      while (!helping && word == 0) {
+        if (++spins > help_polls) {
+          helping = true;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(kLookSleep);
+        word = __hip_atomic_load(&status[ih], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if (helping) {
         const uint64_t c = count_of(ih);
         if (lane == h) {
           helped = true;
@@ -2860,23 +2899,17 @@ __device__ uint64_t bern_lookback(unsigned long long* status, uint64_t j, uint64
                                                __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
         }
-        continue;
       }
-      if (spins > kSpinLimit) {  // unreachable while help_polls < kSpinLimit
-        if (lane == 0) atomicOr(ctl->err, kErrSpinLimit);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
       continue;
     }
-    uint64_t v = lane <= first ? static_cast<uint64_t>(s & kValueMask) : 0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    acc += v;
+    mine += lane <= first ? static_cast<uint64_t>(s & kValueMask) : 0;
     if (first < 64) break;
-    top -= 64;
+    top -= kWidth;
     helped = false;
   }
+  uint64_t acc = mine;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
   if (lane == 0)
     __hip_atomic_store(&status[j], kFlagIncl | (acc + cnt), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
@@ -2917,7 +2950,7 @@ __global__ __launch_bounds__(kBernBlock) void k_bern(uint64_t N, uint64_t seed, 
         bern_pass<kEdges>(st, len, c64, tab, pos, lds_cap, false, out, 0, capacity, base, scr64,
                           &ends);
     if (threadIdx.x < 64) {
-      const uint64_t acc = bern_lookback(status, j, cnt, ctl, help_polls, [&](uint64_t i) {
+      const uint64_t acc = bern_lookback<64>(status, j, cnt, ctl, help_polls, [&](uint64_t i) {
         const uint64_t bi = i * chunk;
         return bern_count64_wave(make_stream(seed, i, kBChunk, 0),
                                  (N - bi) < chunk ? (N - bi) : chunk, c64, threadIdx.x & 63u);
@@ -2945,110 +2978,168 @@ __global__ __launch_bounds__(kBernBlock) void k_bern(uint64_t N, uint64_t seed, 
 
 // One wave's pass over a double-precision chunk: the draws and positions of
 // bern_pass (64-bit draws 2b and 2b+1 of Philox block b; lane l takes block
-// 64r + l in round r, so the positions grow with lane and draw), the positions
-// as doubles (integers below 2^42, exact).  First pass (out == nullptr):
+// 64r + l in round r, so the positions grow with lane and draw).  A round's
+// increments are added up in 32 bits with saturation; only where their sum
+// reaches 2^32 - 1 (no round of a chunk of many hits) the round is redone
+// with sums in double, exact below 2^53.  First pass (out == nullptr):
 // positions - 1 of hits below lds_cap go to pos[] and the hit count is
 // returned; second pass: the hits from lds_cap on are written to out[first +
 // k] as base + position.
 template <bool kEdges>
-__device__ __forceinline__ uint64_t bern64_pass(const Stream& st, uint64_t len64, double c64,
+__device__ __forceinline__ uint64_t bern64_pass(const Stream& st, uint64_t len, double c64,
                                                 const LogEntry* tab, uint32_t lane, uint32_t* pos,
                                                 uint32_t lds_cap, uint64_t* out, uint64_t first,
                                                 uint64_t capacity, uint64_t base) {
-  const double len = static_cast<double>(len64);  // at most 2^32
   const double half = 0.5 - __builtin_fabs(c64) * 0x1p-43;
-  double last = 0.0;
+  uint64_t last = 0;   // at most len <= 2^32
   uint32_t count = 0;  // a chunk of 2^32 elements ends after at most as many draws
   for (uint32_t blk0 = 0;; blk0 += 64) {
     const uint4 w = philox_block(st, blk0 + lane);
-    const uint64_t d0 = static_cast<uint64_t>(w.x) | (static_cast<uint64_t>(w.y) << 32);
-    const uint64_t d1 = static_cast<uint64_t>(w.z) | (static_cast<uint64_t>(w.w) << 32);
-    const double i0 = geom_skip64(d0, c64, half, tab) + 1.0;
-    const double i1 = geom_skip64(d1, c64, half, tab) + 1.0;
-    const double incl = wave_scan_incl(i0 + i1);
-    const double q1 = last + incl;
-    const double q0 = q1 - i1;
-    const double end = last + uniform_double(incl, 63);
-    const uint64_t idx0 = static_cast<uint64_t>(count) + 2 * lane;
-    const bool all = end <= len;
-    if (out == nullptr && all && count + 128u <= lds_cap) {
-      pos[idx0] = static_cast<uint32_t>(q0 - 1.0);
-      pos[idx0 + 1] = static_cast<uint32_t>(q1 - 1.0);
-    } else {
-#pragma unroll
-      for (uint32_t j = 0; j < 2; ++j) {
-        const double q = j ? q1 : q0;
-        const uint64_t idx = idx0 + j;
-        if (q <= len) {
-          if (out == nullptr) {
-            if (idx < lds_cap) pos[idx] = static_cast<uint32_t>(q - 1.0);
-          } else if (idx >= lds_cap && first + idx < capacity) {
-            store_out(out + first + idx, out_value<kEdges>(base + static_cast<uint64_t>(q), 0));
-          }
-        }
+    double g[2];
+    geom_skips64(w, c64, half, tab, g);
+    const uint32_t i1 = add_sat(cvt_sat(g[1]), 1u);
+    const uint32_t sum = add_sat(add_sat(cvt_sat(g[0]), 1u), i1);
+    const uint32_t incl = wave_scan_sat(sum);
+    uint64_t adv = static_cast<uint32_t>(__builtin_amdgcn_readlane(incl, 63));
+    const uint64_t rem = len - last;
+    const uint32_t p = static_cast<uint32_t>(last) + incl - 1u;
+    uint32_t p0 = p - i1, p1 = p;  // positions - 1 of the two draws where they are hits
+    const uint32_t rem32 = rem < 0xFFFFFFFFull ? static_cast<uint32_t>(rem) : 0xFFFFFFFFu;
+    bool in0 = incl - i1 <= rem32, in1 = incl <= rem32;
+    if (adv == 0xFFFFFFFFull) {
+      const double d1 = __builtin_fmin(g[1], 0x1p33) + 1.0;
+      const double q1 = wave_scan_incl(__builtin_fmin(g[0], 0x1p33) + 1.0 + d1);
+      const double q0 = q1 - d1, r = static_cast<double>(rem);
+      adv = static_cast<uint64_t>(uniform_double(q1, 63));
+      in0 = q0 <= r;
+      in1 = q1 <= r;
+      p0 = static_cast<uint32_t>(last) + static_cast<uint32_t>(in0 ? q0 - 1.0 : 0.0);
+      p1 = static_cast<uint32_t>(last) + static_cast<uint32_t>(in1 ? q1 - 1.0 : 0.0);
+    }
+    const uint64_t idx = static_cast<uint64_t>(count) + 2 * lane;
+    const bool all = adv <= rem;
+    if (out == nullptr) {
+      if (all && count + 128u <= lds_cap) {
+        pos[idx] = p0;
+        pos[idx + 1] = p1;
+      } else {
+        if (in0 && idx < lds_cap) pos[idx] = p0;
+        if (in1 && idx + 1 < lds_cap) pos[idx + 1] = p1;
       }
+    } else {
+      if (in0 && idx >= lds_cap && first + idx < capacity)
+        store_out(out + first + idx, out_value<kEdges>(base + 1, p0));
+      if (in1 && idx + 1 >= lds_cap && first + idx + 1 < capacity)
+        store_out(out + first + idx + 1, out_value<kEdges>(base + 1, p1));
     }
     if (all) {
       count += 128;
-      last = end;
+      last += adv;
       continue;
     }
     // hits are a prefix of the round's draws (positions increase)
-    const uint32_t in = static_cast<uint32_t>(
-        __popcll(__builtin_amdgcn_ballot_w64(q0 <= len)) +
-        __popcll(__builtin_amdgcn_ballot_w64(q1 <= len)));
+    const uint32_t in = static_cast<uint32_t>(__popcll(__builtin_amdgcn_ballot_w64(in0)) +
+                                              __popcll(__builtin_amdgcn_ballot_w64(in1)));
     return static_cast<uint64_t>(count) + in;
   }
 }
 
 // Double-precision Bernoulli chunks that expect few hits (chunks clamped at
-// 2^32 for small p), one wave per chunk and no barrier: the hits of k_bern's
-// definition, the first lds_cap positions kept in LDS while the look-back
-// runs, the rest recomputed when written; consecutive lanes write
-// consecutive outputs.
+// 2^32 for small p), one wave per chunk: the hits of k_bern's definition, the
+// first lds_cap positions kept in LDS while the look-back runs, the rest
+// recomputed when written; consecutive lanes write consecutive outputs.
+// Bound by vector instructions (132 per 64 hits, the two logarithms and the
+// edge's root most of them).  The waves of a work-group take consecutive
+// chunks and look back once for all of them: with one look-back per chunk of
+// about 512 hits its instructions and its traffic were a third of the kernel
+// (2^28 edges: 1970 us; 4 / 8 / 16 chunks per unit 1350 / 1310 / 1570; 1210
+// with the round's sums in 32 bits and the narrower look-back).
 template <bool kEdges>
-__global__ __launch_bounds__(64) void k_bern64_wave(uint64_t N, uint64_t seed, uint64_t chunk,
-                                                    uint64_t n_chunks, double c64,
-                                                    unsigned long long* status, uint64_t* out,
-                                                    uint64_t capacity, uint64_t* count_dev,
-                                                    Control* ctl, uint32_t lds_cap,
-                                                    unsigned long long* tickets, uint32_t n_cls,
-                                                    uint32_t help_polls) {
-  extern __shared__ uint32_t pos[];  // lds_cap positions - 1 (dynamic)
+__global__ __launch_bounds__(64 * kBern64Waves) void k_bern64_wave(
+    uint64_t N, uint64_t seed, uint64_t chunk, uint64_t n_chunks, double c64,
+    unsigned long long* status, uint64_t* out, uint64_t capacity, uint64_t* count_dev,
+    Control* ctl, uint32_t lds_cap, unsigned long long* tickets, uint32_t n_cls,
+    uint32_t help_polls) {
+  extern __shared__ uint32_t lists[];  // lds_cap positions - 1 per wave (dynamic)
   __shared__ LogEntry tab[kLogEntries];
-  const uint32_t lane = lane_tid();
-  for (uint32_t i = lane; i < kLogEntries; i += 64) tab[i] = log_entry(i);
+  __shared__ uint64_t counts[kBern64Waves];
+  __shared__ uint64_t cur, excl;
+  const uint32_t lane = lane_tid() & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr uint32_t waves = kBern64Waves;
+  uint32_t* const pos = lists + wave * lds_cap;
+  for (uint32_t i = threadIdx.x; i < kLogEntries; i += blockDim.x) tab[i] = log_entry(i);
   const uint32_t cls = blockIdx.x % n_cls;
+  const uint64_t n_units = (n_chunks + waves - 1) / waves;
   unsigned long long* const ticket = tickets + cls * kTicketStride;
-  for (;;) {
-    uint64_t jt = 0;
-    if (lane == 0) jt = atomicAdd(ticket, 1ull);
-    const uint64_t j = cls + uniform64(jt) * n_cls;
-    if (j >= n_chunks) break;
+  const auto chunk_len = [&](uint64_t j) {
     const uint64_t base = j * chunk;
-    const uint64_t len = (N - base) < chunk ? (N - base) : chunk;
+    return (N - base) < chunk ? (N - base) : chunk;
+  };
+  for (;;) {
+    if (threadIdx.x == 0) cur = cls + atomicAdd(ticket, 1ull) * n_cls;
+    __syncthreads();
+    const uint64_t unit = uniform64(cur);
+    if (unit >= n_units) break;
+    const uint64_t j = unit * waves + wave;
+    const uint64_t base = j * chunk;
+    const bool mine = j < n_chunks;
+    const uint64_t len = mine ? chunk_len(j) : 0;
     const Stream st = make_stream(seed, j, kBChunk, 0);
-    const uint64_t cnt =
-        bern64_pass<kEdges>(st, len, c64, tab, lane, pos, lds_cap, nullptr, 0, 0, 0);
-    const uint64_t first = bern_lookback(status, j, cnt, ctl, help_polls, [&](uint64_t i) {
-      const uint64_t bi = i * chunk;
-      return bern_count64_wave(make_stream(seed, i, kBChunk, 0),
-                               (N - bi) < chunk ? (N - bi) : chunk, c64, lane);
-    });
-    if (lane == 0 && j == n_chunks - 1) {
-      *count_dev = first + cnt;
-      ctl->bern_count = first + cnt;
+    uint64_t cnt = 0, first = 0;
+    // one copy of the pass's code: the first pass, then where the list is too
+    // short the second
+#pragma unroll 1
+    for (bool write = false; mine || !write; write = true) {
+      if (mine)
+        cnt = bern64_pass<kEdges>(st, len, c64, tab, lane, pos, lds_cap, write ? out : nullptr,
+                                  first, capacity, base);
+      if (write) break;
+      if (lane == 0) counts[wave] = cnt;
+      __syncthreads();
+      uint64_t before = 0, all = 0;
+      for (uint32_t w = 0; w < waves; ++w) {
+        const uint64_t x = uniform64(counts[w]);
+        before += w < wave ? x : 0;
+        all += x;
+      }
+      if (wave == 0) {
+        const uint64_t acc = bern_lookback<kLookWidth64>(
+          status, unit, all, ctl, help_polls, [&](uint64_t u) {
+          uint64_t sum = 0;
+          for (uint32_t w = 0; w < waves; ++w) {
+            const uint64_t i = u * waves + w;
+            if (i < n_chunks)
+              sum += bern_count64_wave(make_stream(seed, i, kBChunk, 0), chunk_len(i), c64, lane);
+          }
+          return sum;
+        });
+        if (lane == 0) {
+          excl = acc;
+          if (unit == n_units - 1) {
+            *count_dev = acc + all;
+            ctl->bern_count = acc + all;
+          }
+        }
+      }
+      __syncthreads();
+      first = uniform64(excl) + before;
+      const uint64_t held = cnt < lds_cap ? cnt : lds_cap;
+      const uint64_t room = first < capacity ? capacity - first : 0;
+      const uint32_t n_out = static_cast<uint32_t>(held < room ? held : room);
+      uint64_t* const o = out + first;
+      for (uint32_t i = lane; i < n_out; i += 64)
+        store_out(o + i, out_value<kEdges>(base + 1, pos[i]));
+      if (cnt <= lds_cap) break;
     }
-    const uint64_t held = cnt < lds_cap ? cnt : lds_cap;
-    for (uint64_t i = lane; i < held; i += 64)
-      if (first + i < capacity) store_out(out + first + i, out_value<kEdges>(base + 1, pos[i]));
-    if (cnt > lds_cap)
-      bern64_pass<kEdges>(st, len, c64, tab, lane, pos, lds_cap, out, first, capacity, base);
   }
 }
 
-// Single-precision Bernoulli chunks (p >= 2^-10), one wave per chunk and no
-// barrier: chunk j's hits are its draws up to the one that passes the chunk
+// Single-precision Bernoulli chunks (p >= 2^-10), one wave per chunk, units of
+// kBernWaves chunks as in k_bern64_wave (p = 1/100 of 2^36: 1860 us with a
+// look-back per chunk; 1480 / 1330 / 1480 / 1480 with 2 / 4 / 5 / 8 chunks per
+// unit -- one wave per SIMD is the even split --, 1245 with full groups written
+// without a test per hit, 1090 with the narrow look-back): chunk j's hits are its draws up to the one that passes the chunk
 // end (Sec. 4.7's skips).  The wave keeps each 256-draw group of the first
 // kBernWaveGroups as 16-bit values: the positions relative to the group's
 // start when the group advances less than 2^16, else the increments (below
@@ -3058,6 +3149,7 @@ __global__ __launch_bounds__(64) void k_bern64_wave(uint64_t N, uint64_t seed, u
 constexpr uint32_t kBernWaveGroup = 256;                     // draws per group
 constexpr uint32_t kBernWaveGroups = 15;                     // groups kept in LDS
 constexpr uint32_t kBernWaveList = kBernWaveGroup * kBernWaveGroups;
+constexpr uint32_t kBernWaveLds = kBernWaveList / 2 + kBernWaveGroups + 1;  // words per wave
 
 // Increments of draw group c (lane l: draws 256c + 4l + j) into dst, and
 // their wave-wide inclusive prefix over lanes.
@@ -3106,15 +3198,21 @@ __device__ uint32_t bern_count32_wave(const Stream& st, uint32_t len, float c32,
 }
 
 template <bool kEdges>
-__global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uint64_t chunk,
+__global__ __launch_bounds__(64 * kBernWaves) void k_bern_wave(uint64_t N, uint64_t seed, uint64_t chunk,
                                                   uint64_t n_chunks, float c32,
                                                   unsigned long long* status, uint64_t* out,
                                                   uint64_t capacity, uint64_t* count_dev,
                                                   Control* ctl, unsigned long long* tickets,
                                                   uint32_t n_cls, uint32_t help_polls) {
-  __shared__ __align__(16) uint16_t list[kBernWaveList];
-  __shared__ uint32_t gbase[kBernWaveGroups + 1];  // position before group c (c <= 15)
-  const uint32_t lane = lane_tid();
+  extern __shared__ __align__(16) uint32_t lists[];  // kBernWaveLds words per wave (dynamic)
+  __shared__ uint32_t counts[kBernWaves];
+  __shared__ uint64_t cur, excl;
+  const uint32_t lane = lane_tid() & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr uint32_t waves = kBernWaves;
+  uint16_t* const list = reinterpret_cast<uint16_t*>(lists + wave * kBernWaveLds);
+  // position before group c (c <= kBernWaveGroups)
+  uint32_t* const gbase = lists + wave * kBernWaveLds + kBernWaveList / 2;
   constexpr uint32_t kSpare = (kBernWaveGroups - 1) * kBernWaveGroup;  // recomputed groups
   // Chunks are handed out by n_cls counters, 256 bytes apart: this wave's
   // class c = blockIdx mod n_cls takes chunks c, c + n_cls, ... in order.
@@ -3124,30 +3222,36 @@ __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uin
   // is held up anyway (its class has no running wave because another kernel
   // holds the GPU), the look-back counts it itself (bern_lookback).
   const uint32_t cls = blockIdx.x % n_cls;
+  const uint64_t n_units = (n_chunks + waves - 1) / waves;
   unsigned long long* const ticket = tickets + cls * kTicketStride;
-  for (;;) {
-    uint64_t jt = 0;
-    if (lane == 0) jt = atomicAdd(ticket, 1ull);
-    const uint64_t j = cls + uniform64(jt) * n_cls;
-    if (j >= n_chunks) break;
+  const auto chunk_len = [&](uint64_t j) {
     const uint64_t base = j * chunk;
-    const uint32_t len = static_cast<uint32_t>((N - base) < chunk ? (N - base) : chunk);
+    return static_cast<uint32_t>((N - base) < chunk ? (N - base) : chunk);
+  };
+  for (;;) {
+    if (threadIdx.x == 0) cur = cls + atomicAdd(ticket, 1ull) * n_cls;
+    __syncthreads();
+    const uint64_t unit = uniform64(cur);
+    if (unit >= n_units) break;
+    const uint64_t j = unit * waves + wave;
+    const uint64_t base = j * chunk;
+    const bool mine = j < n_chunks;
+    const uint32_t len = mine ? chunk_len(j) : 0;
     const Stream st = make_stream(seed, j, kBChunk, 0);
     // hits: the draws whose running position stays within the chunk
     uint32_t q_base = 0, cnt = 0;
     uint32_t rel_groups = 0;  // bit c: group c holds relative positions
-    for (uint32_t c = 0;; ++c) {
+    for (uint32_t c = 0; mine; ++c) {
       uint32_t inc[4];
       const uint32_t sum = bern_group(st, c, lane, c32, inc);
       const uint32_t incl = wave_scan_incl(sum);
       const uint32_t adv = __builtin_amdgcn_readlane(incl, 63);
       uint32_t rel[4];
-      uint32_t r = incl - sum, in = 0;
+      uint32_t r = incl - sum;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         r += inc[k];
         rel[k] = r;
-        in += q_base + r <= len ? 1u : 0u;
       }
       if (c <= kBernWaveGroups && lane == 0) gbase[c] = q_base;
       if (c < kBernWaveGroups) {
@@ -3155,27 +3259,54 @@ __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uin
         put_incs(list + c * kBernWaveGroup + 4u * lane, as_rel ? rel : inc);
         rel_groups |= (as_rel ? 1u : 0u) << c;
       }
-      const unsigned long long whole = __ballot(in == 4u);
-      const uint32_t nw = static_cast<uint32_t>(__popcll(whole));
-      const uint32_t got = nw == 64u ? kBernWaveGroup : 4u * nw + __builtin_amdgcn_readlane(in, nw);
-      cnt += got;
+      if (q_base + adv > len) {  // the draw that passes the chunk's end is here
+        uint32_t in = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) in += q_base + rel[k] <= len ? 1u : 0u;
+        const uint32_t nw =
+            static_cast<uint32_t>(__popcll(__builtin_amdgcn_ballot_w64(in == 4u)));
+        cnt += 4u * nw + __builtin_amdgcn_readlane(in, nw);  // nw < 64
+        break;
+      }
+      cnt += kBernWaveGroup;
       q_base += adv;
-      if (got < kBernWaveGroup) break;
     }
-    const uint64_t first = bern_lookback(status, j, cnt, ctl, help_polls, [&](uint64_t i) {
-      const uint64_t bi = i * chunk;
-      return static_cast<uint64_t>(bern_count32_wave(
-          make_stream(seed, i, kBChunk, 0),
-          static_cast<uint32_t>((N - bi) < chunk ? (N - bi) : chunk), c32, lane));
-    });
-    if (lane == 0 && j == n_chunks - 1) {
-      *count_dev = first + cnt;
-      ctl->bern_count = first + cnt;
+    if (lane == 0) counts[wave] = cnt;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (uint32_t w = 0; w < waves; ++w) {
+      const uint32_t x = __builtin_amdgcn_readfirstlane(counts[w]);
+      before += w < wave ? x : 0u;
+      all += x;
     }
+    if (wave == 0) {
+      const uint64_t acc = bern_lookback<kLookWidth32>(
+          status, unit, all, ctl, help_polls, [&](uint64_t u) {
+        uint64_t sum = 0;
+        for (uint32_t w = 0; w < waves; ++w) {
+          const uint64_t i = u * waves + w;
+          if (i < n_chunks)
+            sum += bern_count32_wave(make_stream(seed, i, kBChunk, 0), chunk_len(i), c32, lane);
+        }
+        return sum;
+      });
+      if (lane == 0) {
+        excl = acc;
+        if (unit == n_units - 1) {
+          *count_dev = acc + all;
+          ctl->bern_count = acc + all;
+        }
+      }
+    }
+    __syncthreads();
+    const uint64_t first = uniform64(excl) + before;
     // one 256-draw group per step: lane l takes hits k0 + 64s + l (s < 4);
     // qb: position before the group
+    const uint64_t room = first < capacity ? capacity - first : 0;
+    const uint32_t n_out = cnt < room ? cnt : static_cast<uint32_t>(room);
+    uint64_t* const o = out + first;
     uint32_t qrun = 0;  // position before the next recomputed group
-    for (uint32_t k0 = 0; k0 < cnt; k0 += kBernWaveGroup) {
+    for (uint32_t k0 = 0; k0 < n_out; k0 += kBernWaveGroup) {
       const uint32_t c = k0 / kBernWaveGroup;
       uint32_t sbase = k0;  // list index of hit k0
       bool as_rel = false;
@@ -3192,33 +3323,28 @@ __global__ __launch_bounds__(64) void k_bern_wave(uint64_t N, uint64_t seed, uin
         qrun += __builtin_amdgcn_readlane(wave_scan_incl(sum), 63);
         sbase = kSpare;
       }
+      // list indices stay inside the list; what is read past the last hit is
+      // never written
       uint32_t v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = list[sbase + 64u * t + lane];
+      const uint64_t b1 = base + __builtin_amdgcn_readfirstlane(qb);
+      if (as_rel && k0 + kBernWaveGroup <= n_out) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          store_out(o + k0 + 64u * t + lane, out_value<kEdges>(b1, v[t]));
+        continue;
+      }
+      uint32_t before_t = 0;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const uint32_t k = k0 + 64u * t + lane;
-        // list indices stay inside the list; values past the last hit are
-        // dropped here
-        const uint32_t x = list[sbase + 64u * t + lane];
-        v[t] = k < cnt ? x : 0u;
-      }
-      if (as_rel) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const uint32_t k = k0 + 64u * t + lane;
-          if (k < cnt && first + k < capacity)
-            store_out(out + first + k, out_value<kEdges>(base + qb, v[t]));
+        uint32_t x = v[t];
+        if (!as_rel) {
+          x = before_t + wave_scan_incl(k < cnt ? x : 0u);
+          before_t = __builtin_amdgcn_readlane(x, 63);
         }
-      } else {
-        uint32_t incl[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) incl[t] = wave_scan_incl(v[t]);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const uint32_t k = k0 + 64u * t + lane;
-          if (k < cnt && first + k < capacity)
-            store_out(out + first + k, out_value<kEdges>(base + qb, incl[t]));
-          qb += __builtin_amdgcn_readlane(incl[t], 63);
-        }
+        if (k < n_out) store_out(o + k, out_value<kEdges>(b1, x));
       }
     }
   }
@@ -3671,7 +3797,8 @@ int dense_occupancy() {
 int bern_wave_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_bern_wave<false>), 64, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_bern_wave<false>), 64 * kBernWaves,
+          kBernWaves * kBernWaveLds * sizeof(uint32_t)) != hipSuccess ||
       occ <= 0)
     occ = 8;
   return occ;
@@ -3680,8 +3807,8 @@ int bern_wave_occupancy() {
 int bern64_wave_occupancy(uint32_t lds_cap) {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_bern64_wave<false>), 64,
-          static_cast<size_t>(lds_cap) * sizeof(uint32_t)) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_bern64_wave<false>), 64 * kBern64Waves,
+          static_cast<size_t>(kBern64Waves) * lds_cap * sizeof(uint32_t)) != hipSuccess ||
       occ <= 0)
     occ = 1;
   return occ;
@@ -3763,11 +3890,13 @@ hipError_t launch_bernoulli(double p, uint64_t N, uint64_t seed, uint64_t chunk,
   (void)p;
   const uint32_t n_cls = grid < kTicketClasses ? grid : kTicketClasses;
   if (fp32 == kBernFp32Wave)
-    hipLaunchKernelGGL((edges ? k_bern_wave<true> : k_bern_wave<false>), dim3(grid), dim3(64), 0, stream, N, seed, chunk, n_chunks, c32,
+    hipLaunchKernelGGL((edges ? k_bern_wave<true> : k_bern_wave<false>), dim3(grid),
+                       dim3(64 * kBernWaves), kBernWaves * kBernWaveLds * sizeof(uint32_t), stream, N, seed, chunk, n_chunks, c32,
                        status, out, capacity, count_dev, ctl, tickets, n_cls, help_polls);
   else if (fp32 == kBernFp64Wave)
-    hipLaunchKernelGGL((edges ? k_bern64_wave<true> : k_bern64_wave<false>), dim3(grid), dim3(64),
-                       static_cast<size_t>(lds_cap) * sizeof(uint32_t), stream, N, seed, chunk,
+    hipLaunchKernelGGL((edges ? k_bern64_wave<true> : k_bern64_wave<false>), dim3(grid),
+                       dim3(64 * kBern64Waves),
+                       static_cast<size_t>(kBern64Waves) * lds_cap * sizeof(uint32_t), stream, N, seed, chunk,
                        n_chunks, c64, status, out, capacity, count_dev, ctl, lds_cap, tickets,
                        n_cls, help_polls);
   else

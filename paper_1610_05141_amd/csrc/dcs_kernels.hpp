@@ -203,6 +203,10 @@ constexpr int kBernFp64Group = 0, kBernFp32Wave = 1, kBernFp64Wave = 2;
 // Largest LDS position list (32-bit words) for which the one-wave
 // double-precision kernel is chosen.
 constexpr uint32_t kBern64WaveMaxList = 1024;
+// Waves of a work-group of the one-wave-per-chunk kernels: a unit of so many
+// consecutive chunks is handed out and looked back for at once.
+constexpr uint32_t kBern64Waves = 8;
+constexpr uint32_t kBernWaves = 4;
 hipError_t launch_bernoulli(double p, uint64_t N, uint64_t seed, uint64_t chunk,
                             uint64_t n_chunks, int fp32, double c64, float c32,
                             unsigned long long* status, uint64_t* out, uint64_t capacity,
