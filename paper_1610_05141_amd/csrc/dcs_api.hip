@@ -343,8 +343,6 @@ int32_t device_ctx(DeviceCtx** out) {
     c.sort_occupancy = dcs::sort_occupancy();
     c.bern_wave_occupancy = dcs::bern_wave_occupancy();
     c.wb_occupancy = dcs::wb_occupancy();
-    c.small_occupancy = dcs::small_occupancy();
-    c.dense_occupancy = dcs::dense_occupancy();
     if (const char* e = getenv("DCS_LEAF_GRID")) c.leaf_grid = atoll(e);
     if (dcs::error_slots(&c.err_slots) != hipSuccess || c.err_slots == nullptr) return DCS_EHIP;
     if (hipGetSymbolAddress(&c.noalloc_scratch, HIP_SYMBOL(scratch)) != hipSuccess ||
@@ -537,22 +535,19 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
     e = dcs::launch_leaf_once(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, edges);
     timing_end(s, &t13);
   }
+  // the one-wave leaf kernels: a work-group per compute unit
+  const uint32_t wave_wgs = static_cast<uint32_t>(std::max<uint64_t>(
+      1, std::min<uint64_t>(static_cast<uint64_t>(c->leaf_grid > 0 ? c->leaf_grid : c->cus), leaf_cap)));
   Timing t6{};
   if (e == hipSuccess && !(takes & dcs::kTakesDense)) {
-    uint64_t waves = static_cast<uint64_t>(c->cus) * std::max(1, c->dense_occupancy);
-    if (c->leaf_grid > 0) waves = static_cast<uint64_t>(c->leaf_grid) * (dcs::kLeafBlock / 64);
-    waves = std::max<uint64_t>(1, std::min<uint64_t>(waves, leaf_cap));
     timing_begin(6, s, &t6);
-    e = dcs::launch_leaf_dense(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(waves), s, edges);
+    e = dcs::launch_leaf_dense(leaves, leaf_cap, out, ctl, wave_wgs, s, edges);
     timing_end(s, &t6);
   }
   Timing t12{};
   if (e == hipSuccess && !(takes & dcs::kTakesSmall)) {
-    uint64_t waves = static_cast<uint64_t>(c->cus) * std::max(1, c->small_occupancy);
-    if (c->leaf_grid > 0) waves = static_cast<uint64_t>(c->leaf_grid) * (dcs::kLeafBlock / 64);
-    waves = std::max<uint64_t>(1, std::min<uint64_t>(waves, leaf_cap));
     timing_begin(12, s, &t12);
-    e = dcs::launch_leaf_small(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(waves), s, edges);
+    e = dcs::launch_leaf_small(leaves, leaf_cap, out, ctl, wave_wgs, s, edges);
     timing_end(s, &t12);
   }
   // Second round: the tree threads marked in `redo` run again into the

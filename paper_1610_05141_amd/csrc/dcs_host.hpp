@@ -58,9 +58,7 @@ struct DeviceCtx {
   int leaf_occupancy = 2;
   int sort_occupancy = 4;
   int bern_wave_occupancy = 2;
-  int dense_occupancy = 8;
   int wb_occupancy = 8;
-  int small_occupancy = 8;
   // launch-geometry overrides (never change the sample): DCS_LEAF_GRID sets
   // the number of leaf work-groups, DCS_CUT_BIAS shifts the Algorithm P cut;
   // when set they take precedence over the tuning table

@@ -829,8 +829,10 @@ __device__ void leaf_once(const Leaf& L, uint64_t* out, LeafSmem& sm) {
 }
 
 // ---------------------------------------------------------------------------
-// Sparse and with-replacement leaves: one work-group per leaf, sorted by the
-// leading bits of the raw stream words.
+// Sparse and with-replacement leaves: one work-group (k_leaf_sort) or one
+// wave (k_leaf_small) per leaf, sorted by the leading bits of the raw stream
+// words.  Figures below are k_leaf_sort's; k_leaf_small has 2^11 buckets for
+// its at most 1024 keys.
 //
 // The map from a 32-bit word to its value in [0, N_v) is monotone, so a leaf
 // sorts its words and maps them as they are written out; words are uniform
@@ -854,11 +856,7 @@ __device__ void leaf_once(const Leaf& L, uint64_t* out, LeafSmem& sm) {
 //
 // What bounds it: see k_leaf_sort.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kSortBucketBits = 13;
-constexpr uint32_t kSortCnt = (1u << kSortBucketBits) / 8;  // counter words
-constexpr uint32_t kSortPre = 8;                            // words before position 0
-constexpr uint32_t kSortKeys = kSortPre + kMaxN0 + 152;     // then keys, sentinels
-constexpr uint32_t kSortSpare = kMaxN0 + 15 + 128;          // key slot that nothing reads
+constexpr uint32_t kSortPre = 8;  // words before position 0
 constexpr uint32_t kSortCacheLeaves = 16;
 constexpr uint32_t kSortCache = kSortCacheLeaves * kLeafWords;
 constexpr uint32_t kMaxFix = 32;                            // repeats repaired in place
@@ -870,25 +868,68 @@ constexpr uint32_t kCand = 8;                               // candidates per re
 constexpr uint32_t kSsClass = 16, kSsDups = 17, kSsNext = 18, kSsDead = 19, kSsKeep = 20, kSsAny = 21,
                    kSsDupPos = 32, kSsNew = 64, kSsCand = 96, kSsWords = 112;
 constexpr uint32_t kOnes4 = 0x11111111u, kFours4 = 0x44444444u;
-constexpr uint32_t kSmemSort = kSortKeys + 2 * kSortCnt + kSortCache + kSsWords;
+
+// Back-list leaves (ranges that are no powers of two) of at most so many
+// values are k_leaf_small's.
+constexpr uint32_t kSmallMax = 1024;
+
+// The sort's sizes: threads per leaf, buckets, the largest leaf.
+template <int kThreads, uint32_t kBits, uint32_t kLargest>
+struct SortDims {
+  static constexpr int B = kThreads;
+  static constexpr uint32_t kMax = kLargest;
+  static constexpr uint32_t kCnt = (1u << kBits) / 8;           // counter words
+  static constexpr uint32_t kKeyWords = kSortPre + kMax + 152;  // keys, then sentinels
+  static constexpr uint32_t kSpare = kMax + 15 + 128;           // key slot that nothing reads
+  static constexpr uint32_t kWordShift = 32 - (kBits - 3);
+  static constexpr uint32_t kSmem = kKeyWords + 2 * kCnt + kSsWords;
+  static_assert(kSpare + kSortPre < kKeyWords, "the spare slot lies behind the sentinels");
+};
+using SortGroup = SortDims<kSortBlock, 13, kMaxN0>;  // k_leaf_sort: a work-group per leaf
+using SortWave = SortDims<64, 11, kSmallMax>;        // k_leaf_small: a wave per leaf
+
+// A leaf's threads, their barrier and their scan: a wave of a larger
+// work-group needs no barrier (its LDS accesses complete in order), only that
+// the compiler keeps that order.
+template <int B>
+__device__ __forceinline__ uint32_t sort_tid() {
+  return B == 64 ? lane_tid() & 63u : lane_tid();
+}
+template <int B>
+__device__ __forceinline__ void sort_sync() {
+  if (B == 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+    __syncthreads();
+  }
+}
+template <int B, bool kTail = true>
+__device__ __forceinline__ uint32_t sort_scan(uint32_t x, uint32_t* scratch, uint32_t* total) {
+  if constexpr (B == 64) {
+    const uint32_t incl = wave_scan_incl(x);
+    *total = __builtin_amdgcn_readlane(incl, 63);
+    return incl - x;
+  } else {
+    return block_scan_excl<B, uint32_t, kTail>(x, scratch, total);
+  }
+}
 
 struct SortSmem {
   uint32_t* keys;  // position 0 (kSortPre words before it)
-  uint32_t* cnt;   // kSortCnt counter words, zero between leaves, then as many prefixes
+  uint32_t* cnt;   // kCnt counter words, zero between leaves, then as many prefixes
   uint32_t* scr;   // kSsWords
 };
 
+template <class D>
 __device__ __forceinline__ SortSmem sort_smem(uint32_t* smem) {
   SortSmem sm;
   sm.cnt = smem;  // first: counter and prefix are one two-offset LDS read
-  sm.keys = smem + 2 * kSortCnt + kSortPre;
-  sm.scr = smem + 2 * kSortCnt + kSortKeys + kSortCache;
+  sm.keys = smem + 2 * D::kCnt + kSortPre;
+  sm.scr = smem + 2 * D::kCnt + D::kKeyWords;
   return sm;
 }
-__device__ __forceinline__ uint32_t* sort_cache(uint32_t* smem) {
-  return smem + 2 * kSortCnt + kSortKeys;
-}
-
 // The map from words to values and the void test of a range in [1, 2^32].
 struct WordMap {
   uint32_t s;       // range (2^32 as 0)
@@ -915,9 +956,9 @@ __device__ __forceinline__ uint32_t word_value(const WordMap& m, uint32_t w) {
 }
 
 // The shift of a key's bucket in its counter word.
-constexpr uint32_t kSortWordShift = 32 - (kSortBucketBits - 3);
+template <class D>
 __device__ __forceinline__ uint32_t sort_shift(uint32_t w) {
-  return (w >> (kSortWordShift - 5)) & 28u;
+  return (w >> (D::kWordShift - 5)) & 28u;
 }
 
 // Neighbouring lanes' values: lane i - 1's (0 in lane 0), lane i + 1's
@@ -972,7 +1013,7 @@ __device__ __forceinline__ void row_words(const SortSmem& sm, uint32_t r0, uint3
 template <int B, int R, bool kPow2, bool kEdges>
 __device__ __forceinline__ bool write_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
                                            const WordMap& m, const SortSmem& sm) {
-  const uint32_t tid = lane_tid();
+  const uint32_t tid = sort_tid<B>();
   const uint32_t lane = tid & 63u;
   const bool inner = lane - kHalo < 64u - 2 * kHalo;
   uint64_t dup = 0;
@@ -1014,7 +1055,7 @@ __device__ __forceinline__ bool write_rows_of(uint32_t cls, uint64_t* o, uint64_
 // is appended to the scratch (the first kMaxFix of them) and counted.
 template <int B>
 __device__ void find_repeats(uint32_t s0, uint32_t nn, const WordMap& m, const SortSmem& sm) {
-  const uint32_t tid = lane_tid();
+  const uint32_t tid = sort_tid<B>();
   const uint32_t lane = tid & 63u;
   const bool inner = lane - kHalo < 64u - 2 * kHalo;
   for (uint32_t r0 = kRow * __builtin_amdgcn_readfirstlane(tid >> 6); r0 < nn;
@@ -1043,7 +1084,7 @@ __device__ void find_repeats(uint32_t s0, uint32_t nn, const WordMap& m, const S
 template <int B, bool kEdges>
 __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn, const WordMap& m,
                              const SortSmem& sm, uint32_t D) {
-  const uint32_t tid = lane_tid();
+  const uint32_t tid = sort_tid<B>();
   const uint32_t lane = tid & 63u;
   const bool inner = lane - kHalo < 64u - 2 * kHalo;
   for (uint32_t r0 = kRow * __builtin_amdgcn_readfirstlane(tid >> 6); r0 < nn;
@@ -1085,10 +1126,11 @@ __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
 // dst[0 .. need) = the first `need` non-void words of the stream from word t
 // on; returns the word index just after the last one (ends with a barrier).
 // dst may not overlap scr.
-template <int B>
+template <class D>
 __device__ uint32_t draw_words(const Stream& st, uint32_t t, uint32_t need, const WordMap& m,
                                uint32_t* dst, uint32_t* scr) {
-  constexpr int kBlk = kKeys / (4 * B);
+  constexpr int B = D::B;
+  constexpr int kBlk = D::kMax / (4 * B);
   // words per non-void word
   const float over = 4294967296.0f / (4294967296.0f - static_cast<float>(m.thr));
   uint32_t done = 0;
@@ -1102,7 +1144,7 @@ __device__ uint32_t draw_words(const Stream& st, uint32_t t, uint32_t need, cons
     const uint32_t first = t >> 2;
     const uint32_t blocks = min(((t + (need - done) + extra + 3u) >> 2) - first, kBlk * static_cast<uint32_t>(B));
     const uint32_t per = (blocks + B - 1) / B;
-    const uint32_t tid = lane_tid();
+    const uint32_t tid = sort_tid<B>();
     uint32_t w[4 * kBlk];
     uint32_t ok = 0;
 #pragma unroll
@@ -1118,7 +1160,7 @@ __device__ uint32_t draw_words(const Stream& st, uint32_t t, uint32_t need, cons
       }
     }
     uint32_t total;
-    uint32_t p = done + block_scan_excl<B, uint32_t>(static_cast<uint32_t>(__popc(ok)), scr, &total);
+    uint32_t p = done + sort_scan<B>(static_cast<uint32_t>(__popc(ok)), scr, &total);
 #pragma unroll
     for (int q = 0; q < 4 * kBlk; ++q) {
       if ((ok >> q) & 1u) {
@@ -1129,28 +1171,30 @@ __device__ uint32_t draw_words(const Stream& st, uint32_t t, uint32_t need, cons
     }
     done += total;
     t = 4 * (first + blocks);
-    __syncthreads();
+    sort_sync<B>();
   }
   const uint32_t next = scr[kSsNext];
-  __syncthreads();
+  sort_sync<B>();
   return next;
 }
 
 // Sparse and with-replacement leaves in full generality: keys[0..n) hold the
 // leaf's first n words (any order), word t is the stream's next; sorted by a
-// bitonic network over 4096 keys (the unused ones 2^32 - 1, which sort last),
+// bitonic network over kMax keys (the unused ones 2^32 - 1, which sort last),
 // repeats dropped and drawn again until there is none.  For leaves with a
 // bucket of more than 8 keys or more than kMaxFix repeats.
-template <int B, bool kEdges>
+template <class D, bool kEdges>
 __device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint32_t n,
                                                        const WordMap& m, bool wr, SortSmem& sm,
                                                        uint64_t* out, uint64_t b1) {
+  constexpr int B = D::B;
+  constexpr uint32_t kKeys = D::kMax;
   uint32_t* keys = sm.keys;
   constexpr int R = kKeys / B;
   for (;;) {
-    const uint32_t tid = lane_tid();
+    const uint32_t tid = sort_tid<B>();
     for (uint32_t i = n + tid; i < kKeys; i += B) keys[i] = 0xFFFFFFFFu;
-    __syncthreads();
+    sort_sync<B>();
     for (uint32_t k = 2; k <= kKeys; k <<= 1) {
       for (uint32_t j = k >> 1; j > 0; j >>= 1) {
         for (uint32_t q = tid; q < kKeys / 2; q += B) {
@@ -1161,7 +1205,7 @@ __device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint3
             keys[hi] = x;
           }
         }
-        __syncthreads();
+        sort_sync<B>();
       }
     }
     if (wr) break;
@@ -1173,15 +1217,15 @@ __device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint3
       if (i < n && (i == 0 || word_value(m, keys[i - 1]) != word_value(m, w[q]))) keep |= 1u << q;
     }
     uint32_t have;
-    uint32_t p = block_scan_excl<B, uint32_t>(static_cast<uint32_t>(__popc(keep)), sm.scr, &have);
+    uint32_t p = sort_scan<B>(static_cast<uint32_t>(__popc(keep)), sm.scr, &have);
     if (have == n) break;
 #pragma unroll
     for (int q = 0; q < R; ++q)
       if ((keep >> q) & 1u) keys[p++] = w[q];
-    t = draw_words<B>(st, t, n - have, m, keys + have, sm.scr);
+    t = draw_words<D>(st, t, n - have, m, keys + have, sm.scr);
   }
-  for (uint32_t i = lane_tid(); i < n; i += B) store_out(out + i, out_value<kEdges>(b1, word_value(m, keys[i])));
-  __syncthreads();
+  for (uint32_t i = sort_tid<B>(); i < n; i += B) store_out(out + i, out_value<kEdges>(b1, word_value(m, keys[i])));
+  sort_sync<B>();
 }
 
 // D <= kMaxFix repeats found by the row pass: the stream's next D new values
@@ -1191,7 +1235,7 @@ template <int B>
 __device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t s0, uint32_t nn,
                              const WordMap& m, SortSmem& sm) {
   uint32_t* scr = sm.scr;
-  const uint32_t tid = lane_tid();
+  const uint32_t tid = sort_tid<B>();
   uint32_t have = 0;
   while (have < D) {
     if (tid < 64) {
@@ -1213,7 +1257,7 @@ __device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t 
       if (tid < kCand) scr[kSsCand + tid] = v;
       if (tid == 0) scr[kSsDead] = static_cast<uint32_t>(dm) & ((1u << kCand) - 1u);
     }
-    __syncthreads();
+    sort_sync<B>();
     uint32_t c[kCand], hit = 0;
 #pragma unroll
     for (uint32_t i = 0; i < kCand; ++i) c[i] = scr[kSsCand + i];
@@ -1223,7 +1267,7 @@ __device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t 
       for (uint32_t j = 0; j < kCand; ++j) hit |= c[j] == v ? 1u << j : 0u;
     }
     if (hit != 0) atomicOr(&scr[kSsDead], hit);
-    __syncthreads();
+    sort_sync<B>();
     const uint32_t fresh = ~scr[kSsDead] & ((1u << kCand) - 1u);
     if (tid < kCand && ((fresh >> tid) & 1u)) {
       const uint32_t i = have + static_cast<uint32_t>(__popc(fresh & ((1u << tid) - 1u)));
@@ -1231,16 +1275,16 @@ __device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t 
     }
     have += static_cast<uint32_t>(__popc(fresh));
     t += kCand;
-    __syncthreads();
+    sort_sync<B>();
   }
   uint32_t x = 0, rank = 0;
   if (tid < D) {
     x = scr[kSsNew + tid];
     for (uint32_t i = 0; i < D; ++i) rank += scr[kSsNew + i] < x ? 1u : 0u;
   }
-  __syncthreads();
+  sort_sync<B>();
   if (tid < D) scr[kSsNew + rank] = x;
-  __syncthreads();
+  sort_sync<B>();
 }
 
 // What a key keeps from the counting pass to the scatter (recomputing it
@@ -1259,13 +1303,13 @@ __device__ __forceinline__ uint32_t* sort_word(const SortSmem& sm, const KeyPlac
 // Four keys of a thread, positions i .. i + 3 of the leaf's words, counted
 // into their buckets; returns the largest slot.  kPart: positions from nv on
 // take no part.
-template <bool kPart>
+template <class D, bool kPart>
 __device__ __forceinline__ uint32_t count_keys(const uint32_t* key, KeyPlace* at, uint32_t i,
                                                uint32_t nv, const SortSmem& sm) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    at[j].word = (key[j] >> (kSortWordShift - 2)) & (4 * kSortCnt - 4);
-    at[j].shift = sort_shift(key[j]);
+    at[j].word = (key[j] >> (D::kWordShift - 2)) & (4 * D::kCnt - 4);
+    at[j].shift = sort_shift<D>(key[j]);
     asm volatile("" : "+v"(at[j].word), "+v"(at[j].shift));  // kept, not recomputed
     uint32_t one = 1u << at[j].shift;
     if (kPart && i + j >= nv) one = 0;
@@ -1283,20 +1327,20 @@ __device__ __forceinline__ uint32_t count_keys(const uint32_t* key, KeyPlace* at
 
 // The same keys to their places: the prefix of the counter word, the counts
 // of the word's lower buckets and the slot, all in bytes.
-template <bool kPart>
+template <class D, bool kPart>
 __device__ __forceinline__ void scatter_keys(const uint32_t* key, const KeyPlace* at, uint32_t i,
                                              uint32_t nv, const SortSmem& sm) {
   uint32_t c[4], e[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     c[j] = sort_word(sm, at[j])[0];
-    e[j] = sort_word(sm, at[j])[kSortCnt];
+    e[j] = sort_word(sm, at[j])[D::kCnt];
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const uint32_t below = __builtin_amdgcn_ubfe(c[j], 0, at[j].shift);
     uint32_t bytes = e[j] + 4 * __builtin_amdgcn_udot8(below, kOnes4, at[j].slot, false);
-    if (kPart && i + j >= nv) bytes = 4 * kSortSpare;
+    if (kPart && i + j >= nv) bytes = 4 * D::kSpare;
     *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(sm.keys) + bytes) = key[j];
   }
 }
@@ -1491,7 +1535,7 @@ __device__ __forceinline__ void put_chunk(uint16_t* dst, const uint32_t q[4]) {
 template <bool kEdges>
 __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, uint16_t* list, uint32_t* mask,
                                 uint32_t* bases) {
-  const uint32_t lane = lane_tid();
+  const uint32_t lane = lane_tid() & 63u;
   const uint32_t nv = L.nv;
   const uint32_t Nv = static_cast<uint32_t>(L.Nv);
   const uint32_t n0 = L.flags >> 8;
@@ -1620,25 +1664,6 @@ __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, ui
 // ---------------------------------------------------------------------------
 // Small sparse and with-replacement leaves, one wave per leaf.
 // ---------------------------------------------------------------------------
-// Sparse and with-replacement leaves of the back list (ranges that are not
-// powers of two) with at most kSmallMax values are taken by k_leaf_small,
-// one wave each with no barrier: the same values as leaf_sorted
-// (the first n_v non-void values of the leaf's stream, for a sparse leaf
-// Algorithm H's distinct ones by rounds), ranked in stream order by wave
-// scans, sorted by a counting pass over kSmallBuckets buckets and the
-// Batcher windows, and written with consecutive lanes on consecutive
-// outputs.  The work-group leaf loop skips them.
-constexpr uint32_t kSmallKpl = 16;                     // keys per lane
-constexpr uint32_t kSmallMax = 64 * kSmallKpl;         // 1024 values
-constexpr uint32_t kSmallBucketBits = 10;
-constexpr uint32_t kSmallBuckets = 1u << kSmallBucketBits;
-static_assert(kSmallBuckets == kSmallMax, "one bucket per key slot");
-// counter of bucket b at spad(b): one pad word per 16, so that lane l's
-// run of 16 counters (words 17 l .. 17 l + 15) spans 16 distinct banks
-__device__ __forceinline__ uint32_t spad(uint32_t b) { return b + (b >> 4); }
-constexpr uint32_t kSmallCnt = kSmallBuckets + kSmallBuckets / 16;
-constexpr uint32_t kSmallKeys = kSmallMax + 32;        // keys, then sentinels
-
 __device__ __forceinline__ bool small_by_wave(const Leaf& L) {
   const uint32_t kind = L.flags & 3u;
   return (kind == kKindSparse || kind == kKindWr) && L.nv <= kSmallMax;
@@ -1650,198 +1675,6 @@ __device__ __forceinline__ bool small_by_wave(const Leaf& L) {
 __device__ __forceinline__ bool once_by_group(const Leaf& L) {
   return (L.flags & 3u) == kKindSparse && L.nv > kSmallMax &&
          static_cast<uint64_t>(L.nv) * L.nv >= 2 * L.Nv;
-}
-
-// The first `need` non-void values in [0, s) of the 32-bit stream from word
-// t0 on, in stream order, into dst[0..need), by one wave: lane l maps the
-// words of Philox block (t >> 2) + l, a wave scan ranks the non-void ones.
-// Returns the word index just after the last value taken.
-__device__ uint64_t take_wave(const Stream& st, uint64_t t0, uint32_t need, const RangeInfo& ri,
-                              uint32_t* dst, uint32_t lane) {
-  uint32_t done = 0;
-  uint64_t t = t0, after = t0;
-  while (done < need) {
-    const uint64_t blk = (t >> 2) + lane;
-    const uint4 w = philox_block(st, static_cast<uint32_t>(blk));
-    uint32_t v[4], ok = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bool good = true;
-      if (ri.pow2)
-        v[j] = ri.pshift >= 32 ? 0u : (pick(w, j) >> ri.pshift);
-      else
-        good = range_map(pick(w, j), ri.s, ri.thr, &v[j]);
-      if (good && 4 * blk + j >= t) ok |= 1u << j;
-    }
-    const uint32_t c = static_cast<uint32_t>(__popc(ok));
-    const uint32_t incl = wave_scan_incl(c);
-    uint32_t p = done + incl - c;
-    bool has_last = false;
-    uint64_t last = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if ((ok >> j) & 1u) {
-        if (p < need) dst[p] = v[j];
-        if (p == need - 1) {
-          has_last = true;
-          last = 4 * blk + j + 1;
-        }
-        ++p;
-      }
-    }
-    const unsigned long long m = __ballot(has_last);
-    if (m != 0) {
-      const uint32_t f = static_cast<uint32_t>(__ffsll(static_cast<long long>(m)) - 1);
-      after = static_cast<uint64_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(last), f)) |
-              (static_cast<uint64_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(last >> 32), f))
-               << 32);
-    }
-    done += __builtin_amdgcn_readlane(incl, 63);
-    t = ((t >> 2) + 64) << 2;
-  }
-  return after;
-}
-
-// W-key windows at off + W i of keys[0..n) (sentinels follow n); merge: each
-// window's halves are already sorted.  True iff some window holds equal
-// neighbours below n.
-template <int W, bool kMerge>
-__device__ __forceinline__ bool wave_windows(uint32_t* keys, uint32_t n, uint32_t off,
-                                             uint32_t lane) {
-  bool dup = false;
-  for (uint32_t w0 = off + W * lane; w0 < n; w0 += 64 * W) {
-    uint4* p = reinterpret_cast<uint4*>(keys + w0);
-    uint32_t v[W];
-#pragma unroll
-    for (int q = 0; q < W / 4; ++q) {
-      const uint4 x = p[q];
-      v[4 * q] = x.x;
-      v[4 * q + 1] = x.y;
-      v[4 * q + 2] = x.z;
-      v[4 * q + 3] = x.w;
-    }
-    sort_net<W, kMerge>(v);
-#pragma unroll
-    for (int q = 0; q < W / 4; ++q)
-      p[q] = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    const uint32_t lim = n - w0;
-#pragma unroll
-    for (int i = 0; i + 1 < W; ++i)
-      dup = dup || (v[i] == v[i + 1] && static_cast<uint32_t>(i + 1) < lim);
-  }
-  return __ballot(dup) != 0;
-}
-
-// keys[0..n) ascending by one wave (n <= kSmallMax, keys >> shift below
-// kSmallBuckets); returns true iff a value repeats.  Counting pass by
-// key >> shift (LDS atomics give each key its slot in its bucket), scan of
-// the counts (lane l owns buckets 16 l .. 16 l + 15), scatter back into
-// keys, then the Batcher windows of the work-group sort (8-key windows and
-// merge windows shifted by 4 when no bucket holds more than 5 keys, 16-key
-// ones up to 9), else odd-even transposition rounds.
-__device__ bool wave_sort(uint32_t* keys, uint32_t n, uint32_t shift, uint32_t* cnt,
-                          uint32_t lane) {
-  for (uint32_t w = lane; w < kSmallCnt / 4; w += 64)
-    reinterpret_cast<uint4*>(cnt)[w] = make_uint4(0, 0, 0, 0);
-  uint32_t kk[kSmallKpl], as[kSmallKpl];
-#pragma unroll
-  for (uint32_t q = 0; q < kSmallKpl; ++q) {
-    const uint32_t i = 64 * q + lane;
-    kk[q] = 0;
-    as[q] = ~0u;
-    if (i < n) {
-      kk[q] = keys[i];
-      const uint32_t b = spad(kk[q] >> shift);
-      as[q] = b | (atomicAdd(&cnt[b], 1u) << 16);
-    }
-  }
-  {
-    uint32_t* run = cnt + spad(kSmallKpl * lane);
-    uint32_t c[kSmallKpl];
-    uint32_t sum = 0, big = 0;
-#pragma unroll
-    for (uint32_t m = 0; m < kSmallKpl; ++m) {
-      c[m] = run[m];
-      sum += c[m];
-      big = max(big, c[m]);
-    }
-    const uint32_t incl = wave_scan_incl(sum);
-    uint32_t acc = incl - sum;
-#pragma unroll
-    for (uint32_t m = 0; m < kSmallKpl; ++m) {
-      run[m] = acc;
-      acc += c[m];
-    }
-    big = __builtin_amdgcn_readlane(wave_max_incl(big), 63);
-    if (lane < 24) keys[n + lane] = 0xFFFFFFFFu;
-#pragma unroll
-    for (uint32_t q = 0; q < kSmallKpl; ++q)
-      if (as[q] != ~0u) keys[cnt[as[q] & 0xFFFFu] + (as[q] >> 16)] = kk[q];
-    if (shift == 0 || big <= 1) return shift == 0 && big >= 2;
-    if (big <= 5) {
-      const bool d = wave_windows<8, false>(keys, n, 0, lane);
-      return wave_windows<8, true>(keys, n, 4, lane) || d;
-    }
-    if (big <= 9) {
-      const bool d = wave_windows<16, false>(keys, n, 0, lane);
-      return wave_windows<16, true>(keys, n, 8, lane) || d;
-    }
-    for (uint32_t r = 0; r < big; ++r) {
-      for (uint32_t i = 2 * lane + (r & 1u); i + 1 < n; i += 128) {
-        const uint32_t a = keys[i], b = keys[i + 1];
-        keys[i] = min(a, b);
-        keys[i + 1] = max(a, b);
-      }
-    }
-  }
-  bool dup = false;
-  for (uint32_t i = lane; i + 1 < n; i += 64) dup = dup || keys[i] == keys[i + 1];
-  return __ballot(dup) != 0;
-}
-
-// keys[0..n) ascending with equal values adjacent -> the distinct values in
-// keys[0..d); returns d (one wave; every key is read before any is moved).
-__device__ uint32_t compact_wave(uint32_t* keys, uint32_t n, uint32_t lane) {
-  uint32_t kk[kSmallKpl];
-  uint32_t keep = 0;
-#pragma unroll
-  for (uint32_t q = 0; q < kSmallKpl; ++q) {
-    const uint32_t i = 64 * q + lane;
-    kk[q] = 0;
-    if (i < n) {
-      kk[q] = keys[i];
-      if (i == 0 || keys[i - 1] != kk[q]) keep |= 1u << q;
-    }
-  }
-  uint32_t d = 0;
-#pragma unroll
-  for (uint32_t q = 0; q < kSmallKpl; ++q) {
-    const unsigned long long m = __ballot((keep >> q) & 1u);
-    if ((keep >> q) & 1u) keys[d + lane_rank(m)] = kk[q];
-    d += static_cast<uint32_t>(__popcll(m));
-  }
-  return d;
-}
-
-template <bool kEdges>
-__device__ void leaf_small_wave(const Leaf& L, uint64_t* out, uint32_t* keys, uint32_t* cnt) {
-  const uint32_t lane = lane_tid();
-  const uint32_t nv = L.nv;
-  const bool wr = (L.flags & 3u) == kKindWr;
-  const RangeInfo ri = range_info(L.Nv);
-  const uint32_t kb = bit_length(L.Nv - 1);
-  const uint32_t shift = kb > kSmallBucketBits ? kb - kSmallBucketBits : 0u;
-  const Stream st = make_stream(L.seed, L.id, wr ? kWrLeaf : kLeaf, 0);
-  uint64_t t = take_wave(st, 0, nv, ri, keys, lane);
-  bool dups = wave_sort(keys, nv, shift, cnt, lane);
-  while (dups && !wr) {  // Algorithm H's rounds (sparse leaves only)
-    const uint32_t have = compact_wave(keys, nv, lane);
-    t = take_wave(st, t, nv - have, ri, keys + have, lane);
-    dups = wave_sort(keys, nv, shift, cnt, lane);
-  }
-  const uint64_t b1 = L.lo + 1;
-  uint64_t* o = out + L.off;
-  for (uint32_t i = lane; i < nv; i += 64) store_out(o + i, out_value<kEdges>(b1, keys[i]));
 }
 
 template <int B>
@@ -1895,60 +1728,62 @@ __device__ __forceinline__ uint32_t* lds_uniform(lds_u32* p) {
 // repeats; kRareGeneral: a bucket of more than 8 keys (the leaf's words lie
 // in stream order from position 0); otherwise a constant or dense leaf.
 constexpr uint32_t kRareRepeats = 0, kRareGeneral = 1, kRareOther = 2;
-template <int B, bool kEdges>
+template <class D, bool kEdges>
 __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* out_any,
                                                     uint32_t t_any, uint32_t what_any) {
+  constexpr int B = D::B;
   uint32_t* const smem = lds_uniform(lds);
   const Leaf L = cached_leaf(lds_uniform(rec));
   uint64_t* const out =
       reinterpret_cast<uint64_t*>(uniform64(reinterpret_cast<uint64_t>(out_any)));
   const uint32_t t = __builtin_amdgcn_readfirstlane(t_any);
   const uint32_t what = __builtin_amdgcn_readfirstlane(what_any);
-  SortSmem sm = sort_smem(smem);
-  if (what == kRareOther) {
+  SortSmem sm = sort_smem<D>(smem);
+  if (B > 64 && what == kRareOther) {
     // k_leaf_dense's arrays, over the keys
     uint16_t* const list = reinterpret_cast<uint16_t*>(sm.keys);
     uint32_t* const mask = sm.keys + kWaveList / 2;
     if ((L.flags & 3u) == kKindFill)
       leaf_fill<B>(L, out);
-    else if (threadIdx.x < 64)
+    else if (sort_tid<B>() < 64)
       leaf_dense_wave<kEdges>(L, out, list, mask, mask + kWaveMaskWords);
-    __syncthreads();
+    sort_sync<B>();
     return;
   }
   const SortLeaf v = sort_leaf(L, out);
   if (what == kRareRepeats) {
     find_repeats<B>(v.s0, v.nn, v.m, sm);
-    __syncthreads();
-    const uint32_t D = __builtin_amdgcn_readfirstlane(sm.scr[kSsDups]);
-    if (D <= kMaxFix) {
-      draw_missing<B>(v.st, t, D, v.s0, v.nn, v.m, sm);
-      rewrite_rows<B, kEdges>(v.o, v.b1, v.s0, v.nn, v.m, sm, D);
-      __syncthreads();
+    sort_sync<B>();
+    const uint32_t reps = __builtin_amdgcn_readfirstlane(sm.scr[kSsDups]);
+    if (reps <= kMaxFix) {
+      draw_missing<B>(v.st, t, reps, v.s0, v.nn, v.m, sm);
+      rewrite_rows<B, kEdges>(v.o, v.b1, v.s0, v.nn, v.m, sm, reps);
+      sort_sync<B>();
       return;
     }
-    constexpr int R = kKeys / B;
+    constexpr int R = D::kMax / B;
     uint32_t w[R];
 #pragma unroll
-    for (int q = 0; q < R; ++q) w[q] = sm.keys[v.s0 + threadIdx.x + q * B];
-    __syncthreads();
+    for (int q = 0; q < R; ++q) w[q] = sm.keys[v.s0 + sort_tid<B>() + q * B];
+    sort_sync<B>();
 #pragma unroll
     for (int q = 0; q < R; ++q)
-      if (threadIdx.x + q * B < v.nv) sm.keys[threadIdx.x + q * B] = w[q];
+      if (sort_tid<B>() + q * B < v.nv) sm.keys[sort_tid<B>() + q * B] = w[q];
   }
-  leaf_general<B, kEdges>(v.st, t, v.nv, v.m, v.wr, sm, v.o + v.s0, v.b1);
+  leaf_general<D, kEdges>(v.st, t, v.nv, v.m, v.wr, sm, v.o + v.s0, v.b1);
 }
 
 // One sparse or with-replacement leaf (see above).  The counters are zero on
 // entry and on return; ends with a barrier.
-template <int B, bool kEdges>
+template <class D, bool kEdges>
 __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec, uint64_t* out) {
-  constexpr int kBlk = kKeys / (4 * B);
+  constexpr int B = D::B;
+  constexpr int kBlk = D::kMax / (4 * B);
   constexpr int kQ = 4 * kBlk;
-  constexpr int kParts = kSortCnt / (4 * B);  // counter words per thread: 4 kParts
+  constexpr int kParts = D::kCnt / (4 * B);  // counter words per thread: 4 kParts
   static_assert(kParts == 1 || kParts == 2, "two 16-bit sums share one scanned word");
-  const uint32_t tid = lane_tid();
-  SortSmem sm = sort_smem(smem);
+  const uint32_t tid = sort_tid<B>();
+  SortSmem sm = sort_smem<D>(smem);
   const SortLeaf v = sort_leaf(cached_leaf(rec), out);
   const uint32_t nv = v.nv, s0 = v.s0, nn = v.nn;
   const WordMap& m = v.m;
@@ -1960,7 +1795,7 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
   const uint32_t wave_first = __builtin_amdgcn_readfirstlane(tid & ~63u);
   uint32_t key[kQ];
   uint32_t t_next = nv;
-  if (m.thr != 0) t_next = draw_words<B>(st, 0, nv, m, keys, sm.scr);
+  if (m.thr != 0) t_next = draw_words<D>(st, 0, nv, m, keys, sm.scr);
 #pragma unroll
   for (int k = 0; k < kBlk; ++k) {
     if (4 * (wave_first + k * B) < nv) {
@@ -1983,9 +1818,9 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
   for (int k = 0; k < kBlk; ++k) {
     const uint32_t first = 4 * (wave_first + k * B);
     if (first + 256 <= nv)
-      top = max(top, count_keys<false>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm));
+      top = max(top, count_keys<D, false>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm));
     else if (first < nv)
-      top = max(top, count_keys<true>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm));
+      top = max(top, count_keys<D, true>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm));
   }
   // the leaf's class: buckets of more than 4, 6 and 8 keys
   {
@@ -1996,7 +1831,7 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
       if ((tid & 63u) == 0) atomicOr(&sm.scr[kSsClass], 1u | (six ? 2u : 0u) | (eight ? 4u : 0u));
     }
   }
-  __syncthreads();
+  sort_sync<B>();
   // 2. scan
   {
     const uint4* c4 = reinterpret_cast<const uint4*>(sm.cnt);
@@ -2012,7 +1847,7 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
     }
     const uint32_t packed = kParts == 2 ? sum[0] | (sum[kParts - 1] << 16) : sum[0];
     uint32_t total;
-    const uint32_t excl = block_scan_excl<B, uint32_t, false>(packed, sm.scr, &total);
+    const uint32_t excl = sort_scan<B, false>(packed, sm.scr, &total);
 #pragma unroll
     for (int h = 0; h < kParts; ++h) {
       const uint32_t e0 =
@@ -2022,13 +1857,15 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
       const uint32_t e1 = __builtin_amdgcn_udot8(c[h].x, kFours4, e0, false);
       const uint32_t e2 = __builtin_amdgcn_udot8(c[h].y, kFours4, e1, false);
       const uint32_t e3 = __builtin_amdgcn_udot8(c[h].z, kFours4, e2, false);
-      reinterpret_cast<uint4*>(sm.cnt + kSortCnt)[tid + h * B] = make_uint4(e0, e1, e2, e3);
+      reinterpret_cast<uint4*>(sm.cnt + D::kCnt)[tid + h * B] = make_uint4(e0, e1, e2, e3);
     }
   }
   const uint32_t cls = __builtin_amdgcn_readfirstlane(sm.scr[kSsClass]);
-  __syncthreads();
+  sort_sync<B>();
   // 3. scatter, sentinels around the keys
-  if (tid < 128) keys[nn + tid] = 0xFFFFFFFFu;
+#pragma unroll
+  for (uint32_t i = 0; i < 128; i += min(B, 128))
+    if (B <= 128 || tid < 128) keys[nn + tid + i] = 0xFFFFFFFFu;
   if (tid < s0) keys[tid] = 0;
   if (tid == 0) {
     sm.scr[kSsDups] = 0;
@@ -2039,13 +1876,13 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
     for (int k = 0; k < kBlk; ++k) {
       const uint32_t first = 4 * (wave_first + k * B);
       if (first + 256 <= nv)
-        scatter_keys<false>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm);
+        scatter_keys<D, false>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm);
       else if (first < nv)
-        scatter_keys<true>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm);
+        scatter_keys<D, true>(&key[4 * k], &at[4 * k], 4 * (tid + k * B), nv, sm);
     }
   } else {
     // a bucket of more than 8 keys: the words in stream order
-    __syncthreads();
+    sort_sync<B>();
 #pragma unroll
     for (int q = 0; q < kQ; ++q) {
       const uint32_t i = 4 * (tid + (q >> 2) * B) + (q & 3);
@@ -2053,7 +1890,7 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
     }
   }
   __builtin_amdgcn_s_setprio(0);
-  __syncthreads();
+  sort_sync<B>();
   // 4. rows; the counters are zeroed for the next leaf (from a register set
   // here: four kept zeros would be spilled and reloaded behind the stores)
   uint32_t zero = 0;
@@ -2067,11 +1904,11 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
     const bool rep = m.pow2 ? write_rows_of<B, true, kEdges>(cls, v.o, v.b1, s0, nn, m, sm)
                             : write_rows_of<B, false, kEdges>(cls, v.o, v.b1, s0, nn, m, sm);
     if (rep && !v.wr) sm.scr[kSsAny] = 1;
-    __syncthreads();
+    sort_sync<B>();
     if (__builtin_amdgcn_readfirstlane(sm.scr[kSsAny]) == 0) return;
     what = kRareRepeats;
   }
-  leaf_rare<B, kEdges>(lds_address(smem), lds_address(rec), out, t_next, what);
+  leaf_rare<D, kEdges>(lds_address(smem), lds_address(rec), out, t_next, what);
 }
 
 // Persistent work-groups: job i of the front and then the back list goes to
@@ -2096,14 +1933,16 @@ __device__ __forceinline__ void leaf_sorted(uint32_t* smem, const uint32_t* rec,
 // 2.32 ms; a key's place recomputed in the scatter instead of kept 1.05 /
 // 2.48 ms; rows of 256 positions, four to a lane, whose two stores each write
 // half lines, 1.54 / 5.2 ms.
-template <int B, bool kEdges>
-__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_sort(
+template <bool kEdges>
+__global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(6))) void k_leaf_sort(
     const Leaf* __restrict__ leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl, int round2,
     uint32_t takes) {
-  __shared__ __align__(16) uint32_t smem[kSmemSort];
-  SortSmem sm = sort_smem(smem);
-  uint32_t* const cache = sort_cache(smem);
-  static_assert(kSortPre + kWaveList / 2 + kWaveMaskWords + kWaveBases <= kSortKeys,
+  using D = SortGroup;
+  constexpr int B = D::B;
+  __shared__ __align__(16) uint32_t smem[D::kSmem];
+  __shared__ __align__(16) uint32_t cache[kSortCache];
+  SortSmem sm = sort_smem<D>(smem);
+  static_assert(kSortPre + kWaveList / 2 + kWaveMaskWords + kWaveBases <= D::kKeyWords,
                 "a dense leaf's arrays fit the keys");
   const uint64_t counts = uniform64(job_counts(ctl, round2));
   const uint64_t front = counts & 0xFFFFFFFFull, n_leaves = front + (counts >> 32);
@@ -2114,10 +1953,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_l
     return;
   }
   if (round2) takes = kTakesDense | kTakesSmall | kTakesOnce;
-  for (uint32_t i = threadIdx.x; i < kSortCnt; i += B) sm.cnt[i] = 0;
-  if (threadIdx.x < kSortPre) smem[2 * kSortCnt + threadIdx.x] = 0;
+  for (uint32_t i = threadIdx.x; i < D::kCnt; i += B) sm.cnt[i] = 0;
+  if (threadIdx.x < kSortPre) smem[2 * D::kCnt + threadIdx.x] = 0;
   if (threadIdx.x == 0) sm.scr[kSsClass] = 0;
-  static_assert(kSortSpare + kSortPre < kSortKeys, "the spare slot lies behind the sentinels");
   const uint64_t G = gridDim.x;
   uint32_t keep = 0;  // bit s: cached job s is run here
   for (uint64_t j = 0;; ++j) {
@@ -2166,9 +2004,9 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_l
     const uint32_t* const rec = cache + slot * kLeafWords;
     const uint32_t kind = __builtin_amdgcn_readfirstlane(rec[11]) & 3u;
     if (kind == kKindSparse || kind == kKindWr)
-      leaf_sorted<B, kEdges>(smem, rec, out);
+      leaf_sorted<D, kEdges>(smem, rec, out);
     else
-      leaf_rare<B, kEdges>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
+      leaf_rare<D, kEdges>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
   }
 }
 
@@ -2251,54 +2089,100 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_l
   leaf_loop<B, kListOnce, kEdges>(leaves, leaf_cap, out, ctl);
 }
 
-// Dense leaves of the back list, one wave (and work-group) per leaf: back job
-// i goes to wave i mod G; other jobs are left to k_leaf_mixed.
+// The jobs of the one-wave leaf kernels.  One work-group of kLeafWaves waves
+// per compute unit: back jobs i = blockIdx mod G are its own, handed to its
+// waves one by one (a counter in LDS), each job's record on the way while the
+// one before is run.  (Dealt to single-wave work-groups in advance, the same
+// jobs leave the older waves, which the issue favours, done after half the
+// time; a counter in memory for all of them costs more than that.)
+constexpr int kLeafWaves = 16;
+
+struct WaveJobs {
+  const Leaf* end;  // job i at end[-1 - i]
+  uint64_t n, job;
+  uint32_t* handed;
+  uint4 part;
+  __device__ __forceinline__ WaveJobs(const Leaf* e, uint64_t count, uint32_t* h)
+      : end(e), n(count), handed(h), part(make_uint4(0, 0, 0, 0)) {
+    next();
+  }
+  __device__ __forceinline__ void next() {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t t = 0;
+    if (lane == 0) t = atomicAdd(handed, 1u);
+    job = blockIdx.x + static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(t)) * gridDim.x;
+    if (job < n && lane < 3) part = reinterpret_cast<const uint4*>(end - 1 - job)[lane];
+  }
+  __device__ __forceinline__ bool more() const { return job < n; }
+  // The job, through the wave's kLeafWords words of LDS at rec.
+  __device__ __forceinline__ Leaf take(uint32_t* rec) {
+    const uint32_t lane = threadIdx.x & 63u;
+    if (lane < 3) reinterpret_cast<uint4*>(rec)[lane] = part;
+    sort_sync<64>();
+    next();
+    return cached_leaf(rec);
+  }
+};
+
+// Dense leaves of the back list, one wave per leaf.  Handed out in LDS: 1340
+// against 1540 us for n = 2^29 of 2^30 (4.3 GB written).
 template <bool kEdges>
-__global__ __launch_bounds__(64) void k_leaf_dense(const Leaf* __restrict__ leaves,
-                                                   uint64_t leaf_cap, uint64_t* out, Control* ctl) {
-  __shared__ __align__(16) uint16_t list[kWaveList];
-  __shared__ uint32_t mask[kWaveMaskWords];
-  __shared__ uint32_t bases[kWaveBases];
+__global__ __launch_bounds__(64 * kLeafWaves) void k_leaf_dense(const Leaf* __restrict__ leaves,
+                                                                uint64_t leaf_cap, uint64_t* out,
+                                                                Control* ctl) {
+  constexpr uint32_t kArrays = (kWaveList / 2 + kWaveMaskWords + kWaveBases + 3) / 4 * 4;
+  constexpr uint32_t kWords = kArrays + kLeafWords;
+  __shared__ __align__(16) uint32_t lds[kLeafWaves * kWords];
+  __shared__ uint32_t handed;
   const uint64_t counts = uniform64(job_counts(ctl, 0));
   const uint64_t front = counts & 0xFFFFFFFFull, back = counts >> 32;
-  if (front + back > leaf_cap) return;  // reported by k_leaf_mixed
-  for (uint64_t i = blockIdx.x; i < back; i += gridDim.x) {
-    const Leaf* rec = leaves + (leaf_cap - 1 - i);
-    Leaf L;
-    L.id = uniform64(rec->id);
-    L.lo = uniform64(rec->lo);
-    L.Nv = uniform64(rec->Nv);
-    L.off = uniform64(rec->off);
-    L.seed = uniform64(rec->seed);
-    L.nv = __builtin_amdgcn_readfirstlane(rec->nv);
-    L.flags = __builtin_amdgcn_readfirstlane(rec->flags);
-    if (!dense_by_wave(L) || L.nv == 0) continue;
-    leaf_dense_wave<kEdges>(L, out, list, mask, bases);
+  if (front + back > leaf_cap) return;  // reported by k_leaf_sort
+  uint32_t* const list = lds + kWords * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* const mask = list + kWaveList / 2;
+  if (threadIdx.x == 0) handed = 0;
+  __syncthreads();
+  WaveJobs jobs(leaves + leaf_cap, back, &handed);
+  while (jobs.more()) {
+    const Leaf L = jobs.take(list + kArrays);
+    if (dense_by_wave(L) && L.nv != 0)
+      leaf_dense_wave<kEdges>(L, out, reinterpret_cast<uint16_t*>(list), mask,
+                              mask + kWaveMaskWords);
+    sort_sync<64>();
   }
 }
 
-// Small sparse and with-replacement leaves of the back list, one wave (and
-// work-group) per leaf: back job i goes to wave i mod G.
+// Small sparse and with-replacement leaves of the back list, one wave per
+// leaf, sorted as in k_leaf_sort.  Bound by vector instructions (113 per 64
+// values with edges written, the edge's root a third of them).  2^28 edges of
+// 2^26 vertices, leaves of 512 values: 1360 us with values counted into 1024
+// word counters and sorting-network windows, 1260 with this sort, 980 with
+// the jobs handed out in LDS.
 template <bool kEdges>
-__global__ __launch_bounds__(64) void k_leaf_small(const Leaf* __restrict__ leaves,
-                                                   uint64_t leaf_cap, uint64_t* out, Control* ctl) {
-  __shared__ __align__(16) uint32_t keys[kSmallKeys];
-  __shared__ __align__(16) uint32_t cnt[kSmallCnt];
+__global__ __launch_bounds__(64 * kLeafWaves) void k_leaf_small(const Leaf* __restrict__ leaves,
+                                                                uint64_t leaf_cap, uint64_t* out,
+                                                                Control* ctl) {
+  using D = SortWave;
+  constexpr uint32_t kWords = D::kSmem + kLeafWords;
+  static_assert(D::kSmem % 4 == 0 && kWords % 4 == 0, "16-byte aligned arrays");
+  __shared__ __align__(16) uint32_t lds[kLeafWaves * kWords];
+  __shared__ uint32_t handed;
   const uint64_t counts = uniform64(job_counts(ctl, 0));
   const uint64_t front = counts & 0xFFFFFFFFull, back = counts >> 32;
-  if (front + back > leaf_cap) return;  // reported by k_leaf_mixed
-  for (uint64_t i = blockIdx.x; i < back; i += gridDim.x) {
-    const Leaf* rec = leaves + (leaf_cap - 1 - i);
-    Leaf L;
-    L.nv = __builtin_amdgcn_readfirstlane(rec->nv);
-    L.flags = __builtin_amdgcn_readfirstlane(rec->flags);
-    if (!small_by_wave(L) || L.nv == 0) continue;
-    L.id = uniform64(rec->id);
-    L.lo = uniform64(rec->lo);
-    L.Nv = uniform64(rec->Nv);
-    L.off = uniform64(rec->off);
-    L.seed = uniform64(rec->seed);
-    leaf_small_wave<kEdges>(L, out, keys, cnt);
+  if (front + back > leaf_cap) return;  // reported by k_leaf_sort
+  const uint32_t lane = lane_tid() & 63u;
+  uint32_t* const smem = lds + kWords * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* const rec = smem + D::kSmem;
+  SortSmem sm = sort_smem<D>(smem);
+  for (uint32_t i = lane; i < D::kCnt; i += 64) sm.cnt[i] = 0;
+  if (lane < kSortPre) smem[2 * D::kCnt + lane] = 0;
+  if (lane == 0) sm.scr[kSsClass] = 0;
+  if (threadIdx.x == 0) handed = 0;
+  __syncthreads();
+  WaveJobs jobs(leaves + leaf_cap, back, &handed);
+  while (jobs.more()) {
+    const Leaf L = jobs.take(rec);
+    if (small_by_wave(L) && L.nv != 0) leaf_sorted<D, kEdges>(smem, rec, out);
+    sort_sync<64>();
   }
 }
 
@@ -3764,34 +3648,16 @@ int leaf_occupancy() {
 int sort_occupancy() {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_sort<kSortBlock, false>), kSortBlock, 0) != hipSuccess ||
+          &occ, reinterpret_cast<const void*>(k_leaf_sort<false>), kSortBlock, 0) != hipSuccess ||
       occ <= 0)
     occ = 4;
   return occ;
 }
 
-int small_occupancy() {
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_small<false>), 64, 0) != hipSuccess ||
-      occ <= 0)
-    occ = 8;
-  return occ;
-}
-
 hipError_t launch_leaf_small(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream, bool edges) {
-  hipLaunchKernelGGL((edges ? k_leaf_small<true> : k_leaf_small<false>), dim3(grid), dim3(64), 0, stream, leaves, leaf_cap, out, ctl);
+  hipLaunchKernelGGL((edges ? k_leaf_small<true> : k_leaf_small<false>), dim3(grid), dim3(64 * kLeafWaves), 0, stream, leaves, leaf_cap, out, ctl);
   return hipGetLastError();
-}
-
-int dense_occupancy() {
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &occ, reinterpret_cast<const void*>(k_leaf_dense<false>), 64, 0) != hipSuccess ||
-      occ <= 0)
-    occ = 8;
-  return occ;
 }
 
 int bern_wave_occupancy() {
@@ -3849,7 +3715,7 @@ hipError_t launch_tree(const Instance* inst, uint32_t n_inst, uint64_t total_thr
 
 hipError_t launch_leaf_sort(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                             uint32_t grid, hipStream_t stream, int round2, uint32_t takes, bool edges) {
-  hipLaunchKernelGGL((edges ? k_leaf_sort<kSortBlock, true> : k_leaf_sort<kSortBlock, false>), dim3(grid), dim3(kSortBlock), 0, stream, leaves,
+  hipLaunchKernelGGL((edges ? k_leaf_sort<true> : k_leaf_sort<false>), dim3(grid), dim3(kSortBlock), 0, stream, leaves,
                      leaf_cap, out, ctl, round2, takes);
   return hipGetLastError();
 }
@@ -3878,7 +3744,7 @@ hipError_t launch_part_roots(const Instance& I, uint32_t depth, Node* roots, hip
 
 hipError_t launch_leaf_dense(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream, bool edges) {
-  hipLaunchKernelGGL((edges ? k_leaf_dense<true> : k_leaf_dense<false>), dim3(grid), dim3(64), 0, stream, leaves, leaf_cap, out, ctl);
+  hipLaunchKernelGGL((edges ? k_leaf_dense<true> : k_leaf_dense<false>), dim3(grid), dim3(64 * kLeafWaves), 0, stream, leaves, leaf_cap, out, ctl);
   return hipGetLastError();
 }
 

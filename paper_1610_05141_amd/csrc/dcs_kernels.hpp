@@ -140,10 +140,6 @@ hipError_t launch_zero(Control* ctl, unsigned long long* status, uint64_t n,
 // of k_leaf_sort.
 int leaf_occupancy();
 int sort_occupancy();
-// Resident k_leaf_dense work-groups (one wave each) per compute unit.
-int dense_occupancy();
-// Resident k_leaf_small work-groups (one wave each) per compute unit.
-int small_occupancy();
 // Resident work-groups per compute unit of the double-precision Bernoulli
 // kernel holding lds_cap offsets in LDS, and of the one-wave
 // single-precision one.
