@@ -251,10 +251,13 @@ __device__ __forceinline__ void geom_skips32(const uint4& w, float c, uint32_t (
     unsure[j] = !(__builtin_fabsf(off) <= __builtin_fmaf(x, -5e-7f, 0.5f - 0x1p-22f));
     skip[j] = static_cast<uint32_t>(x);
   }
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(unsure[0] || unsure[1] || unsure[2] ||
+                                                   unsure[3]) != 0, 0)) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (__builtin_amdgcn_ballot_w64(unsure[j]) != 0)
-      skip[j] = static_cast<uint32_t>(geom_skip32(pick(w, j), c));
+    for (int j = 0; j < 4; ++j)
+      if (__builtin_amdgcn_ballot_w64(unsure[j]) != 0)
+        skip[j] = static_cast<uint32_t>(geom_skip32(pick(w, j), c));
+  }
 }
 
 // Double-precision skips.  The defined skip is the floor of x = log64(U) c
@@ -305,8 +308,9 @@ __device__ __forceinline__ void geom_skips64(const uint4& w, double c, double ha
   const double f0 = __builtin_amdgcn_fract(x0), f1 = __builtin_amdgcn_fract(x1);
   g[0] = x0 - f0;
   g[1] = x1 - f1;
-  if (__builtin_amdgcn_ballot_w64(!(__builtin_fabs(f0 - 0.5) <= half) ||
-                                  !(__builtin_fabs(f1 - 0.5) <= half)) != 0) {
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(__builtin_fabs(f0 - 0.5) <= half) ||
+                                                   !(__builtin_fabs(f1 - 0.5) <= half)) != 0,
+                       0)) {
 #pragma unroll 1
     for (int j = 0; j < 2; ++j) {
       const uint64_t d = static_cast<uint64_t>(j ? w.z : w.x) |

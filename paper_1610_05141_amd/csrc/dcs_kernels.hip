@@ -1558,65 +1558,49 @@ __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, ui
         uint32_t q[4];
         if (lane == 0) bases[c] = q_base;
         const uint32_t adv = skip_chunk(st, c, lane, cg, q_base, q);
-        uint32_t in = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) in += q[j] <= Nv ? 1u : 0u;
         if (c < kWaveListChunks) put_chunk(list + c * kWaveChunk + 4u * lane, q);
-        // hits are a prefix of the chunk: whole lanes, then one partial lane
-        const unsigned long long whole = __ballot(in == 4u);
-        const uint32_t nw = static_cast<uint32_t>(__popcll(whole));
-        const uint32_t got =
-            nw == 64u ? kWaveChunk : 4u * nw + __builtin_amdgcn_readlane(in, nw);
-        cnt += got;
+        if (q_base + adv > Nv) {  // the draw that passes the range's end is here
+          uint32_t in = 0;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) in += q[j] <= Nv ? 1u : 0u;
+          // hits are a prefix of the chunk: whole lanes, then one partial lane
+          const uint32_t nw =
+              static_cast<uint32_t>(__popcll(__builtin_amdgcn_ballot_w64(in == 4u)));
+          cnt += 4u * nw + __builtin_amdgcn_readlane(in, nw);  // nw < 64
+          break;
+        }
+        cnt += kWaveChunk;
         q_base += adv;
-        if (got < kWaveChunk || cnt > cap) break;
+        if (cnt > cap) break;
       }
       if (cnt < nv || cnt > cap) continue;
     }
-    // Repair: remove the first (cnt - nv) distinct values of the REPAIR
-    // stream mapped into [0, cnt).  Words are taken 64 at a time in stream
-    // order (lane m holds word 64 j + m of a 256-word Philox round), so the
-    // r-th new value is found with a ballot.
+    // Repair: remove the first r = cnt - nv distinct values of the REPAIR
+    // stream mapped into [0, cnt).  While h of them are marked, the next r - h
+    // words hold no more than are missing, so all of them are marked, in any
+    // order; r / cnt of them or so repeat, and two or three rounds do.
     const uint32_t r = cnt - nv;
     const uint32_t mwords = (cnt + 31u) / 32u;
     for (uint32_t i = lane; i < mwords; i += 64u) mask[i] = 0u;
     if (r > 0) {
       const Stream sr = make_stream(L.seed, L.id, kRepair, attempt);
       const uint32_t thr = range_threshold(cnt);
-      uint32_t have = 0;
-      for (uint32_t it = 0; have < r; ++it) {
-        const uint4 w4 = philox_block(sr, it * 64u + lane);
-        for (uint32_t j = 0; j < 4u && have < r; ++j) {
-          const int src = static_cast<int>(16u * j + (lane >> 2));
-          const uint32_t x0 = __shfl(w4.x, src), x1 = __shfl(w4.y, src);
-          const uint32_t x2 = __shfl(w4.z, src), x3 = __shfl(w4.w, src);
-          const uint32_t cmp = lane & 3u;
-          const uint32_t word = cmp == 0 ? x0 : (cmp == 1 ? x1 : (cmp == 2 ? x2 : x3));
+      uint4 w4 = make_uint4(0, 0, 0, 0);
+      uint32_t have = 0, t = 0;  // values marked, words read
+      while (have < r) {
+        const uint32_t t0 = t & ~255u;  // lane l holds words t0 + 4l + j
+        if (t == t0) w4 = philox_block(sr, (t0 >> 2) + lane);
+        const uint32_t end = min(t + (r - have), t0 + 256u);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t i = t0 + 4u * lane + static_cast<uint32_t>(j);
           uint32_t v;
-          const bool ok = range_map(word, cnt, thr, &v);
+          const bool ok = range_map(pick(w4, j), cnt, thr, &v) && i >= t && i < end;
           const uint32_t bit = 1u << (v & 31u);
-          uint32_t* mw = mask + (v >> 5);
-          const bool fresh = ok && !(*mw & bit);
-          const uint32_t old = fresh ? atomicOr(mw, bit) : 0u;
-          // equal fresh values in one step: the lowest lane is the first
-          unsigned long long raced = __ballot(fresh && (old & bit));
-          bool later = false;
-          while (raced) {
-            const uint32_t s = static_cast<uint32_t>(__ffsll(static_cast<long long>(raced)) - 1);
-            const uint32_t vs = __builtin_amdgcn_readlane(v, s);
-            const unsigned long long same = __ballot(fresh && v == vs);
-            const uint32_t first = static_cast<uint32_t>(__ffsll(static_cast<long long>(same)) - 1);
-            later = later || (fresh && v == vs && lane != first);
-            raced &= ~same;
-          }
-          const bool firsts = fresh && !later;
-          const unsigned long long F = __ballot(firsts);
-          const uint32_t need = r - have;
-          // values past the r-th are not removed: take their bits back
-          if (firsts && lane_rank(F) >= need) atomicAnd(mw, ~bit);
-          const uint32_t nf = static_cast<uint32_t>(__popcll(F));
-          have += nf < need ? nf : need;
+          const uint32_t old = ok ? atomicOr(mask + (v >> 5), bit) : ~0u;
+          have += static_cast<uint32_t>(__popcll(__builtin_amdgcn_ballot_w64((old & bit) == 0)));
         }
+        t = end;
       }
     }
     // Kept hits in order, consecutive lanes on consecutive outputs (exactly
@@ -1636,25 +1620,40 @@ __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, ui
         put_chunk(list + kSpare + 4u * lane, q);
         sbase = kSpare;
       }
-      uint32_t pos[4], rm[4];
+      uint32_t pos[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)  // inside the list; past the last hit never stored
+        pos[t] = full ? k0 + 64u * t + lane : static_cast<uint32_t>(list[sbase + 64u * t + lane]);
+      // the chunk's removal bits (the words past the mask's, read as whatever
+      // lies there, belong to no hit)
+      const uint4 ma = *reinterpret_cast<const uint4*>(mask + k0 / 32u);
+      const uint4 mb = *reinterpret_cast<const uint4*>(mask + k0 / 32u + 4u);
+      const uint32_t mw[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
+      uint64_t K[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const uint32_t k = k0 + 64u * t + lane;
-        // every index stays inside the list and the mask; values past the
-        // last hit are read but never stored
-        pos[t] = full ? k : static_cast<uint32_t>(list[sbase + 64u * t + lane]);
-        const uint32_t w = k >> 5;
-        rm[t] = mask[w < kWaveMaskWords ? w : kWaveMaskWords - 1];
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(mw[2 * t]);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane(mw[2 * t + 1]);
+        K[t] = ~(static_cast<uint64_t>(lo) | (static_cast<uint64_t>(hi) << 32));
       }
+      if (k0 + kWaveChunk > cnt) {
+        const uint32_t left = cnt - k0;  // hits in this last chunk
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t k = k0 + 64u * t + lane;
-        const bool kept = k < cnt && !((rm[t] >> (k & 31u)) & 1u);
-        const unsigned long long K = __ballot(kept);
-        const uint32_t at = done + lane_rank(K);
-        if (kept && at < nv) store_out(o0 + at, out_value<kEdges>(b1, pos[t]));
-        done += static_cast<uint32_t>(__popcll(K));
+        for (uint32_t t = 0; t < 4; ++t) {
+          const uint32_t h = left > 64u * t ? left - 64u * t : 0u;
+          K[t] &= h < 64u ? (1ull << h) - 1u : ~0ull;
+        }
       }
+      uint32_t at[5];
+      at[0] = done;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) at[t + 1] = at[t] + static_cast<uint32_t>(__popcll(K[t]));
+      done = at[4];
+      if (done > nv) break;  // never: exactly nv hits are kept
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (__builtin_amdgcn_inverse_ballot_w64(K[t]))
+          store_out(o0 + (at[t] + lane_rank(K[t])), out_value<kEdges>(b1, pos[t]));
     }
     break;
   }
