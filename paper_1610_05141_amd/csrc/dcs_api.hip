@@ -567,6 +567,32 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   return DCS_OK;
 }
 
+// Whether a sample is one leaf that k_leaf_one takes, and that leaf.  Left to
+// the other kernels: dense leaves over more than 2^16, and sparse ones that
+// expect 20 or more repeats (the sort's repair takes 32 of them).  Profiled
+// and forced-grid calls keep the general launches.
+bool one_leaf(const DeviceCtx* c, const Instance& I, Leaf* leaf) {
+  if (I.n >= I.n0 || I.N > kLeafRange) return false;
+  if (g_profile || g_debug_takes.load() >= 0 || c->leaf_grid > 0) return false;
+  uint32_t kind;
+  if (I.variant == 1) {
+    kind = I.N == 1 ? dcs::kKindFill : dcs::kKindWr;
+  } else if (static_cast<uint64_t>(I.dense_ratio) * I.n >= I.N) {
+    if (I.N > (1u << 16)) return false;
+    kind = dcs::kKindDense;
+  } else {
+    if (I.n * I.n >= 40 * I.N) return false;
+    kind = dcs::kKindSparse;
+  }
+  *leaf = Leaf{};
+  leaf->id = 1;  // the root's
+  leaf->Nv = I.N;
+  leaf->seed = I.seed;
+  leaf->nv = static_cast<uint32_t>(I.n);
+  leaf->flags = kind | (I.n0 << 8);
+  return true;
+}
+
 std::mutex& lock() { return g_mu; }
 
 int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, const dcs_params* params,
@@ -608,6 +634,9 @@ int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, con
   I.variant = variant;
   I.cut = pl.cut;
   I.top_cut = pl.top_cut;
+  Leaf leaf;
+  if (one_leaf(c, I, &leaf))
+    return hip_status(dcs::launch_leaf_one(leaf, out, static_cast<hipStream_t>(stream), edges));
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out, static_cast<hipStream_t>(stream),
                            error_word(c, stream), leaf_wgs_for(c, variant, n),

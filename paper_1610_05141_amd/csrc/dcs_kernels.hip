@@ -2088,6 +2088,27 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(6))) void k_l
   leaf_loop<B, kListOnce, kEdges>(leaves, leaf_cap, out, ctl);
 }
 
+// A sample that is one leaf: no tree and no job record, one launch.
+template <bool kEdges>
+__global__ __launch_bounds__(kSortBlock) void k_leaf_one(Leaf L, uint64_t* out) {
+  using D = SortGroup;
+  __shared__ __align__(16) uint32_t smem[D::kSmem];
+  __shared__ __align__(16) uint32_t rec[kLeafWords];
+  SortSmem sm = sort_smem<D>(smem);
+  for (uint32_t i = threadIdx.x; i < D::kCnt; i += D::B) sm.cnt[i] = 0;
+  if (threadIdx.x < kSortPre) smem[2 * D::kCnt + threadIdx.x] = 0;
+  if (threadIdx.x == 0) {
+    sm.scr[kSsClass] = 0;
+    *reinterpret_cast<Leaf*>(rec) = L;
+  }
+  __syncthreads();
+  const uint32_t kind = L.flags & 3u;
+  if (kind == kKindSparse || kind == kKindWr)
+    leaf_sorted<D, kEdges>(smem, rec, out);
+  else
+    leaf_rare<D, kEdges>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
+}
+
 // The jobs of the one-wave leaf kernels.  One work-group of kLeafWaves waves
 // per compute unit: back jobs i = blockIdx mod G are its own, handed to its
 // waves one by one (a counter in LDS), each job's record on the way while the
@@ -3738,6 +3759,12 @@ hipError_t launch_part_roots(const Instance& I, uint32_t depth, Node* roots, hip
   const uint64_t blocks = (parts + 255) / 256;
   hipLaunchKernelGGL(k_part_roots, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, stream, I,
                      depth, parts, roots);
+  return hipGetLastError();
+}
+
+hipError_t launch_leaf_one(const Leaf& leaf, uint64_t* out, hipStream_t stream, bool edges) {
+  hipLaunchKernelGGL((edges ? k_leaf_one<true> : k_leaf_one<false>), dim3(1), dim3(kSortBlock), 0,
+                     stream, leaf, out);
   return hipGetLastError();
 }
 
