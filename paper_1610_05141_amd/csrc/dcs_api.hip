@@ -567,11 +567,12 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   return DCS_OK;
 }
 
-// Whether a sample is one leaf that k_leaf_one takes, and that leaf.  Left to
-// the other kernels: dense leaves over more than 2^16, and sparse ones that
-// expect 20 or more repeats (the sort's repair takes 32 of them).  Profiled
-// and forced-grid calls keep the general launches.
-bool one_leaf(const DeviceCtx* c, const Instance& I, Leaf* leaf) {
+// Whether a sample is one leaf that k_leaf_one takes, and that leaf; one_pass:
+// it expects 20 repeats or more (the sort's repair takes 32 of them).  Dense
+// leaves over more than 2^16 are left to the other kernels; profiled and
+// forced-grid calls keep the general launches.
+bool one_leaf(const DeviceCtx* c, const Instance& I, Leaf* leaf, bool* one_pass) {
+  *one_pass = false;
   if (I.n >= I.n0 || I.N > kLeafRange) return false;
   if (g_profile || g_debug_takes.load() >= 0 || c->leaf_grid > 0) return false;
   uint32_t kind;
@@ -581,8 +582,8 @@ bool one_leaf(const DeviceCtx* c, const Instance& I, Leaf* leaf) {
     if (I.N > (1u << 16)) return false;
     kind = dcs::kKindDense;
   } else {
-    if (I.n * I.n >= 40 * I.N) return false;
     kind = dcs::kKindSparse;
+    *one_pass = I.n * I.n >= 40 * I.N;
   }
   *leaf = Leaf{};
   leaf->id = 1;  // the root's
@@ -635,8 +636,10 @@ int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, con
   I.cut = pl.cut;
   I.top_cut = pl.top_cut;
   Leaf leaf;
-  if (one_leaf(c, I, &leaf))
-    return hip_status(dcs::launch_leaf_one(leaf, out, static_cast<hipStream_t>(stream), edges));
+  bool one_pass;
+  if (one_leaf(c, I, &leaf, &one_pass))
+    return hip_status(
+        dcs::launch_leaf_one(leaf, one_pass, out, static_cast<hipStream_t>(stream), edges));
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out, static_cast<hipStream_t>(stream),
                            error_word(c, stream), leaf_wgs_for(c, variant, n),

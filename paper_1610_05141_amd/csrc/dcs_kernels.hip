@@ -2014,18 +2014,24 @@ __global__ __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(6)))
 // once_by_group.
 constexpr int kListWide = 0, kListOnce = 1;
 
-template <int B, int kList, bool kEdges>
-__device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint64_t leaf_cap,
-                                          uint64_t* out, Control* ctl, int round2 = 0) {
-  __shared__ uint32_t smem[kSmemWords];
+// The arrays of the 512-thread kernels in kSmemWords words of LDS.
+__device__ __forceinline__ LeafSmem leaf_smem(uint32_t* smem) {
   LeafSmem sm;
   sm.keys = smem;
   sm.tmp = smem + kKeys;
   sm.buck = smem + kRegionA;
   sm.kept = sm.buck;
   sm.mask = sm.buck + kKeys;
+  sm.scr = smem + kRegionA + kRegionB + kCacheWords;
+  return sm;
+}
+
+template <int B, int kList, bool kEdges>
+__device__ __forceinline__ void leaf_loop(const Leaf* __restrict__ leaves, uint64_t leaf_cap,
+                                          uint64_t* out, Control* ctl, int round2 = 0) {
+  __shared__ uint32_t smem[kSmemWords];
+  LeafSmem sm = leaf_smem(smem);
   uint32_t* cache = smem + kRegionA + kRegionB;
-  sm.scr = cache + kCacheWords;
   const uint64_t counts = uniform64(job_counts(ctl, round2));
   const uint64_t front = counts & 0xFFFFFFFFull, n_leaves = counts >> 32;
   if (front + n_leaves > leaf_cap) return;  // reported by k_leaf_sort
@@ -2107,6 +2113,14 @@ __global__ __launch_bounds__(kSortBlock) void k_leaf_one(Leaf L, uint64_t* out) 
     leaf_sorted<D, kEdges>(smem, rec, out);
   else
     leaf_rare<D, kEdges>(lds_address(smem), lds_address(rec), out, 0, kRareOther);
+}
+
+// The same for a sparse leaf of many repeats, in one pass.
+template <int B, bool kEdges>
+__global__ __launch_bounds__(B) void k_leaf_one_pass(Leaf L, uint64_t* out) {
+  __shared__ uint32_t smem[kSmemWords];
+  LeafSmem sm = leaf_smem(smem);
+  leaf_once<B, kEdges>(L, out, sm);
 }
 
 // The jobs of the one-wave leaf kernels.  One work-group of kLeafWaves waves
@@ -3762,9 +3776,14 @@ hipError_t launch_part_roots(const Instance& I, uint32_t depth, Node* roots, hip
   return hipGetLastError();
 }
 
-hipError_t launch_leaf_one(const Leaf& leaf, uint64_t* out, hipStream_t stream, bool edges) {
-  hipLaunchKernelGGL((edges ? k_leaf_one<true> : k_leaf_one<false>), dim3(1), dim3(kSortBlock), 0,
-                     stream, leaf, out);
+hipError_t launch_leaf_one(const Leaf& leaf, bool one_pass, uint64_t* out, hipStream_t stream,
+                           bool edges) {
+  if (one_pass)
+    hipLaunchKernelGGL((edges ? k_leaf_one_pass<kLeafBlock, true> : k_leaf_one_pass<kLeafBlock, false>),
+                       dim3(1), dim3(kLeafBlock), 0, stream, leaf, out);
+  else
+    hipLaunchKernelGGL((edges ? k_leaf_one<true> : k_leaf_one<false>), dim3(1), dim3(kSortBlock), 0,
+                       stream, leaf, out);
   return hipGetLastError();
 }
 

@@ -186,8 +186,9 @@ hipError_t launch_leaf_once(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out
 // Dense leaves of the back list whose range fits 16-bit positions, one wave
 // per leaf (k_leaf_sort skips them).
 // One leaf as the whole sample (sparse, with replacement, constant, or dense
-// over at most 2^16).
-hipError_t launch_leaf_one(const Leaf& leaf, uint64_t* out, hipStream_t stream, bool edges);
+// over at most 2^16); one_pass: a sparse leaf of many repeats.
+hipError_t launch_leaf_one(const Leaf& leaf, bool one_pass, uint64_t* out, hipStream_t stream,
+                           bool edges);
 hipError_t launch_leaf_dense(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream, bool edges);
 // Sparse and with-replacement leaves of the back list with at most 1024

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
     (0, 33, 1 << 20, 4096), (0, 4095, 1 << 32, 4096), (0, 4095, (1 << 32) + 1, 4096),
     (0, 4096, 1 << 32, 4096), (0, 1023, 1 << 31, 1024), (0, 500, 500, 4096), (0, 4000, 8000, 4096),
     (0, 4095, 65_520, 4096), (0, 4000, 65_536, 4096), (0, 4000, 399_999, 4096),
-    (0, 4000, 400_001, 4096), (0, 1, 2, 2),
+    (0, 4000, 400_001, 4096), (0, 1, 2, 2), (0, 4095, 65_521, 4096), (0, 1794, 60_720, 4096),
+    (0, 1000, 16_001, 4096), (0, 700, 11_201, 4096), (0, 1200, 1 << 15, 4096),
     (1, 1, 1, 4096), (1, 4095, 1, 4096), (1, 4096, 1, 4096), (1, 4095, 2, 4096),
     (1, 3000, 1 << 32, 4096), (1, 100, 3_000_000_019, 4096)])
 def test_one_leaf(ref, variant, n, N, n0):
@@ -31,6 +32,16 @@ def test_one_leaf(ref, variant, n, N, n0):
             assert np.array_equal(got, want), first_mismatch(got, want)
     finally:
         m.debug_leaf_kernels(-1)
+
+
+@pytest.mark.parametrize("n,N", [(100, 230), (90, 201), (1500, 3100), (2000, 90_000)])
+def test_one_leaf_of_many_repeats(ref, n, N):
+    m = dcs()
+    announce(f"one leaf: n={n} N={N} dense_ratio=2")
+    got = to_np_u64(m.sample(n, N, 22, dense_ratio=2))
+    m.synchronize()
+    want = ref.sample(n, N, 22, dense_ratio=2)
+    assert np.array_equal(got, want), first_mismatch(got, want)
 
 
 def test_captured_one_leaf(ref):
