@@ -861,12 +861,11 @@ constexpr uint32_t kSortCacheLeaves = 16;
 constexpr uint32_t kSortCache = kSortCacheLeaves * kLeafWords;
 constexpr uint32_t kMaxFix = 32;                            // repeats repaired in place
 constexpr uint32_t kCand = 8;                               // candidates per repair step
-// scratch words: [0, 16) scan; 16 class bits; 17 repeats; 18 next word;
-// 19 candidates that are no new values; 20 jobs to run; 21 some value
-// repeats; [32, 64) repeats' positions;
-// [64, 96) new values; [96, 104) candidates
-constexpr uint32_t kSsClass = 16, kSsDups = 17, kSsNext = 18, kSsDead = 19, kSsKeep = 20, kSsAny = 21,
-                   kSsDupPos = 32, kSsNew = 64, kSsCand = 96, kSsWords = 112;
+// scratch words: [0, 16) scan; 16 class bits; 17 repeats; 18 next word; 20
+// jobs to run; 21 some value repeats; [32, 64) repeats' positions; [64, 96)
+// new values
+constexpr uint32_t kSsClass = 16, kSsDups = 17, kSsNext = 18, kSsKeep = 20, kSsAny = 21,
+                   kSsDupPos = 32, kSsNew = 64, kSsWords = 96;
 constexpr uint32_t kOnes4 = 0x11111111u, kFours4 = 0x44444444u;
 
 // Back-list leaves (ranges that are no powers of two) of at most so many
@@ -1080,13 +1079,21 @@ __device__ void find_repeats(uint32_t s0, uint32_t nn, const WordMap& m, const S
 // The row pass after a repair: D removed positions (the repeats) and D new
 // values, ascending.  Position p keeps its value v at p - (removed below p) +
 // (new values below v); a new value belongs right after the last position
-// whose value is smaller.
+// whose value is smaller.  A full row without a removed position or a new
+// value in it moves as a whole, or stays.
+struct __attribute__((packed, aligned(8))) OutPair {
+  uint64_t x, y;
+};
 template <int B, bool kEdges>
 __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn, const WordMap& m,
                              const SortSmem& sm, uint32_t D) {
   const uint32_t tid = sort_tid<B>();
   const uint32_t lane = tid & 63u;
   const bool inner = lane - kHalo < 64u - 2 * kHalo;
+  const bool has = lane < D;
+  const uint32_t dpos = has ? sm.scr[kSsDupPos + lane] : 0u;
+  const uint32_t dnew = has ? sm.scr[kSsNew + lane] : 0u;
+  const auto count = [](uint64_t mask) { return static_cast<uint32_t>(__popcll(mask)); };
   for (uint32_t r0 = kRow * __builtin_amdgcn_readfirstlane(tid >> 6); r0 < nn;
        r0 += kRow * (B / 64)) {
     uint32_t v[3];
@@ -1095,6 +1102,23 @@ __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
     v[1] = word_value(m, v[1]);
     v[2] = lane_after(v[0]);
     const uint32_t p = r0 + 2 * lane - 2 * kHalo;
+    if (r0 >= s0 && r0 + kRow < nn) {
+      const uint32_t vf = __builtin_amdgcn_readlane(v[0], kHalo);       // position r0
+      const uint32_t vn = __builtin_amdgcn_readlane(v[0], 64 - kHalo);  // r0 + kRow
+      const uint64_t at = __builtin_amdgcn_ballot_w64(
+          has && ((dpos >= r0 && dpos < r0 + kRow) || (dnew > vf && dnew < vn)));
+      if (at == 0) {
+        const uint32_t shift = count(__builtin_amdgcn_ballot_w64(has && dnew < vf)) -
+                               count(__builtin_amdgcn_ballot_w64(has && dpos < r0));
+        if (shift != 0 && inner) {
+          OutPair pr;
+          pr.x = out_value<kEdges>(b1, v[0]);
+          pr.y = out_value<kEdges>(b1, v[1]);
+          *reinterpret_cast<OutPair*>(o + static_cast<int32_t>(p + shift)) = pr;
+        }
+        continue;
+      }
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const uint32_t q = p + h;
@@ -1107,7 +1131,8 @@ __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
           removed = removed || dp == q;
           below += sm.scr[kSsNew + i] < v[h] ? 1u : 0u;
         }
-        if (!removed && gone != below) store_out(o + (q - gone + below), out_value<kEdges>(b1, v[h]));
+        if (!removed && gone != below)
+          store_out(o + (q - gone + below), out_value<kEdges>(b1, v[h]));
         // positions up to q that stay, then the new values in the gap above q
         const uint32_t stay = q + 1 - gone - (removed ? 1u : 0u);
         const bool last = q + 1 == nn;
@@ -1228,62 +1253,58 @@ __device__ __forceinline__ void leaf_general(const Stream& st, uint32_t t, uint3
   sort_sync<B>();
 }
 
-// D <= kMaxFix repeats found by the row pass: the stream's next D new values
-// from word t on, ascending, into the scratch.  keys[s0 .. nn) hold the
-// leaf's words.  Ends with a barrier.
-template <int B>
-__device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t s0, uint32_t nn,
-                             const WordMap& m, SortSmem& sm) {
-  uint32_t* scr = sm.scr;
+// D <= kMaxFix repeats noted by the row pass: the stream's next D new values
+// from word t on, ascending, into the scratch, by the leaf's first wave: kCand
+// words at a time, eight lanes to a word.  Words of one value differ by less
+// than 2^32 / N_v + 1, so a word's value can only be among the keys of the
+// counter words that cover so many words around it, about 32 keys mostly.
+// Ends with a barrier.
+template <class D_>
+__device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t nn,
+                             const WordMap& m, const SortSmem& sm) {
+  constexpr int B = D_::B;
+  uint32_t* const scr = sm.scr;
   const uint32_t tid = sort_tid<B>();
-  uint32_t have = 0;
-  while (have < D) {
-    if (tid < 64) {
-      uint32_t v = 0;
-      bool good = false;  // not void
-      if (tid < kCand) {
-        const uint32_t w = pick(philox_block(st, (t + tid) >> 2), (t + tid) & 3u);
-        v = word_value(m, w);
-        good = w * m.s >= m.thr;
-      }
-      const unsigned long long gm = __ballot(good);
+  if (tid < 64) {
+    const uint32_t c = tid >> 3, l = tid & 7u;
+    const uint32_t width = m.s == 0 ? 1u : 0xFFFFFFFFu / m.s + 1u;
+    const uint32_t* const start = sm.cnt + D_::kCnt;  // bytes, by counter word
+    uint32_t have = 0;
+    while (have < D) {
+      const uint32_t w = pick(philox_block(st, (t + c) >> 2), (t + c) & 3u);
+      const uint32_t v = word_value(m, w);
+      const bool good = w * m.s >= m.thr;  // not void
+      const uint32_t lo = w > width ? w - width : 0u;
+      const uint32_t after = (add_sat(w, width) >> D_::kWordShift) + 1u;
+      const uint32_t i0 = start[lo >> D_::kWordShift] >> 2;
+      const uint32_t i1 = after < D_::kCnt ? start[after] >> 2 : nn;
       bool dead = !good;
-      for (uint32_t i = 0; i < have; ++i) dead = dead || scr[kSsNew + i] == v;
+      for (uint32_t i = i0 + l; i < i1; i += 8) dead = dead || word_value(m, sm.keys[i]) == v;
+      for (uint32_t i = l; i < have; i += 8) dead = dead || scr[kSsNew + i] == v;
+      const unsigned long long gm = __builtin_amdgcn_ballot_w64(good);
 #pragma unroll
-      for (uint32_t c = 0; c < kCand; ++c)  // an earlier candidate of this step
-        dead = dead || (c < tid && ((gm >> c) & 1u) != 0 &&
-                        static_cast<uint32_t>(__builtin_amdgcn_readlane(v, c)) == v);
-      const unsigned long long dm = __ballot(dead);
-      if (tid < kCand) scr[kSsCand + tid] = v;
-      if (tid == 0) scr[kSsDead] = static_cast<uint32_t>(dm) & ((1u << kCand) - 1u);
-    }
-    sort_sync<B>();
-    uint32_t c[kCand], hit = 0;
+      for (uint32_t e = 0; e + 1 < kCand; ++e)  // an earlier word of this step
+        dead = dead || (e < c && ((gm >> (8 * e)) & 1u) != 0 &&
+                        static_cast<uint32_t>(__builtin_amdgcn_readlane(v, 8 * e)) == v);
+      const unsigned long long dm = __builtin_amdgcn_ballot_w64(dead);
+      uint32_t fresh = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kCand; ++i) c[i] = scr[kSsCand + i];
-    for (uint32_t i = s0 + tid; i < nn; i += B) {
-      const uint32_t v = word_value(m, sm.keys[i]);
-#pragma unroll
-      for (uint32_t j = 0; j < kCand; ++j) hit |= c[j] == v ? 1u << j : 0u;
+      for (uint32_t e = 0; e < kCand; ++e)
+        fresh |= ((dm >> (8 * e)) & 0xFFu) == 0 ? 1u << e : 0u;
+      const uint32_t i = have + static_cast<uint32_t>(__popc(fresh & ((1u << c) - 1u)));
+      if (l == 0 && ((fresh >> c) & 1u) != 0 && i < D) scr[kSsNew + i] = v;
+      sort_sync<64>();
+      have += static_cast<uint32_t>(__popc(fresh));
+      t += kCand;
     }
-    if (hit != 0) atomicOr(&scr[kSsDead], hit);
-    sort_sync<B>();
-    const uint32_t fresh = ~scr[kSsDead] & ((1u << kCand) - 1u);
-    if (tid < kCand && ((fresh >> tid) & 1u)) {
-      const uint32_t i = have + static_cast<uint32_t>(__popc(fresh & ((1u << tid) - 1u)));
-      if (i < D) scr[kSsNew + i] = scr[kSsCand + tid];
+    uint32_t x = 0, rank = 0;
+    if (tid < D) {
+      x = scr[kSsNew + tid];
+      for (uint32_t i = 0; i < D; ++i) rank += scr[kSsNew + i] < x ? 1u : 0u;
     }
-    have += static_cast<uint32_t>(__popc(fresh));
-    t += kCand;
-    sort_sync<B>();
+    sort_sync<64>();
+    if (tid < D) scr[kSsNew + rank] = x;
   }
-  uint32_t x = 0, rank = 0;
-  if (tid < D) {
-    x = scr[kSsNew + tid];
-    for (uint32_t i = 0; i < D; ++i) rank += scr[kSsNew + i] < x ? 1u : 0u;
-  }
-  sort_sync<B>();
-  if (tid < D) scr[kSsNew + rank] = x;
   sort_sync<B>();
 }
 
@@ -1755,7 +1776,7 @@ __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* 
     sort_sync<B>();
     const uint32_t reps = __builtin_amdgcn_readfirstlane(sm.scr[kSsDups]);
     if (reps <= kMaxFix) {
-      draw_missing<B>(v.st, t, reps, v.s0, v.nn, v.m, sm);
+      draw_missing<D>(v.st, t, reps, v.nn, v.m, sm);
       rewrite_rows<B, kEdges>(v.o, v.b1, v.s0, v.nn, v.m, sm, reps);
       sort_sync<B>();
       return;
