@@ -35,18 +35,18 @@ BYTES_PER_SAMPLE = 8
 # kernels as built from the sources with this digest and are reported only
 # while the sources still match it.
 TRAFFIC_SOURCES_SHA256 = "431c57e9dcd1f5baf469f65b8ad6f8d117199f33f06d809519e880a0cee3b159"
-LEAF_TRAFFIC = {  # k_leaf_pow2, n = 2^30 of N = 2^48
+LEAF_TRAFFIC = {  # k_leaf_sort, n = 2^30 of N = 2^48
     "fetch_bytes": 70_600_684,      # 34473.0 KiB FETCH_SIZE x 2.0
     "write_bytes": 8_877_810_144,   # 8669736.5 KiB WRITE_SIZE x 1.0
 }
 CONFIG_TRAFFIC = {
-    "c1_wor_2^20_of_2^32": {"kernel": "k_leaf_pow2", "fetch_bytes": 655_498,
+    "c1_wor_2^20_of_2^32": {"kernel": "k_leaf_sort", "fetch_bytes": 655_498,
         "write_bytes": 12_126_592, "algorithmic_bytes": 8_388_608},
     "c2b_wor_dense_2^29_of_2^30": {"kernel": "k_leaf_dense", "fetch_bytes": 38_021_868,
         "write_bytes": 4_831_421_120, "algorithmic_bytes": 4_294_967_296},
     "c3a_bernoulli_p0.01_of_2^36": {"kernel": "k_bern_wave", "fetch_bytes": 228_354_369,
         "write_bytes": 5_894_884_217, "algorithmic_bytes": 5_497_618_384},
-    "c3b_wr_2^28_of_2^40": {"kernel": "k_leaf_pow2", "fetch_bytes": 23_125_584,
+    "c3b_wr_2^28_of_2^40": {"kernel": "k_leaf_sort", "fetch_bytes": 23_125_584,
         "write_bytes": 2_228_530_617, "algorithmic_bytes": 2_147_483_648},
     "c2b_wholerange_B_2^29_of_2^30": {"kernel": "k_wb_write", "fetch_bytes": 171_987_807,
         "write_bytes": 4_669_660_403, "algorithmic_bytes": 4_362_099_332},
@@ -242,7 +242,7 @@ def bench_other_configs(dcs, reps: int = 5, only=None):
             out = torch.empty(n, dtype=torch.int64, device="cuda")
             f = dcs.sample if kind == "wor" else dcs.sample_replacement
             run = lambda: f(n, N, seed, out=out, stream=stream)
-            kernels = {"k_leaf_pow2": 4, "k_leaf_mixed": 5, "k_leaf_dense": 6,
+            kernels = {"k_leaf_sort": 4, "k_leaf_mixed": 5, "k_leaf_dense": 6,
                        "k_leaf_small": 12, "k_leaf_once": 13}
         run()
         dcs.synchronize(stream)
@@ -458,16 +458,12 @@ def bench_graph(dcs, reps: int = 5):
     }
     for name, (run, count) in cases.items():
         run()
-        dt, prof, _ = time_calls(dcs, run, reps, stream, (7,))
-        d_ms, d_n = prof[7]
+        dt, _, _ = time_calls(dcs, run, reps, stream, ())
         edges = m if count is None else (count if isinstance(count, int) else int(count.item()))
-        dec = d_ms / max(d_n, 1)
         res[name] = {
             "edges": edges,
             "ms_per_call": dt * 1e3,
             "edges_per_s": edges / dt,
-            "decode_kernel_ms": dec,
-            "decode_GBs": 16 * edges / (dec * 1e-3) / 1e9 if dec > 0 else None,
         }
     del e, eg
     torch.cuda.empty_cache()
@@ -600,7 +596,7 @@ def main() -> int:
         dcs.sample(N_SAMPLE, UNIVERSE, SEED, out=out, stream=stream, n0=N0)
     dcs.synchronize(stream)
     stage_ms, stage_n = dcs.profile_read(2)
-    mixed_ms, mixed_n = dcs.profile_read(5)   # work-group leaf kernel of the other kinds
+    mixed_ms, mixed_n = dcs.profile_read(5)   # dense leaves above 2^16
     dense_ms, dense_n = dcs.profile_read(6)   # one-wave dense leaf kernel
     small_ms, small_n = dcs.profile_read(12)  # one-wave small leaf kernel
     once_ms, once_n = dcs.profile_read(13)    # one-pass kernel of repeating sparse leaves
@@ -641,13 +637,13 @@ def main() -> int:
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": recorded_traffic(),
-            "kernel": "k_leaf_pow2",
+            "kernel": "k_leaf_sort",
             "kernel_avg_ms": leaf_avg_ms,
         },
         "geometry": {"cut_bias,leaf_wgs_per_cu": list(dcs.tune_get(0, 30))},
         "kernels_ms_per_step": {"reset": reset_ms / max(reset_n, 1),
                                 "tree": tree_ms / max(tree_n, 1),
-                                "k_leaf_pow2": leaf_avg_ms,
+                                "k_leaf_sort": leaf_avg_ms,
                                 "k_leaf_mixed": mixed_ms / max(mixed_n, 1),
                                 "k_leaf_dense": dense_ms / max(dense_n, 1),
                                 "k_leaf_small": small_ms / max(small_n, 1),

@@ -217,8 +217,8 @@ int32_t dcs_online_destroy(dcs_online* online);
  * vertices 0..n_vertices-1 (Sec. 7: such a graph is a sample without
  * replacement of m of the n(n-1)/2 possible edges).  Edge index k (0-based)
  * is the pair (u, v), v < u, with k = u(u-1)/2 + v; the edges are those of
- * dcs_sample_ex(m, n(n-1)/2, seed, params) (value k+1 <-> index k), decoded
- * in place.
+ * dcs_sample_ex(m, n(n-1)/2, seed, params) (value k+1 <-> index k), written
+ * as pairs by the kernels that sample them.
  *   uv_dev: 2m uint32 in device memory, 8-byte aligned: edge i is
  *           (uv_dev[2i], uv_dev[2i+1]) = (u, v), in increasing (u, v) order.
  * Errors: DCS_EINVAL if n(n-1)/2 > DCS_MAX_UNIVERSE, m > n(n-1)/2, uv_dev
@@ -230,7 +230,7 @@ int32_t dcs_sample_edges_gnm(uint64_t n_vertices, uint64_t m, uint64_t seed,
  * dcs_sample_edges_gnp -- the edges of a random graph G(n, p): each of the
  * n(n-1)/2 pairs independently with probability p (Sec. 7: Bernoulli
  * sampling of the possible edges), i.e. dcs_sample_bernoulli_ex over
- * 1..n(n-1)/2 decoded as for G(n, m).
+ * 1..n(n-1)/2 written as for G(n, m).
  *   uv_dev:    2 * capacity uint32 (8-byte aligned); the first
  *              min(count, capacity) edges are written.
  *   count_dev: one uint64 in device memory, receives the true edge count
@@ -464,8 +464,9 @@ int32_t dcs_debug_lookback_help(uint32_t polls);
 int32_t dcs_debug_bernoulli_list(uint32_t words);
 /* dcs_debug_leaf_kernels -- test hook: which specialised leaf kernels a
  * single-instance tree call (or a call of an online session, whose parts
- * are subtrees of one sample's tree) leaves out, their leaves then run in the general
- * work-group kernel: bit 0 the one-wave dense kernel, bit 1 the one-wave
+ * are subtrees of one sample's tree) leaves out, their leaves then run in the
+ * work-group leaf kernel of the sparse jobs (and a sample of one leaf takes the
+ * general launches): bit 0 the one-wave dense kernel, bit 1 the one-wave
  * kernel of leaves of at most 1024 values, bit 2 the one-pass kernel of
  * leaves expected to repeat.  By default (mask < 0) a call leaves out the
  * kernels whose leaves its tree cannot plausibly hold.  Never changes a
@@ -487,19 +488,21 @@ const char* dcs_status_string(int32_t status);
  * dcs_profile_read: after the stream is synchronized, accumulated
  * milliseconds and launch count for kernel `kind`
  * (0 = reset, 1 = tree split, 2 = leaf stage: all leaf kernels,
- * 3 = Bernoulli chunk, 4 = leaf kernel of the sparse and with-replacement
- * jobs over power-of-two ranges,
- * 5 = work-group leaf kernel of the other jobs and of the second round's
- * jobs, 6 = one-wave-per-leaf
- * kernel of the dense jobs with ranges up to 2^16, 7 = edge-index
- * decoding of the graph entry points, 8 = the segment splits of
+ * 3 = Bernoulli chunk, 4 = work-group leaf kernel of the sparse, with-
+ * replacement and constant jobs, 5 = work-group leaf kernel of the dense jobs
+ * with ranges above 2^16 (nothing is launched where there can be none),
+ * 6 = one-wave-per-leaf
+ * kernel of the dense jobs with ranges up to 2^16, 7 = nothing any more (the
+ * sampling kernels write edges themselves), 8 = the segment splits of
  * dcs_sample_segments, 9 / 10 / 11 = the count passes / the scan and
  * repair / the write passes of dcs_sample_wholerange, 12 = one-wave-per-leaf
  * kernel of the sparse and with-replacement jobs of at most 1024 values over
  * ranges that are not powers of two (and of the sparse ones over powers of
  * two that are expected to repeat), 13 = work-group kernel of the sparse jobs
  * of more than 1024 values with n_v^2 >= 2 N_v, which samples each in one
- * pass instead of repeat rounds); DCS_EINVAL for another kind. */
+ * pass instead of repeat rounds); DCS_EINVAL for another kind.  A sample that
+ * is one leaf takes one launch when nothing is timed, and the launches above
+ * while it is. */
 int32_t dcs_profile_enable(int32_t enable);
 int32_t dcs_profile_read(int32_t kind, double* total_ms, uint64_t* launches);
 /* Restrict the timing to the kinds whose bit is set in `mask` (bit k: kind

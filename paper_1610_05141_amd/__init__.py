@@ -505,9 +505,9 @@ def profile_kinds(kinds=None):
 
 def profile_read(kind: int):
     """(total milliseconds, launches) of kernel kind 0 reset, 1 tree, 2 leaf
-    stage (all leaf kernels), 3 Bernoulli, 4 leaf kernel of the sparse and
-    with-replacement jobs over power-of-two ranges, 5 work-group leaf kernel
-    of the other jobs, 6 one-wave dense leaf kernel, 7 edge decoding, 8
+    stage (all leaf kernels), 3 Bernoulli, 4 work-group leaf kernel of the
+    sparse, with-replacement and constant jobs, 5 work-group leaf kernel of
+    dense jobs above 2^16, 6 one-wave dense leaf kernel, 7 nothing, 8
     segment splits, 9 / 10 / 11 whole-range B count / repair / write, 12
     one-wave leaf kernel of jobs of at most 1024 values, 13 one-pass kernel
     of sparse jobs expected to repeat, accumulated since profile_enable (read

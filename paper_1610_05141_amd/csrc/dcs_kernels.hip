@@ -8,11 +8,13 @@
 //                a depth-first walk; every leaf becomes a self-contained job.
 //   k_leaf_*     persistent work-groups, each taking every G-th leaf job (the
 //                atomic jobs of Sec. 4.2, assigned statically so that job
-//                records stream into LDS ahead of use), run the base case:
+//                records stream into LDS ahead of use; a one-wave kernel's
+//                work-group hands its jobs to its waves), run the base case:
 //                  sparse  Algorithm H semantics (Sec. 2): the first n_v
 //                          distinct values of the node's stream, in order by
 //                          an LDS counting sort by most significant bits
-//                          (the sorted-H idea of Sec. 4.1);
+//                          (the sorted-H idea of Sec. 4.1), finished by
+//                          transposition rounds in registers;
 //                  dense   Algorithm B (Sec. 2): geometric skips + prefix sum
 //                          (Sec. 4.7), restart on a short sample, removal of
 //                          the excess by Algorithm H semantics;
@@ -813,7 +815,7 @@ __device__ const uint32_t* leaf_sparse_once(const Stream& st, uint32_t nv, const
 
 // Sparse leaves of more than kSmallMax values whose first n_v values are
 // expected to repeat (n_v^2 >= 2 N_v, any range) run in k_leaf_once, in one
-// pass; k_leaf_mixed skips them, so that its own leaf bodies keep their
+// pass; k_leaf_sort skips them, so that its own leaf bodies keep their
 // registers.
 template <int B, bool kEdges>
 __device__ void leaf_once(const Leaf& L, uint64_t* out, LeafSmem& sm) {
@@ -1499,7 +1501,7 @@ __device__ void leaf_dense(const Leaf& L, uint64_t* out, LeafSmem& sm) {
 // Dense leaf, one wave per leaf (same sample as leaf_dense).
 // ---------------------------------------------------------------------------
 // Leaves whose range fits 16-bit positions are taken by k_leaf_dense, one
-// wave each with no barrier; the work-group leaf loop skips them.  With the
+// wave each with no barrier; k_leaf_mixed skips them.  With the
 // default dense ratio (16) and n0 <= 4096 that is every dense leaf.
 constexpr uint32_t kWaveMaxRange = 1u << 16;
 constexpr uint32_t kWaveChunk = 256;                             // draws per chunk

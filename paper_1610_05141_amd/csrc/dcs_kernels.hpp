@@ -183,16 +183,16 @@ hipError_t launch_leaf_mixed(const Leaf* leaves, uint64_t leaf_cap, uint64_t* ou
 // (one-pass sampler).
 hipError_t launch_leaf_once(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                             uint32_t grid, hipStream_t stream, bool edges);
-// Dense leaves of the back list whose range fits 16-bit positions, one wave
-// per leaf (k_leaf_sort skips them).
 // One leaf as the whole sample (sparse, with replacement, constant, or dense
 // over at most 2^16); one_pass: a sparse leaf of many repeats.
 hipError_t launch_leaf_one(const Leaf& leaf, bool one_pass, uint64_t* out, hipStream_t stream,
                            bool edges);
+// Dense leaves of the back list whose range fits 16-bit positions, one wave
+// per leaf (k_leaf_sort skips them); grid: work-groups of 16 waves.
 hipError_t launch_leaf_dense(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream, bool edges);
 // Sparse and with-replacement leaves of the back list with at most 1024
-// values, one wave per leaf (k_leaf_sort skips them).
+// values, one wave per leaf (k_leaf_sort skips them); grid as for dense ones.
 hipError_t launch_leaf_small(const Leaf* leaves, uint64_t leaf_cap, uint64_t* out, Control* ctl,
                              uint32_t grid, hipStream_t stream, bool edges);
 // Bernoulli chunk kernels: kBernFp64Group = k_bern (double-precision skips,
