@@ -1037,8 +1037,8 @@ __device__ __forceinline__ bool write_rows(uint64_t* o, uint64_t b1, uint32_t s0
     } else {
       dup |= __builtin_amdgcn_ballot_w64(inner && ((a == b && p >= s0 && p + 1 < nn) ||
                                                    (b == na && p + 1 >= s0 && p + 2 < nn)));
-      if (inner && p >= s0 && p < nn) store_out(o + p, pr.x);
-      if (inner && p + 1 >= s0 && p + 1 < nn) store_out(o + p + 1, pr.y);
+      if (inner && p >= s0 && p < nn) o[p] = pr.x;
+      if (inner && p + 1 >= s0 && p + 1 < nn) o[p + 1] = pr.y;
     }
   }
   return dup != 0;
@@ -1134,16 +1134,16 @@ __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
           below += sm.scr[kSsNew + i] < v[h] ? 1u : 0u;
         }
         if (!removed && gone != below)
-          store_out(o + (q - gone + below), out_value<kEdges>(b1, v[h]));
+          o[q - gone + below] = out_value<kEdges>(b1, v[h]);
         // positions up to q that stay, then the new values in the gap above q
         const uint32_t stay = q + 1 - gone - (removed ? 1u : 0u);
         const bool last = q + 1 == nn;
         for (uint32_t i = 0; i < D; ++i) {
           const uint32_t x = sm.scr[kSsNew + i];
           if (x > v[h] && (last || x < v[h + 1]))
-            store_out(o + (stay + i), out_value<kEdges>(b1, x));
+            o[stay + i] = out_value<kEdges>(b1, x);
           else if (q == s0 && x < v[h])
-            store_out(o + (s0 + i), out_value<kEdges>(b1, x));
+            o[s0 + i] = out_value<kEdges>(b1, x);
         }
       }
     }
