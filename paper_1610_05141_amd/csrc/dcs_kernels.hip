@@ -1082,7 +1082,8 @@ __device__ void find_repeats(uint32_t s0, uint32_t nn, const WordMap& m, const S
 // values, ascending.  Position p keeps its value v at p - (removed below p) +
 // (new values below v); a new value belongs right after the last position
 // whose value is smaller.  A full row without a removed position or a new
-// value in it moves as a whole, or stays.
+// value in it (for a leaf's first row, or below it) moves as a whole, or
+// stays.
 struct __attribute__((packed, aligned(8))) OutPair {
   uint64_t x, y;
 };
@@ -1108,7 +1109,7 @@ __device__ void rewrite_rows(uint64_t* o, uint64_t b1, uint32_t s0, uint32_t nn,
       const uint32_t vf = __builtin_amdgcn_readlane(v[0], kHalo);       // position r0
       const uint32_t vn = __builtin_amdgcn_readlane(v[0], 64 - kHalo);  // r0 + kRow
       const uint64_t at = __builtin_amdgcn_ballot_w64(
-          has && ((dpos >= r0 && dpos < r0 + kRow) || (dnew > vf && dnew < vn)));
+          has && ((dpos >= r0 && dpos < r0 + kRow) || (dnew < vn && (dnew > vf || r0 == s0))));
       if (at == 0) {
         const uint32_t shift = count(__builtin_amdgcn_ballot_w64(has && dnew < vf)) -
                                count(__builtin_amdgcn_ballot_w64(has && dpos < r0));
@@ -1774,6 +1775,9 @@ __device__ __forceinline__ void leaf_rare(lds_u32* lds, lds_u32* rec, uint64_t* 
   }
   const SortLeaf v = sort_leaf(L, out);
   if (what == kRareRepeats) {
+    // The second row pass writes places that other waves wrote in the first:
+    // their stores have to be done, not only issued, before the barrier.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     find_repeats<B>(v.s0, v.nn, v.m, sm);
     sort_sync<B>();
     const uint32_t reps = __builtin_amdgcn_readfirstlane(sm.scr[kSsDups]);

@@ -35,3 +35,17 @@ def test_many_leaves(ref, n, N, n0, variant):
     m.synchronize()
     want = g(n, N, 4, n0=n0)
     assert np.array_equal(got, want), first_mismatch(got, want)
+
+
+@pytest.mark.parametrize("n,N,n0", [(300, 5003, 4096), (1500, 60_013, 4096), (40, 1009, 4096)])
+def test_new_values_at_a_leaf_s_ends(ref, n, N, n0):
+    """Repairs of leaves that start at a line of the output, over enough seeds
+    for new values below the first and above the last one (each new value is
+    either with probability 1/n)."""
+    m = dcs()
+    announce(f"repairs at a leaf's ends: n={n} N={N}, 300 seeds")
+    for seed in range(300):
+        got = to_np_u64(m.sample(n, N, seed, n0=n0))
+        m.synchronize()
+        want = ref.sample(n, N, seed, n0=n0)
+        assert np.array_equal(got, want), f"seed {seed}: {first_mismatch(got, want)}"
