@@ -1,6 +1,7 @@
-"""Leaves whose values repeat cost little more than leaves whose values don't
-(GPU, times of one process's calls against each other, the least of several
-runs on each side)."""
+"""Leaves whose values repeat: they cost little more than leaves whose values
+don't (times of one process's calls against each other, the least of several
+runs on each side), and around the rules that choose how they are sampled they
+are the oracle's, bit for bit."""
 import time
 
 import pytest
@@ -87,3 +88,18 @@ def test_small_leaves_around_the_rules(ref, n, Ns):
     for (o, want), spec in zip(wants, specs):
         assert np.array_equal(got[o:o + n], want), (spec.N, spec.seed,
                                                     first_mismatch(got[o:o + n], want))
+
+
+# n^2 = 2 N and one less and more, where one launch changes to the other
+@pytest.mark.parametrize("n", [5, 8, 33, 200, 1024, 1025, 3000, 4094, 4095])
+def test_one_leaf_around_one_expected_repeat(ref, n):
+    import numpy as np
+    from tests.gpu_util import first_mismatch, to_np_u64
+    m = dcs()
+    for N in (n * n // 2 - 1, n * n // 2, n * n // 2 + 1):
+        for seed in range(3):
+            announce(f"one leaf around one repeat: n={n} N={N} seed={seed}")
+            got = to_np_u64(m.sample(n, N, seed, dense_ratio=2))
+            m.synchronize()
+            want = ref.sample(n, N, seed, dense_ratio=2)
+            assert np.array_equal(got, want), first_mismatch(got, want)
