@@ -502,19 +502,15 @@ __device__ __forceinline__ uint64_t out_value(uint64_t b1, V v) {
   return kEdges ? edge_pair(b1 - 1, v) : b1 + v;
 }
 
-// floor(x y / z) for a quotient below 2^41 and z below 2^61: the quick
-// quotient is off by one at most, and the remainder (below 2^63 in size, so
-// its low 64 bits hold it) says which way.
+// floor(x y / z) for a quotient below 2^41 and z at most 2^63 + 1: the quick
+// quotient is within 2^-3, so the integer nearest to it is the floor or one
+// above, and the remainder (at most 0.63 z in size, so its low 64 bits hold
+// it) says which.
 __device__ __forceinline__ uint64_t quick_muldiv(uint64_t x, uint64_t y, uint64_t z) {
   const double e = (static_cast<double>(x) * static_cast<double>(y)) *
                    quick_rcp(static_cast<double>(z));
-  uint64_t q = static_cast<uint64_t>(e);
-  const int64_t r = static_cast<int64_t>(x * y - q * z);
-  if (r < 0)
-    --q;
-  else if (r >= static_cast<int64_t>(z))
-    ++q;
-  return q;
+  const uint64_t q = static_cast<uint64_t>(e + 0.5);
+  return static_cast<int64_t>(x * y - q * z) < 0 ? q - 1 : q;
 }
 
 // One centred run's correction divided by delta (d2 = delta^2), with h =
@@ -642,7 +638,7 @@ __device__ __forceinline__ uint64_t hyp_core(uint64_t n, uint64_t M, uint64_t N,
     g.s = __builtin_fma(kD1, w, kD2);
     g.kcap = __builtin_fma(16.0, w, g.a);
     g.q = static_cast<double>(q);
-    g.on = N < (1ull << 60) && mu < 0x1p40;
+    g.on = N < (1ull << 63) && mu < 0x1p40;
     g.mode = g.on ? static_cast<double>(quick_muldiv(n + 1, M + 1, N + 2)) : 0.0;
   }
   return rou_first_accepted<kWave>(
@@ -745,7 +741,7 @@ __device__ __forceinline__ uint64_t binom_core(uint64_t n, uint64_t l, uint64_t 
     g.s = __builtin_fma(kD1, w, kD2);
     g.kcap = __builtin_fma(16.0, w, g.a);
     g.q = nd;
-    g.on = Nv < (1ull << 60) && mu < 0x1p40;
+    g.on = Nv < (1ull << 63) && mu < 0x1p40;
     g.mode = g.on ? static_cast<double>(quick_muldiv(n + 1, l, Nv)) : 0.0;
   }
   return rou_first_accepted<kWave>(
