@@ -602,6 +602,48 @@ __device__ __forceinline__ int rou_quick(const RouQuick& g, double u, double v, 
   return kRouUnsure;
 }
 
+// The defined steps of an attempt (rou_first_accepted's `exact`): the accepted
+// integer, or kRouNone.  Out of line: they are rare, and inlined their
+// registers cost the tree kernels a wave per SIMD (k_segments with 300000
+// segments 412 us inlined, 323 so).
+constexpr uint64_t kRouNone = ~0ull;
+__device__ __attribute__((noinline)) uint64_t hyp_exact(uint64_t n, uint64_t M, uint64_t N,
+                                                         double u, double v) {
+  const uint64_t q = n < M ? n : M;
+  const uint64_t rest = N - M - n;
+  const double pm = static_cast<double>(M) / static_cast<double>(N);
+  const double mu = static_cast<double>(n) * pm;
+  const double var =
+      (mu * (1.0 - pm)) * (static_cast<double>(N - n) / static_cast<double>(N - 1));
+  const double a = mu + 0.5;
+  const double w = __builtin_sqrt(var + 0.5);
+  const double s = kD1 * w + kD2;
+  const double x = a + (s * (v - 0.5)) / u;
+  const double kcap = floor(a + 16.0 * w);
+  uint64_t kmax = q + 1;
+  if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
+  if (x < 0.0 || x >= static_cast<double>(kmax)) return kRouNone;
+  const uint64_t k = static_cast<uint64_t>(floor(x));
+  const uint64_t mode = floor_muldiv(n + 1, M + 1, N + 2);
+  double T = 0.0;
+#pragma nounroll
+  for (int i = 0; i < 4; ++i) {
+    uint64_t ta = mode, tb = k;
+    if (i == 1) {
+      ta = M - mode;
+      tb = M - k;
+    } else if (i == 2) {
+      ta = n - mode;
+      tb = n - k;
+    } else if (i == 3) {
+      ta = rest + mode;
+      tb = rest + k;
+    }
+    T = T + lnfact_diff(ta, tb);  // 0.0 + the first term is that term
+  }
+  return rou_accept(u, T, 2.0 * log64(u)) ? k : kRouNone;
+}
+
 // Hypergeometric core for 1 <= n, M <= N/2.
 template <bool kWave>
 __device__ __forceinline__ uint64_t hyp_core(uint64_t n, uint64_t M, uint64_t N, Draws64& d) {
@@ -652,39 +694,9 @@ __device__ __forceinline__ uint64_t hyp_core(uint64_t n, uint64_t M, uint64_t N,
           z[3] = rd + up;
         });
       },
-      [&](double u, double v, uint64_t* out) {  // the defined steps
-        const double pm = static_cast<double>(M) / static_cast<double>(N);
-        const double mu = static_cast<double>(n) * pm;
-        const double var =
-            (mu * (1.0 - pm)) * (static_cast<double>(N - n) / static_cast<double>(N - 1));
-        const double a = mu + 0.5;
-        const double w = __builtin_sqrt(var + 0.5);
-        const double s = kD1 * w + kD2;
-        const double x = a + (s * (v - 0.5)) / u;
-        const double kcap = floor(a + 16.0 * w);
-        uint64_t kmax = q + 1;
-        if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
-        if (x < 0.0 || x >= static_cast<double>(kmax)) return false;
-        const uint64_t k = static_cast<uint64_t>(floor(x));
-        const uint64_t mode = floor_muldiv(n + 1, M + 1, N + 2);
-        double T = 0.0;
-#pragma nounroll
-        for (int i = 0; i < 4; ++i) {
-          uint64_t ta = mode, tb = k;
-          if (i == 1) {
-            ta = M - mode;
-            tb = M - k;
-          } else if (i == 2) {
-            ta = n - mode;
-            tb = n - k;
-          } else if (i == 3) {
-            ta = rest + mode;
-            tb = rest + k;
-          }
-          T = T + lnfact_diff(ta, tb);  // 0.0 + the first term is that term
-        }
-        *out = k;
-        return rou_accept(u, T, 2.0 * log64(u));
+      [&](double u, double v, uint64_t* out) {
+        *out = hyp_exact(n, M, N, u, v);
+        return *out != kRouNone;
       });
 }
 
@@ -708,6 +720,31 @@ __device__ __forceinline__ uint64_t hypergeometric(uint64_t n, uint64_t M, uint6
   if (flip_m) k = n1 - k;
   if (flip_n) k = M - k;
   return k;
+}
+
+__device__ __attribute__((noinline)) uint64_t binom_exact(uint64_t n, uint64_t l, uint64_t Nv,
+                                                           double u, double v) {
+  const uint64_t r = Nv - l;
+  const double pp = static_cast<double>(l) / static_cast<double>(Nv);
+  const double mu = static_cast<double>(n) * pp;
+  const double var = mu * (1.0 - pp);
+  const double a = mu + 0.5;
+  const double w = __builtin_sqrt(var + 0.5);
+  const double s = kD1 * w + kD2;
+  const double x = a + (s * (v - 0.5)) / u;
+  const double kcap = floor(a + 16.0 * w);
+  uint64_t kmax = n + 1;
+  if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
+  if (x < 0.0 || x >= static_cast<double>(kmax)) return kRouNone;
+  const uint64_t k = static_cast<uint64_t>(floor(x));
+  const uint64_t mode = floor_muldiv(n + 1, l, Nv);
+  const double lodds = log1p64(
+      static_cast<double>(static_cast<int64_t>(2 * l) - static_cast<int64_t>(Nv)) /
+      static_cast<double>(r));
+  double T = static_cast<double>(static_cast<int64_t>(k) - static_cast<int64_t>(mode)) * lodds;
+  T = T + lnfact_diff(mode, k);
+  T = T + lnfact_diff(n - mode, n - k);
+  return rou_accept(u, T, 2.0 * log64(u)) ? k : kRouNone;
 }
 
 // Binomial core for 1 <= l <= Nv - l.
@@ -754,28 +791,9 @@ __device__ __forceinline__ uint64_t binom_core(uint64_t n, uint64_t l, uint64_t 
           z[3] = rd;
         });
       },
-      [&](double u, double v, uint64_t* out) {  // the defined steps
-        const double pp = static_cast<double>(l) / static_cast<double>(Nv);
-        const double mu = static_cast<double>(n) * pp;
-        const double var = mu * (1.0 - pp);
-        const double a = mu + 0.5;
-        const double w = __builtin_sqrt(var + 0.5);
-        const double s = kD1 * w + kD2;
-        const double x = a + (s * (v - 0.5)) / u;
-        const double kcap = floor(a + 16.0 * w);
-        uint64_t kmax = n + 1;
-        if (kcap < static_cast<double>(kmax)) kmax = static_cast<uint64_t>(kcap);
-        if (x < 0.0 || x >= static_cast<double>(kmax)) return false;
-        const uint64_t k = static_cast<uint64_t>(floor(x));
-        const uint64_t mode = floor_muldiv(n + 1, l, Nv);
-        const double lodds = log1p64(
-            static_cast<double>(static_cast<int64_t>(2 * l) - static_cast<int64_t>(Nv)) /
-            static_cast<double>(r));
-        double T = static_cast<double>(static_cast<int64_t>(k) - static_cast<int64_t>(mode)) * lodds;
-        T = T + lnfact_diff(mode, k);
-        T = T + lnfact_diff(n - mode, n - k);
-        *out = k;
-        return rou_accept(u, T, 2.0 * log64(u));
+      [&](double u, double v, uint64_t* out) {
+        *out = binom_exact(n, l, Nv, u, v);
+        return *out != kRouNone;
       });
 }
 
