@@ -571,8 +571,8 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
 // it expects a repeat, as the leaves of k_leaf_once do (sort and repair / one
 // pass, us per call: 1000 values with 0.6 / 1.1 / 4 expected repeats 6.4 / 7.3
 // / 9.1 and 6.5 / 6.6 / 6.7; 3000 values 9.0 / 10.4 / 13.1 and 8.8 / 8.7 / 9.9;
-// 4095 values, for which the pass has no words to spare, 11.6 / 13.5 / 15.6
-// and 15.4 / 15.0 / 15.2).  Dense
+// 4095 values, for which the pass's 4096 words leave none to spare, 11.6 /
+// 13.5 / 15.6 and 15.4 / 15.0 / 15.2: from four repeats on).  Dense
 // leaves over more than 2^16 are left to the other kernels; profiled and
 // forced-grid calls keep the general launches.
 bool one_leaf(const DeviceCtx* c, const Instance& I, Leaf* leaf, bool* one_pass) {
@@ -587,7 +587,7 @@ bool one_leaf(const DeviceCtx* c, const Instance& I, Leaf* leaf, bool* one_pass)
     kind = dcs::kKindDense;
   } else {
     kind = dcs::kKindSparse;
-    *one_pass = I.n * I.n >= 2 * I.N;
+    *one_pass = I.n * I.n >= (I.n + 4 > dcs::kMaxN0 ? 8 : 2) * I.N;
   }
   *leaf = Leaf{};
   leaf->id = 1;  // the root's
