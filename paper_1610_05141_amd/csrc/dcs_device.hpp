@@ -603,11 +603,14 @@ __device__ __forceinline__ int rou_quick(const RouQuick& g, double u, double v, 
 }
 
 // The defined steps of an attempt (rou_first_accepted's `exact`): the accepted
-// integer, or kRouNone.  Out of line: they are rare, and inlined their
-// registers cost the tree kernels a wave per SIMD (k_segments with 300000
-// segments 412 us inlined, 323 so).
+// integer, or kRouNone.  Out of line where lanes share a deviate: there they
+// are rare, and inlined their registers cost those kernels a wave per SIMD
+// (k_segments with 300000 segments 412 us inlined, 323 so).  A lane alone
+// takes them inlined: some lane of its wave needs them in most splits with
+// means of a few tens (200001 values in leaves of 15, k_tree: 97 us, 102 by
+// call).
 constexpr uint64_t kRouNone = ~0ull;
-__device__ __attribute__((noinline)) uint64_t hyp_exact(uint64_t n, uint64_t M, uint64_t N,
+__device__ __forceinline__ uint64_t hyp_exact_steps(uint64_t n, uint64_t M, uint64_t N,
                                                          double u, double v) {
   const uint64_t q = n < M ? n : M;
   const uint64_t rest = N - M - n;
@@ -642,6 +645,9 @@ __device__ __attribute__((noinline)) uint64_t hyp_exact(uint64_t n, uint64_t M, 
     T = T + lnfact_diff(ta, tb);  // 0.0 + the first term is that term
   }
   return rou_accept(u, T, 2.0 * log64(u)) ? k : kRouNone;
+}
+__device__ __attribute__((noinline)) uint64_t hyp_exact(uint64_t n, uint64_t M, uint64_t N, double u, double v) {
+  return hyp_exact_steps(n, M, N, u, v);
 }
 
 // Hypergeometric core for 1 <= n, M <= N/2.
@@ -695,7 +701,7 @@ __device__ __forceinline__ uint64_t hyp_core(uint64_t n, uint64_t M, uint64_t N,
         });
       },
       [&](double u, double v, uint64_t* out) {
-        *out = hyp_exact(n, M, N, u, v);
+        *out = kWave ? hyp_exact(n, M, N, u, v) : hyp_exact_steps(n, M, N, u, v);
         return *out != kRouNone;
       });
 }
@@ -722,7 +728,7 @@ __device__ __forceinline__ uint64_t hypergeometric(uint64_t n, uint64_t M, uint6
   return k;
 }
 
-__device__ __attribute__((noinline)) uint64_t binom_exact(uint64_t n, uint64_t l, uint64_t Nv,
+__device__ __forceinline__ uint64_t binom_exact_steps(uint64_t n, uint64_t l, uint64_t Nv,
                                                            double u, double v) {
   const uint64_t r = Nv - l;
   const double pp = static_cast<double>(l) / static_cast<double>(Nv);
@@ -745,6 +751,9 @@ __device__ __attribute__((noinline)) uint64_t binom_exact(uint64_t n, uint64_t l
   T = T + lnfact_diff(mode, k);
   T = T + lnfact_diff(n - mode, n - k);
   return rou_accept(u, T, 2.0 * log64(u)) ? k : kRouNone;
+}
+__device__ __attribute__((noinline)) uint64_t binom_exact(uint64_t n, uint64_t l, uint64_t Nv, double u, double v) {
+  return binom_exact_steps(n, l, Nv, u, v);
 }
 
 // Binomial core for 1 <= l <= Nv - l.
@@ -792,7 +801,7 @@ __device__ __forceinline__ uint64_t binom_core(uint64_t n, uint64_t l, uint64_t 
         });
       },
       [&](double u, double v, uint64_t* out) {
-        *out = binom_exact(n, l, Nv, u, v);
+        *out = kWave ? binom_exact(n, l, Nv, u, v) : binom_exact_steps(n, l, Nv, u, v);
         return *out != kRouNone;
       });
 }
