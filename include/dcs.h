@@ -490,8 +490,8 @@ const char* dcs_status_string(int32_t status);
  * (0 = reset, 1 = tree split, 2 = leaf stage: all leaf kernels,
  * 3 = Bernoulli chunk, 4 = work-group leaf kernel of the sparse, with-
  * replacement and constant jobs, 5 = work-group leaf kernel of the dense jobs
- * with ranges above 2^16 (nothing is launched where there can be none),
- * 6 = one-wave-per-leaf
+ * with ranges above 2^16 (where there can be none nothing is launched: the
+ * call is counted, with no time), 6 = one-wave-per-leaf
  * kernel of the dense jobs with ranges up to 2^16, 7 = nothing any more (the
  * sampling kernels write edges themselves), 8 = the segment splits of
  * dcs_sample_segments, 9 / 10 / 11 = the count passes / the scan and

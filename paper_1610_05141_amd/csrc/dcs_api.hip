@@ -319,11 +319,13 @@ void release_timings() {
   g_timings.clear();
 }
 // kinds: 0 reset, 1 tree, 2 leaf stage (all leaf kernels), 3 Bernoulli,
-// 4 leaf kernel of the power-of-two list, 5 work-group leaf kernel of
-// the rest, 6 one-wave dense leaf kernel, 7 edge-index decoding, 8 splits
-// of the segments of an uneven universe, 9 / 10 / 11 whole-range
-// Algorithm B: count passes / scan and repair / write passes, 12 one-wave
-// leaf kernel of the small sparse and with-replacement leaves
+// 4 work-group leaf kernel of the sparse, with-replacement and constant jobs,
+// 5 work-group leaf kernel of the dense jobs above 2^16 (no time where nothing
+// is launched), 6 one-wave dense leaf kernel, 7 nothing, 8 splits of the
+// segments of an uneven universe, 9 / 10 / 11 whole-range Algorithm B: count
+// passes / scan and repair / write passes, 12 one-wave leaf kernel of the small
+// sparse and with-replacement leaves, 13 one-pass kernel of the sparse leaves
+// expected to repeat
 constexpr int kProfKinds = 14;
 double g_prof_ms[kProfKinds] = {};
 uint64_t g_prof_n[kProfKinds] = {};
@@ -448,6 +450,11 @@ void timing_end(hipStream_t s, Timing* t) {
   g_timings.push_back(*t);
 }
 
+// A stage that had nothing to launch: it counts, with no time.
+void timing_none(int kind) {
+  if (g_profile && ((g_prof_mask >> kind) & 1u)) g_prof_n[kind] += 1;
+}
+
 // Leaf kinds that no leaf of a single instance's tree can have except by a
 // deviation of its counts from their expectations by tens of standard
 // deviations; their kernels are then not launched and k_leaf_sort runs any
@@ -522,12 +529,13 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   e = dcs::launch_leaf_sort(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(sort_want), s, 0,
                             takes, edges);
   timing_end(s, &t4);
-  if (e == hipSuccess) {
+  if (e == hipSuccess && wide_dense) {
     timing_begin(5, s, &t5);
-    if (wide_dense)
-      e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 0,
-                                 edges);
+    e = dcs::launch_leaf_mixed(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, 0,
+                               edges);
     timing_end(s, &t5);
+  } else if (e == hipSuccess) {
+    timing_none(5);
   }
   Timing t13{};
   if (e == hipSuccess && !(takes & dcs::kTakesOnce)) {
