@@ -411,8 +411,10 @@ int32_t dcs_synchronize(void* stream);
  * A size class is (variant: 0 without, 1 with replacement; log2_n =
  * floor(log2 n), 0..63).  cut_bias is added to the depth at which the tree
  * kernels hand subtrees to threads (2^cut threads per instance);
- * leaf_wgs_per_cu is the number of leaf work-groups per compute unit (0 =
- * the kernel's occupancy, larger values are clamped to it).  Sample calls,
+ * leaf_wgs_per_cu is the number of leaf work-groups of 512 threads per compute
+ * unit (0 = the kernel's occupancy, larger values are clamped to it; where a
+ * leaf takes 256 threads, twice as many work-groups; the kernels that give a
+ * leaf one wave always fill the unit).  Sample calls,
  * batches and served requests take the entry of their class (a batch or a
  * served batch: the class of its total sample count for the leaf grid);
  * the DCS_CUT_BIAS and DCS_LEAF_GRID environment variables override the

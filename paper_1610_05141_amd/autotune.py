@@ -4,8 +4,8 @@ workload, its leaf size.
 Geometry never changes a sample (the sample is a function of (n, N, seed,
 n0, dense_ratio) only): for each size class (variant, floor(log2 n)) the
 tuner times the cut-depth bias of the tree kernels (the depth at which the
-recursion is handed to threads, Sec. 4.2's Algorithm P cut) and the number
-of leaf work-groups per compute unit, and keeps the fastest pair.
+recursion is handed to threads, Sec. 4.2's Algorithm P cut) with the leaf
+kernels at their occupancy, and keeps the fastest.
 
 The leaf size n0 does change the sample, so it is never applied behind the
 caller's back: for the classes (floor(log2 n), dense or sparse) of the
@@ -13,9 +13,10 @@ batched workload the tuner times n0 in {1024, 2048, 4096} and records the
 fastest; n0_for(n, N) returns the recorded value, which a caller passes with
 the instance (and an oracle check passes to the oracle).
 
-    python -m paper_1610_05141_amd.autotune [--out PATH] [--quick]
+    python -m paper_1610_05141_amd.autotune [--out PATH] [--quick] [--geometry-only]
 
-runs the sweeps on cuda:0 and writes the table with every measurement.
+runs the sweeps on cuda:0 and writes the table with every measurement
+(--geometry-only keeps the committed table's leaf sizes).
 apply_table() pushes the geometry into the library; the binding calls it
 when it loads the library.
 """
@@ -34,7 +35,13 @@ TABLE_PATH = os.path.join(_HERE, "tune_table.json")
 DEFAULT_N0 = 4096
 DENSE_RATIO = 16
 CUT_BIASES = (-2, -1, 0, 1, 2)
-LEAF_WGS = (1, 2, 3)
+# Leaf work-groups of 512 threads per compute unit: 3 is the leaf kernels'
+# occupancy.  Fewer gain 2 % at most, where a sample has less than a leaf per
+# work-group (2^19 of 2^37 34.0 us at 1, 34.9 at 3), and lose as soon as it has
+# more: 2^20 of 2^44 53.0 / 45.7 / 44.8 us at 1 / 2 / 3, 2^28 of 2^46 918 / 617 /
+# 538 us.  So they are not searched over.
+LEAF_WGS = (3,)
+SWEEPS = 5  # a pair's time is the least of so many
 N0_CHOICES = (1024, 2048, 4096)
 N_CLASSES = 64
 
@@ -131,10 +138,12 @@ def tune_geometry(classes=GEOMETRY_CLASSES, log=print):
         out = torch.empty(n, dtype=torch.int64, device="cuda")
         f = dcs.sample if variant == 0 else dcs.sample_replacement
         ms = {}
-        for cb in CUT_BIASES:
-            for w in LEAF_WGS:
-                dcs.tune_set(variant, k, cb, w)
-                ms[f"{cb},{w}"] = _time_ms(lambda: f(n, N, 7, out=out), dcs.synchronize)
+        for _ in range(SWEEPS):
+            for cb in CUT_BIASES:
+                for w in LEAF_WGS:
+                    dcs.tune_set(variant, k, cb, w)
+                    t = _time_ms(lambda: f(n, N, 7, out=out), dcs.synchronize)
+                    ms[f"{cb},{w}"] = min(t, ms.get(f"{cb},{w}", t))
         best = min(ms, key=ms.get)
         cb, w = (int(x) for x in best.split(","))
         dcs.tune_set(variant, k, cb, w)
@@ -191,6 +200,8 @@ def main(argv=None) -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--out", default=TABLE_PATH)
     ap.add_argument("--quick", action="store_true", help="a few classes only")
+    ap.add_argument("--geometry-only", action="store_true",
+                    help="keep the committed table's leaf sizes (they are part of its samples)")
     args = ap.parse_args(argv)
     if os.environ.get("DCS_CUT_BIAS") or os.environ.get("DCS_LEAF_GRID"):
         print("unset DCS_CUT_BIAS / DCS_LEAF_GRID: they override the geometry being tuned",
@@ -204,16 +215,24 @@ def main(argv=None) -> int:
     classes = GEOMETRY_CLASSES if not args.quick else GEOMETRY_CLASSES[::4]
     t0 = time.time()
     geometry = tune_geometry(classes)
-    leaf = tune_leaf_size(min_group=8 if not args.quick else 200)
+    if args.geometry_only:
+        old = load_table() or {}
+        leaf, leaf_date = old.get("leaf_size", []), old.get("leaf_size_date", old.get("date"))
+    else:
+        leaf = tune_leaf_size(min_group=8 if not args.quick else 200)
+        leaf_date = time.strftime("%Y-%m-%d %H:%M:%S")
     table = {
         "device": torch.cuda.get_device_name(0),
         "host": platform.node(),
         "date": time.strftime("%Y-%m-%d %H:%M:%S"),
-        "command": "python -m paper_1610_05141_amd.autotune" + (" --quick" if args.quick else ""),
+        "command": "python -m paper_1610_05141_amd.autotune" + (" --quick" if args.quick else "")
+                   + (" --geometry-only" if args.geometry_only else ""),
         "seconds": round(time.time() - t0, 1),
         "method": "wall-clock ms per call after one warm-up call, at least 3 calls and 25 ms; "
-                  "geometry keys are cut_bias,leaf_wgs_per_cu; default geometry is 0,3",
+                  f"geometry: the least of {SWEEPS} sweeps, "
+                  "keys are cut_bias,leaf_wgs_per_cu; default geometry is 0,3",
         "geometry": geometry,
+        "leaf_size_date": leaf_date,
         "leaf_size": leaf,
     }
     with open(args.out, "w") as f:

@@ -511,9 +511,15 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
                          ctl, redo, 0, s);
   timing_end(s, &t1);
   if (e != hipSuccess) return DCS_EHIP;
-  // work-groups of the 512-thread kernels, and of the sort kernel
+  // work-groups of the 512-thread kernels, and of the sort kernel, whose
+  // work-groups are half as large: twice as many, or as many as fit where the
+  // larger ones fill the unit
   uint64_t want = static_cast<uint64_t>(c->cus) * std::max<uint32_t>(1, leaf_wgs_per_cu);
-  uint64_t sort_want = static_cast<uint64_t>(c->cus) * std::max(1, c->sort_occupancy);
+  const uint32_t sort_occ = static_cast<uint32_t>(std::max(1, c->sort_occupancy));
+  uint64_t sort_want = static_cast<uint64_t>(c->cus) *
+                       (leaf_wgs_per_cu >= static_cast<uint32_t>(std::max(1, c->leaf_occupancy))
+                            ? sort_occ
+                            : std::min(sort_occ, 2 * leaf_wgs_per_cu));
   if (c->leaf_grid > 0) want = sort_want = static_cast<uint64_t>(c->leaf_grid);
   want = std::max<uint64_t>(1, std::min<uint64_t>(want, leaf_cap));
   sort_want = std::max<uint64_t>(1, std::min<uint64_t>(sort_want, leaf_cap));

@@ -88,7 +88,7 @@ unsigned int* error_word(DeviceCtx* c, void* stream);
 // dcs_tune_set; never changes a sample.
 struct Tune {
   int32_t cut_bias = 0;          // added to the Algorithm P cut depth
-  uint32_t leaf_wgs_per_cu = 0;  // leaf work-groups per compute unit, 0 = occupancy
+  uint32_t leaf_wgs_per_cu = 0;  // 512-thread leaf work-groups per compute unit, 0 = occupancy
 };
 constexpr uint32_t kTuneClasses = 64;
 // Entry for an instance of n samples (caller holds lock()).
@@ -109,8 +109,9 @@ int32_t device_ctx(DeviceCtx** out);
 // (`single` != NULL: store that one instance first); the kernels latch
 // errors at `err` (nullptr: the workspace's own control block); caller
 // holds lock().
-// Leaf work-groups: DCS_LEAF_GRID if set, else cus * leaf_wgs_per_cu (both
-// leaf kernels use it).
+// Leaf work-groups: DCS_LEAF_GRID if set, else cus * leaf_wgs_per_cu (twice as
+// many of the sort kernel's, which are half as large; the one-wave kernels take
+// one work-group per compute unit).
 // wide_dense: some instance's tree satisfies has_wide_dense.
 // edges: write the values as the vertex pairs of edge indices.
 // whole: an instance whose canonical tree holds every leaf of the launch
