@@ -524,6 +524,16 @@ int32_t dcs_profile_kinds(uint32_t mask);
  *   op 7: y_u64 = Bin(n, l/Nv) for node ids x_u64, params p0..p2 = n, l, Nv, p3 = seed
  *   op 8: y_u32[4i..4i+3] = Philox block of counter x_u32[4i..4i+3], key (p0, p1)
  *   op 9: y_f32 = U of the geometric skip for word x_u32
+ *   op 10: single-precision skips of words p0 .. p0 + 4 count - 1 (mod 2^32)
+ *          at the constant whose bits are p1, as the kernels read them off the
+ *          hardware logarithm: y_u64[0] += those that are not the defined
+ *          skip, y_u64[1] = the largest relative distance of the two
+ *          logarithms so far, as the bits of a double (x unused, not NULL)
+ *   op 11: double-precision skips of draws x_u64[0 .. 2 count - 1] at the
+ *          constant whose bits are p0, in the same way: y_u64[0] += those that
+ *          are not the defined skip, y_u64[1] = the largest absolute distance
+ *          of the two logarithms so far
+ *   op 12: y_f64 = the quick 1 / x_f64        op 13: y_f64 = the quick sqrt(x_f64)
  */
 int32_t dcs_debug_primitive(int32_t op, const void* x_dev, const void* x2_dev, void* y_dev,
                             uint64_t count, uint64_t p0, uint64_t p1, uint64_t p2, uint64_t p3,

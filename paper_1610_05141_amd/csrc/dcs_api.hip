@@ -1503,7 +1503,7 @@ int32_t dcs_profile_read(int32_t kind, double* total_ms, uint64_t* launches) {
 int32_t dcs_debug_primitive(int32_t op, const void* x_dev, const void* x2_dev, void* y_dev,
                             uint64_t count, uint64_t p0, uint64_t p1, uint64_t p2, uint64_t p3,
                             void* stream) {
-  if (op < 0 || op > 9 || (count > 0 && (x_dev == nullptr || y_dev == nullptr))) return DCS_EINVAL;
+  if (op < 0 || op > 13 || (count > 0 && (x_dev == nullptr || y_dev == nullptr))) return DCS_EINVAL;
   if ((op == 4 || op == 5) && count > 0 && x2_dev == nullptr) return DCS_EINVAL;
   return hip_status(dcs::launch_debug(op, x_dev, x2_dev, y_dev, count, p0, p1, p2, p3,
                                       static_cast<hipStream_t>(stream)));

@@ -3709,9 +3709,22 @@ __global__ __launch_bounds__(64) void k_wb_write(uint64_t N, uint64_t seed, uint
 // ---------------------------------------------------------------------------
 // Diagnostics kernel.
 // ---------------------------------------------------------------------------
+// o[0] += wrong, o[1] = the larger of itself and `most`, as bits.
+__device__ inline void debug_tally(unsigned long long* o, uint64_t wrong, double most) {
+  if (wrong != 0) atomicAdd(o, static_cast<unsigned long long>(wrong));
+  const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(most));
+  if (bits > __hip_atomic_load(o + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(o + 1, bits);
+}
+
 __global__ void k_debug(int op, const void* x, const void* x2, void* y, uint64_t count,
                         uint64_t p0, uint64_t p1, uint64_t p2, uint64_t p3) {
   const uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  __shared__ LogEntry tab[kLogEntries];
+  if (op == 11) {
+    for (uint32_t e = threadIdx.x; e < kLogEntries; e += blockDim.x) tab[e] = log_entry(e);
+    __syncthreads();
+  }
   if (i >= count) return;
   switch (op) {
     case 0: static_cast<double*>(y)[i] = log64(static_cast<const double*>(x)[i]); break;
@@ -3749,6 +3762,45 @@ __global__ void k_debug(int op, const void* x, const void* x2, void* y, uint64_t
     case 9:
       static_cast<float*>(y)[i] = geom_unit(static_cast<const uint32_t*>(x)[i]);
       break;
+    case 10: {
+      const float c = __uint_as_float(static_cast<uint32_t>(p1));
+      const uint32_t w0 = static_cast<uint32_t>(p0 + 4 * i);
+      const uint4 w = make_uint4(w0, w0 + 1, w0 + 2, w0 + 3);
+      uint32_t skip[4];
+      geom_skips32(w, c, skip);
+      uint64_t wrong = 0;
+      double most = 0.0;
+      for (uint32_t j = 0; j < 4; ++j) {
+        wrong += skip[j] != static_cast<uint32_t>(geom_skip32(w0 + j, c)) ? 1 : 0;
+        const double l = static_cast<double>(log32(geom_unit(w0 + j)));
+        const double q = static_cast<double>(__builtin_amdgcn_logf(
+            static_cast<float>(w0 + j + 1u) * 0x1p-32f)) * 0x1.62e42fefa39efp-1;
+        if (l != 0.0 && w0 + j != ~0u) most = __builtin_fmax(most, __builtin_fabs((q - l) / l));
+      }
+      debug_tally(static_cast<unsigned long long*>(y), wrong, most);
+      break;
+    }
+    case 11: {
+      const double c = __longlong_as_double(static_cast<long long>(p0));
+      const uint64_t* d = static_cast<const uint64_t*>(x) + 2 * i;
+      const uint4 w = make_uint4(static_cast<uint32_t>(d[0]), static_cast<uint32_t>(d[0] >> 32),
+                                 static_cast<uint32_t>(d[1]), static_cast<uint32_t>(d[1] >> 32));
+      double g[2];
+      geom_skips64(w, c, 0.5 - __builtin_fabs(c) * 0x1p-43, tab, g);
+      uint64_t wrong = 0;
+      double most = 0.0;
+      for (int j = 0; j < 2; ++j) {
+        const double l = log64(unit_open0(d[j]));
+        wrong += g[j] != __builtin_floor(l * c) ? 1 : 0;
+        most = __builtin_fmax(most, __builtin_fabs(geom_quick64(static_cast<uint32_t>(d[j]),
+                                                               static_cast<uint32_t>(d[j] >> 32),
+                                                               1.0, tab) - l));
+      }
+      debug_tally(static_cast<unsigned long long*>(y), wrong, most);
+      break;
+    }
+    case 12: static_cast<double*>(y)[i] = quick_rcp(static_cast<const double*>(x)[i]); break;
+    case 13: static_cast<double*>(y)[i] = quick_sqrt(static_cast<const double*>(x)[i]); break;
     default: break;
   }
 }
