@@ -728,9 +728,10 @@ int32_t sample_bernoulli(double p, uint64_t N, uint64_t seed, const dcs_params* 
   DeviceCtx* c;
   int32_t rc = device_ctx(&c);
   if (rc) return rc;
-  if (p == 0.0 || N == 0) {
-    return hip_status(hipMemsetAsync(count_dev, 0, sizeof(uint64_t), s));
-  }
+  // nothing to sample: a kernel, not a memset, writes the count (a memset's node
+  // in a captured graph may go wrong on later replays)
+  if (p == 0.0 || N == 0)
+    return hip_status(dcs::launch_bernoulli_fill(0, out_dev, 0, count_dev, edges, s));
   if (p == 1.0) return hip_status(dcs::launch_bernoulli_fill(N, out_dev, capacity, count_dev, edges,
                                                       s));
   const uint64_t chunk = bern_chunk_len(p, P.n0);

@@ -4058,7 +4058,10 @@ int wb_occupancy() {
 
 hipError_t launch_bernoulli_fill(uint64_t N, uint64_t* out, uint64_t capacity, uint64_t* count_dev,
                                  bool edges, hipStream_t stream) {
-  hipLaunchKernelGGL((edges ? k_bern_fill<true> : k_bern_fill<false>), dim3(1024), dim3(256), 0, stream, N, out, capacity, count_dev);
+  const uint64_t lim = N < capacity ? N : capacity;
+  const uint32_t blocks = static_cast<uint32_t>(lim >= 1024 * 256 ? 1024 : lim / 256 + 1);
+  hipLaunchKernelGGL((edges ? k_bern_fill<true> : k_bern_fill<false>), dim3(blocks), dim3(256), 0,
+                     stream, N, out, capacity, count_dev);
   return hipGetLastError();
 }
 
