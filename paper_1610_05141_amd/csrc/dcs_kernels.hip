@@ -19,8 +19,8 @@
 //                          (Sec. 4.7), restart on a short sample, removal of
 //                          the excess by Algorithm H semantics;
 //                  with replacement (Sec. 4.6): sorted draws, repeats kept.
-//                The leaf's sorted values leave LDS as coalesced
-//                non-temporal 64-bit stores.
+//                Whole lines of the output are stored non-temporally, what is
+//                less plainly, for the L2 to join.
 //   k_bern       Bernoulli sampling over fixed chunks (Sec. 4.7), chunk
 //                offsets by a decoupled look-back over an atomic ticket.
 //   k_debug      elementwise primitives for bit-exact tests.
@@ -1309,8 +1309,8 @@ __device__ void draw_missing(const Stream& st, uint32_t t, uint32_t D, uint32_t 
 }
 
 // What a key keeps from the counting pass to the scatter (recomputing it
-// there costs more issue slots than the registers do: the kernel is bound by
-// VALU issue and its LDS holds it at four waves per SIMD).
+// there costs more issue slots than the registers do: k_leaf_sort is bound by
+// VALU issue).
 struct KeyPlace {
   uint32_t word;   // byte offset of its counter word
   uint32_t shift;  // of its bucket's four bits
@@ -1680,10 +1680,10 @@ __device__ __forceinline__ void leaf_dense_wave(const Leaf& L, uint64_t* out, ui
   }
 }
 
-// Constant leaf of a with-replacement tree: N_v = 1, every draw is lo+1.
 // ---------------------------------------------------------------------------
-// Small sparse and with-replacement leaves, one wave per leaf.
+// Which kernel takes a job; constant leaves.
 // ---------------------------------------------------------------------------
+// Small sparse and with-replacement leaves: k_leaf_small.
 __device__ __forceinline__ bool small_by_wave(const Leaf& L) {
   const uint32_t kind = L.flags & 3u;
   return (kind == kKindSparse || kind == kKindWr) && L.nv <= kSmallMax;
@@ -1697,6 +1697,7 @@ __device__ __forceinline__ bool once_by_group(const Leaf& L) {
          static_cast<uint64_t>(L.nv) * L.nv >= 2 * L.Nv;
 }
 
+// Constant leaf of a with-replacement tree: N_v = 1, every draw is lo+1.
 template <int B>
 __device__ __forceinline__ void leaf_fill(const Leaf& L, uint64_t* out) {
   uint64_t* o = out + L.off;
@@ -2286,7 +2287,7 @@ __global__ __launch_bounds__(64 * kLeafWaves) void k_leaf_dense(const Leaf* __re
 }
 
 // Small sparse and with-replacement leaves of the back list, one wave per
-// leaf, sorted as in k_leaf_sort.  Bound by vector instructions (113 per 64
+// leaf: sorted as in k_leaf_sort, or marked (leaf_marked).  Bound by vector instructions (113 per 64
 // values with edges written, the edge's root a third of them).  2^28 edges of
 // 2^26 vertices, leaves of 512 values: 1360 us with values counted into 1024
 // word counters and sorting-network windows, 1260 with this sort, 980 with
@@ -2752,7 +2753,6 @@ __global__ void k_zero(Control* ctl, unsigned long long* status, uint64_t n,
 constexpr unsigned long long kFlagAgg = 1ull << 62;
 constexpr unsigned long long kFlagIncl = 2ull << 62;
 constexpr unsigned long long kValueMask = (1ull << 62) - 1;
-constexpr uint32_t kSpinLimit = 1u << 26;
 // Words per step of a look-back.  Status words are read past the L2 while all
 // other work-groups write and poll theirs, and what is read slows everyone:
 // 64 / 32 / 16 / 8 / 4 words took 1202 / 1172 / 1141 / 1090 / 1120 us for

@@ -102,8 +102,6 @@ hipError_t error_slots(unsigned int** out);
 
 constexpr unsigned kErrLeafCapacity = 1u;   // more leaves than the workspace holds
 constexpr unsigned kErrStackDepth = 2u;     // tree deeper than the planned stack
-constexpr unsigned kErrSpinLimit = 4u;      // Bernoulli look-back waited too long
-constexpr unsigned kErrLeafTooLarge = 8u;   // a leaf exceeds the kernel's LDS bound
 constexpr unsigned kErrRestartLimit = 16u;  // whole-range B: no attempt accepted
 
 constexpr uint64_t kMaxLeafJobs = 1ull << 31;  // keeps the two halves of leaf_counts apart
