@@ -2016,13 +2016,14 @@ __device__ __forceinline__ void leaf_marked(uint32_t* smem, const uint32_t* rec,
 // kTakesDense / kTakesSmall / kTakesOnce: this kernel runs them too).
 // round2: the second round's jobs, all of them but k_leaf_mixed's.
 // What bounds it: the energy and issue slots of its vector instructions.  On
-// n = 2^30 of 2^48 the vector units issue about three quarters of the time at
-// a clock that falls from 2.17 to 2.0 GHz as they are used better (the same
-// cycles take 532 or 585 us with equal counters), the LDS is in use half of
-// it, and without its stores it takes 0.2 ms less.  2.1 ms, 4.1 TB/s written;
-// the counting sort of values over 4096 counters with sorting-network
-// windows that this replaced took 2.88 ms (3.0 TB/s).  Ranges that are no
-// power of two: n = 2^28 of 286538054670896 1.05 ms per call against 2.26 ms.
+// n = 2^30 of 2^48 (44 of them per 64 values) the vector units issue two thirds
+// of the time at a clock that falls from 2.17 to 2.0 GHz as they are used
+// better (the same cycles take 532 or 585 us with equal counters), the LDS is
+// in use half of it, and without its stores it takes 0.2 ms less.  1.94 to 2.07
+// ms, 4.1 to 4.4 TB/s written; the counting sort of values over 4096 counters
+// with sorting-network windows that this replaced took 2.88 ms (3.0 TB/s).
+// Ranges that are no power of two: n = 2^28 of 286538054670896 1.02 ms per call
+// against 2.26 ms.
 // Measured choices (that call, the headline call): 2^13 buckets 1.05 / 2.28
 // ms, 2^14 (fewer leaves in flight, fewer rounds) 1.19 / 2.34 ms; six waves
 // per SIMD with some spills 1.05 / 2.28, five 1.09 / 2.42, four without
