@@ -5,7 +5,8 @@ Geometry never changes a sample (the sample is a function of (n, N, seed,
 n0, dense_ratio) only): for each size class (variant, floor(log2 n)) the
 tuner times the cut-depth bias of the tree kernels (the depth at which the
 recursion is handed to threads, Sec. 4.2's Algorithm P cut) with the leaf
-kernels at their occupancy, and keeps the fastest.
+kernels at their occupancy, and keeps the fastest that leaves the workspaces
+of allocation-free calls within their scratch.
 
 The leaf size n0 does change the sample, so it is never applied behind the
 caller's back: for the classes (floor(log2 n), dense or sparse) of the
@@ -113,6 +114,41 @@ def n0_for(n: int, N: int, table=None) -> int:
     return int(e["n0"]) if e else DEFAULT_N0
 
 
+def small_workspaces(variant: int, log2_n: int):
+    """The calls of size class log2_n (over universes of 2^32 to 2^62, a few
+    leaf sizes) whose workspace under the library's present table fits the
+    static scratch of allocation-free calls."""
+    from . import NOALLOC_SCRATCH_BYTES, workspace_size
+    return {(n, b, n0) for n in (1 << log2_n, 3 << log2_n >> 1, (2 << log2_n) - 1)
+            for b in range(max(32, log2_n + 1), 63) for n0 in (4096, 1024, 256, 64, 8)
+            if workspace_size(variant, n, 1 << b, n0=n0) <= NOALLOC_SCRATCH_BYTES}
+
+
+def allowed_biases(classes, table):
+    """{(variant, log2 n of a measured class): cut biases} for `classes`: a
+    deeper cut needs more stacks, so a bias is left out where a call of a class
+    that takes it would outgrow the allocation-free scratch that it fits with
+    `table`."""
+    import paper_1610_05141_amd as dcs
+    rows = geometry_rows({"geometry": [{"variant": v, "log2_n": k, "cut_bias": k,
+                                        "leaf_wgs_per_cu": 0} for v, k, _ in classes]})
+    dcs.tune_reset()
+    if table:
+        apply_table(table=table)
+    allowed = {(v, k): set(CUT_BIASES) for v, k, _ in classes}
+    for v, c, k, _ in rows:
+        fit = small_workspaces(v, c)
+        if not fit:
+            continue
+        before = dcs.tune_get(v, c)
+        for cb in sorted(allowed[v, k]):
+            dcs.tune_set(v, c, cb, 0)
+            if not fit <= small_workspaces(v, c):
+                allowed[v, k].discard(cb)
+        dcs.tune_set(v, c, *before)
+    return {key: sorted(biases) for key, biases in allowed.items()}
+
+
 # ---------------------------------------------------------------------------
 # sweeps (GPU)
 # ---------------------------------------------------------------------------
@@ -133,13 +169,15 @@ def tune_geometry(classes=GEOMETRY_CLASSES, log=print):
     import torch
     import paper_1610_05141_amd as dcs
     out_rows = []
+    biases = allowed_biases(classes, load_table())
+    dcs.tune_reset()
     for variant, k, N in classes:
         n = 1 << k
         out = torch.empty(n, dtype=torch.int64, device="cuda")
         f = dcs.sample if variant == 0 else dcs.sample_replacement
         ms = {}
         for _ in range(SWEEPS):
-            for cb in CUT_BIASES:
+            for cb in biases[variant, k]:
                 for w in LEAF_WGS:
                     dcs.tune_set(variant, k, cb, w)
                     t = _time_ms(lambda: f(n, N, 7, out=out), dcs.synchronize)
@@ -148,10 +186,10 @@ def tune_geometry(classes=GEOMETRY_CLASSES, log=print):
         cb, w = (int(x) for x in best.split(","))
         dcs.tune_set(variant, k, cb, w)
         row = {"variant": variant, "log2_n": k, "N": N, "cut_bias": cb, "leaf_wgs_per_cu": w,
-               "best_ms": ms[best], "default_ms": ms["0,3"], "ms": ms}
+               "best_ms": ms[best], "default_ms": ms.get("0,3", ms[best]), "ms": ms}
         out_rows.append(row)
         log(f"[tune] geometry variant={variant} n=2^{k}: cut_bias={cb} wgs={w} "
-            f"{ms[best]:.3f} ms (default {ms['0,3']:.3f})")
+            f"{ms[best]:.3f} ms (default {row['default_ms']:.3f})")
         del out
         torch.cuda.empty_cache()
     return out_rows
