@@ -468,7 +468,9 @@ void timing_none(int kind) {
 // 1024 < n_v < n0) exist only for n0 > 1025; when N >= n n0, the expected
 // count n N_v / N of such a leaf's range is at most n_v^2 / (2 n0) < n_v / 2,
 // so n_v lies more than n_v / 2 above it: over sqrt(n_v / 2) > 22 standard
-// deviations.
+// deviations.  When dense_ratio n >= 2 N such a leaf, sparse over more than
+// 1024 dense_ratio elements, holds less than half of the more than 2048 values
+// expected there: over 22 below.
 uint32_t mixed_takes(const Instance& I) {
   uint32_t forced = 0;
   while (ceil_div_pow2(I.N, forced) > kLeafRange) ++forced;
@@ -476,7 +478,8 @@ uint32_t mixed_takes(const Instance& I) {
   uint32_t takes = 0;
   if (I.variant == 1 || (I.n0 >= 1024 && n * 128u * I.dense_ratio < N)) takes |= dcs::kTakesDense;
   if (I.n0 >= 4096 && (I.n >> forced) >= 2ull * I.n0) takes |= dcs::kTakesSmall;
-  if (I.variant == 1 || I.n0 <= 1025 || n * I.n0 <= N) takes |= dcs::kTakesOnce;
+  if (I.variant == 1 || I.n0 <= 1025 || n * I.n0 <= N || n * I.dense_ratio >= 2 * N)
+    takes |= dcs::kTakesOnce;
   return takes;
 }
 
@@ -488,8 +491,8 @@ bool has_wide_dense(uint32_t variant, uint32_t n0, uint32_t dense_ratio) {
 int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Instance* single,
                           uint32_t n_inst, uint64_t threads, uint64_t top_threads,
                           uint64_t leaf_cap, uint32_t stack_depth, uint64_t* out, hipStream_t s,
-                          unsigned int* err, uint32_t leaf_wgs_per_cu, bool wide_dense,
-                          uint64_t* part_out, const Instance* whole, bool edges) {
+                          unsigned int* err, uint64_t values, uint32_t leaf_wgs_per_cu,
+                          bool wide_dense, uint64_t* part_out, const Instance* whole, bool edges) {
   if (leaf_cap >= dcs::kMaxLeafJobs) return DCS_ENOMEM;
   char* base = static_cast<char*>(ws);
   Control* ctl = reinterpret_cast<Control*>(base + L.ctl);
@@ -545,8 +548,12 @@ int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Ins
   }
   Timing t13{};
   if (e == hipSuccess && !(takes & dcs::kTakesOnce)) {
+    // each of its leaves holds more than 1024 values, and an idle work-group of
+    // its size costs its launch (768 of them 1.5 us more than 256)
+    const uint64_t once =
+        c->leaf_grid > 0 ? want : std::min<uint64_t>(want, values / (dcs::kSmallMax + 1) + 1);
     timing_begin(13, s, &t13);
-    e = dcs::launch_leaf_once(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(want), s, edges);
+    e = dcs::launch_leaf_once(leaves, leaf_cap, out, ctl, static_cast<uint32_t>(once), s, edges);
     timing_end(s, &t13);
   }
   // the one-wave leaf kernels: a work-group per compute unit
@@ -660,7 +667,7 @@ int32_t sample_tree(uint32_t variant, uint64_t n, uint64_t N, uint64_t seed, con
         dcs::launch_leaf_one(leaf, one_pass, out, static_cast<hipStream_t>(stream), edges));
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out, static_cast<hipStream_t>(stream),
-                           error_word(c, stream), leaf_wgs_for(c, variant, n),
+                           error_word(c, stream), n, leaf_wgs_for(c, variant, n),
                            has_wide_dense(variant, P.n0, P.dense_ratio), nullptr, nullptr, edges);
 }
 
@@ -877,7 +884,7 @@ int32_t dcs_sample_part(int32_t variant, uint64_t n, uint64_t N, uint64_t seed,
   I.part_cap = capacity;
   return run_tree_pipeline(c, ws, L, &I, 1, pl.threads, pl.top_threads, pl.leaf_cap,
                            pl.stack_depth, out_dev, static_cast<hipStream_t>(stream),
-                           error_word(c, stream),
+                           error_word(c, stream), np,
                            leaf_wgs_for(c, static_cast<uint32_t>(variant), np),
                            has_wide_dense(I.variant, P.n0, P.dense_ratio), count_rank_dev);
 }
@@ -958,7 +965,7 @@ int32_t dcs_sample_segments(uint64_t n, const uint64_t* lengths, uint64_t K, uin
   if (e != hipSuccess) return DCS_EHIP;
   if (n == 0) return DCS_OK;
   return run_tree_pipeline(c, ws, L, nullptr, static_cast<uint32_t>(K), tb, tt, leaf_cap,
-                           stack_depth, out_dev, s, error_word(c, stream),
+                           stack_depth, out_dev, s, error_word(c, stream), n,
                            leaf_wgs_for(c, 0, n), has_wide_dense(0, P.n0, P.dense_ratio));
 }
 
@@ -1168,7 +1175,7 @@ int32_t dcs_batch_run(dcs_batch* b, uint64_t* out_dev, int32_t use_graph, void* 
   unsigned int* err = error_word(c, stream);
   if (!use_graph || g_profile) {
     return run_tree_pipeline(c, b->ws, b->layout, nullptr, n_inst, b->threads, b->top_threads,
-                             b->leaf_cap, b->stack_depth, out_dev, s, err,
+                             b->leaf_cap, b->stack_depth, out_dev, s, err, b->total_out,
                              leaf_wgs_for(c, 0, b->total_out), b->wide_dense);
   }
   if (s == nullptr) return DCS_EINVAL;  // capture needs a real stream
@@ -1185,7 +1192,7 @@ int32_t dcs_batch_run(dcs_batch* b, uint64_t* out_dev, int32_t use_graph, void* 
     }
     if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) return DCS_EHIP;
     rc = run_tree_pipeline(c, b->ws, b->layout, nullptr, n_inst, b->threads, b->top_threads,
-                           b->leaf_cap, b->stack_depth, out_dev, s, err,
+                           b->leaf_cap, b->stack_depth, out_dev, s, err, b->total_out,
                            leaf_wgs_for(c, 0, b->total_out), b->wide_dense);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(s, &g);
@@ -1350,7 +1357,7 @@ int32_t dcs_online_next(dcs_online* o, uint64_t first, uint64_t count, uint64_t*
   whole.dense_ratio = o->P.dense_ratio;
   whole.variant = v;
   return run_tree_pipeline(c, ws, L, nullptr, n_inst, tb, tt, leaf_cap, stack_depth, out_dev, s,
-                           error_word(c, stream), leaf_wgs_for(c, v, total),
+                           error_word(c, stream), total, leaf_wgs_for(c, v, total),
                            has_wide_dense(v, o->P.n0, o->P.dense_ratio), nullptr, &whole);
 }
 

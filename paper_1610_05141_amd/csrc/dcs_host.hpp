@@ -112,6 +112,7 @@ int32_t device_ctx(DeviceCtx** out);
 // Leaf work-groups: DCS_LEAF_GRID if set, else cus * leaf_wgs_per_cu (twice as
 // many of the sort kernel's, which are half as large; the one-wave kernels take
 // one work-group per compute unit).
+// values: about how many the call writes (bounds grids only).
 // wide_dense: some instance's tree satisfies has_wide_dense.
 // edges: write the values as the vertex pairs of edge indices.
 // whole: an instance whose canonical tree holds every leaf of the launch
@@ -120,7 +121,7 @@ int32_t device_ctx(DeviceCtx** out);
 int32_t run_tree_pipeline(DeviceCtx* c, void* ws, const TreeLayout& L, const Instance* single,
                           uint32_t n_inst, uint64_t threads, uint64_t top_threads,
                           uint64_t leaf_cap, uint32_t stack_depth, uint64_t* out, hipStream_t s,
-                          unsigned int* err, uint32_t leaf_wgs_per_cu,
+                          unsigned int* err, uint64_t values, uint32_t leaf_wgs_per_cu,
                           bool wide_dense, uint64_t* part_out = nullptr,
                           const Instance* whole = nullptr, bool edges = false);
 // Whether an instance's tree can hold dense leaves over ranges above 2^16

@@ -870,10 +870,6 @@ constexpr uint32_t kSsClass = 16, kSsDups = 17, kSsNext = 18, kSsKeep = 20, kSsA
                    kSsDupPos = 32, kSsNew = 64, kSsWords = 96;
 constexpr uint32_t kOnes4 = 0x11111111u, kFours4 = 0x44444444u;
 
-// Back-list leaves (ranges that are no powers of two) of at most so many
-// values are k_leaf_small's.
-constexpr uint32_t kSmallMax = 1024;
-
 // The sort's sizes: threads per leaf, buckets, the largest leaf.
 template <int kThreads, uint32_t kBits, uint32_t kLargest>
 struct SortDims {

@@ -109,6 +109,9 @@ constexpr int kLeafBlock = 512;             // threads of a k_leaf_mixed / k_lea
 constexpr int kSortBlock = 256;             // threads of a k_leaf_sort work-group
 constexpr int kBernBlock = 256;             // threads of a Bernoulli work-group
 constexpr uint32_t kMaxN0 = 4096;           // largest n0 (LDS bound of a leaf)
+// Back-list leaves (ranges that are no powers of two) of at most so many
+// values are k_leaf_small's.
+constexpr uint32_t kSmallMax = 1024;
 constexpr uint64_t kFillPiece = 1ull << 16; // constant-fill leaves are cut to this
 // Sparse and with-replacement leaves of at most this many values are
 // sampled by the tree kernels themselves (no job record).

@@ -252,7 +252,7 @@ bool dcs_server::launch_batch() {
   }
   int32_t rc = dcs::host::run_tree_pipeline(c, sl->ws, L, nullptr, n_inst, threads, top_threads,
                                             leaf_cap, stack_depth,
-                                            reinterpret_cast<uint64_t*>(arena), sl->stream, nullptr,
+                                            reinterpret_cast<uint64_t*>(arena), sl->stream, nullptr, total_n,
                                             dcs::host::leaf_wgs_for(c, 0, total_n),
                                             dcs::host::has_wide_dense(0, dcs::kMaxN0, 16));
   if (rc == DCS_OK &&
